@@ -2,7 +2,9 @@
 
     python -m paper_1501_04706_amd.build
 
-The library is one translation unit (csrc/sqh_host.hip includes the kernels).
+Two translation units, compiled in parallel: csrc/sqh_host.hip (host driver,
+the streaming, general and engine kernels, which it includes) and
+csrc/sqh_local.hip (the workgroup-local kernels and their launches).
 Flags: -ffp-contract=off keeps every floating-point operation separately
 rounded, which the predicate error bounds assume; packed fp32 instructions
 are disabled for all device code.
@@ -30,7 +32,7 @@ def hipcc() -> str:
 
 def flags(extra=()):
     return [
-        f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
+        f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
         "-ffp-contract=off", "-fno-fast-math",
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
         "-Wall", "-Wno-unused-function", "-Wno-unused-variable", "-Wno-unused-but-set-variable",
@@ -39,20 +41,28 @@ def flags(extra=()):
     ]
 
 
+UNITS = ("sqh_host.hip", "sqh_local.hip")
+
+
 def build(verbose: bool = False, extra=()) -> str:
-    src = os.path.join(CSRC, "sqh_host.hip")
+    procs = []
+    for unit in UNITS:
+        obj = os.path.join(CSRC, unit.replace(".hip", ".o"))
+        cmd = [hipcc(), *flags(extra), "-c", "-o", obj, os.path.join(CSRC, unit)]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        procs.append((obj, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    done = [(obj, p.communicate()[0], p.returncode) for obj, p in procs]
+    for obj, out, rc in done:
+        # the host pass does not know the gfx target feature; that note is expected
+        lines = [l for l in out.splitlines() if "packed-fp32-ops" not in l and l.strip()]
+        if rc != 0:
+            raise RuntimeError("hipcc failed:\n" + "\n".join(lines))
+        if verbose and lines:
+            print("\n".join(lines))
     tmp = LIB + ".tmp"
-    cmd = [hipcc(), *flags(extra), "-o", tmp, src]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    out = (res.stdout or "") + (res.stderr or "")
-    # the host pass does not know the gfx target feature; that note is expected
-    lines = [l for l in out.splitlines() if "packed-fp32-ops" not in l and l.strip()]
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + "\n".join(lines))
-    if verbose and lines:
-        print("\n".join(lines))
+    subprocess.run([hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *[obj for obj, _, _ in done]],
+                   check=True)
     os.replace(tmp, LIB)
     return LIB
 

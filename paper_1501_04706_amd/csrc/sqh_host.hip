@@ -19,6 +19,7 @@
 #include "sqh_stream.hip"
 #include "sqh_engine.hip"
 #include "sqh_diag.hip"
+#include "sqh_local.hpp"
 
 using namespace sqh;
 
@@ -172,6 +173,7 @@ struct sqh_ctx {
     HullInfo* hinfo = nullptr;   // ... its info block
     uint32_t* hstats = nullptr;  // ... its counters
     int* herr = nullptr;         // ... its error word
+    LocalStatus* lstat = nullptr;  // pinned status the workgroup-local kernels write
     sqh_stats stats{};
     static constexpr int kMaxTune = 40;
     TuneEntry tune[kMaxTune];
@@ -524,6 +526,37 @@ void phase_times(const HullInfo& hi, sqh_stats& S)
     }
 }
 
+// The counters and return code of a call that the workgroup-local kernels
+// finished (their status is in pinned memory; the stream is synchronised).
+int collect_local(sqh_ctx* ctx, int64_t N, int64_t out_cap, int64_t* h_total)
+{
+    const LocalStatus& L = *ctx->lstat;
+    sqh_stats& S = ctx->stats;
+    S = sqh_stats{};
+    S.points = N;
+    S.passes = L.passes;
+    S.first_survivors = L.first_v;
+    for (int p = 0; p < L.passes && p < kLocalStatPasses; ++p) {
+        S.survivors_total += L.pass_v[p];
+        S.max_segments = std::max<int64_t>(S.max_segments, L.pass_s[p]);
+        if (p < SQH_MAX_TIMED_PASSES) {
+            S.pass_points[p] = L.pass_v[p];
+            S.pass_segments[p] = L.pass_s[p];
+        }
+    }
+    S.orient_evals = L.orient;
+    S.orient_exact = L.orient_exact;
+    S.cmp_exact = L.cmp_exact;
+    S.hull_size = L.h;
+    S.prefilter_points = -1;
+    S.sorted_points = -1;
+    S.ms_total = S.ms_kernel = (double)(L.t1 - L.t0) * 1e-5;  // 100 MHz clock
+    if (h_total) *h_total = L.h;
+    if (L.err & (kErrNonFinite | kErrBounds)) return SQH_EINVAL;
+    if (L.err) return SQH_EDEVICE;
+    return L.h > out_cap ? SQH_ECAPACITY : SQH_OK;
+}
+
 int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const int64_t* d_set_off, int32_t* d_out,
               int64_t* d_out_off, int64_t out_cap, int64_t* h_total, void* d_ws, size_t ws_bytes, hipStream_t st,
               const TuneEntry& tu)
@@ -532,6 +565,19 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
     int reset_grid = 1;
     int rc = setup(ctx, d_xy, N, nsets, d_set_off, d_out, d_out_off, out_cap, d_ws, ws_bytes, tu, a, reset_grid);
     if (rc != SQH_OK) return rc;
+    // a small set in plain mode: one workgroup, its points in LDS. Up to
+    // kLocalPoints points in every precision mode; more, up to kLocalMax,
+    // where the static float32 certificates may be used (the sieve's)
+    if (nsets == 1 && !d_set_off && !a.prefilter && !a.sorted && !ctx->trace &&
+        (N <= kLocalPoints || (N <= kLocalMax && a.line_ok && !a.fp64))) {
+        LocalArgs l{a.xy, (int)N, d_out, out_cap, nullptr, a.fp64, a.line_ok, ctx->lstat};
+        ctx->nl = 0;
+        if (time_open(ctx, "k_local_one", st) != SQH_OK) return SQH_EDEVICE;
+        HIP_OK(launch_local_one(l, st));
+        if (time_close(ctx, "k_local_one", st) != SQH_OK) return SQH_EDEVICE;
+        HIP_OK(hipStreamSynchronize(st));
+        if (!ctx->lstat->left) return collect_local(ctx, N, out_cap, h_total);
+    }
     if (!a.stream) {
         rc = enqueue(ctx, a, reset_grid, tu.grid, tu.sgrid, st);
         if (rc != SQH_OK) return rc;
@@ -784,7 +830,8 @@ int sqh_create(sqh_ctx** out, int device)
     if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->evk) != hipSuccess ||
         hipEventCreate(&c->ev1) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&c->hstatus), status_offsets().bytes, hipHostMallocDefault) !=
-            hipSuccess) {
+            hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&c->lstat), sizeof(LocalStatus), hipHostMallocDefault) != hipSuccess) {
         sqh_destroy(c);
         return SQH_EDEVICE;
     }
@@ -807,6 +854,7 @@ void sqh_destroy(sqh_ctx* c)
     if (c->evk) (void)hipEventDestroy(c->evk);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
     if (c->hstatus) (void)hipHostFree(c->hstatus);
+    if (c->lstat) (void)hipHostFree(c->lstat);
     delete c;
 }
 

@@ -1,0 +1,278 @@
+// Sieve of a point set by a polygon of its own points (device code, gfx950).
+//
+// The paper's first mode (section 4.2) drops the points inside a polygon of
+// extreme points before the first split. Here the polygon is the hull of a
+// strided sample, and its interior is tabulated as vertical slabs: slab b
+// covers the x that map to b and holds a y interval such that every point of
+// the slab with y strictly inside it lies in the polygon and is none of its
+// vertices' positions, hence is no hull vertex of the set (a strict hull
+// vertex inside the polygon is at a vertex of it, and copies of a polygon
+// vertex stay: they decide the lowest index). A point costs one subtraction,
+// one product, a conversion, one 8-byte LDS read and two comparisons.
+#pragma once
+#include "sqh_solve.hpp"
+
+namespace sqh {
+
+constexpr int kSetDense = -1;  // solve_set: too many vertices for one workgroup's LDS
+constexpr int kSetBad = -2;    // ... a non-finite coordinate
+
+struct Slabs {
+    float x0, scale;  // slab of x: (x - x0) * scale, truncated, at most last
+    uint32_t last;
+};
+
+__device__ __forceinline__ bool slab_inside(const Slabs& s, const float2* bins, float x, float y)
+{
+    const float f = (x - s.x0) * s.scale;
+    // (the conversion takes negative values and NaN to 0, large ones to the top)
+    const uint32_t b = min(__float2uint_rz(f), s.last);
+    const float2 v = bins[b];
+    return (y > v.x) & (y < v.y);
+}
+
+// largest float <= v / smallest float >= v
+__device__ __forceinline__ float down32(double v)
+{
+    const float f = (float)v;
+    return (double)f > v ? nextafterf(f, -INFINITY) : f;
+}
+__device__ __forceinline__ float up32(double v)
+{
+    const float f = (float)v;
+    return (double)f < v ? nextafterf(f, INFINITY) : f;
+}
+
+// Slabs of the convex polygon L.ring[0 .. h) (counter-clockwise from its
+// lexicographic minimum) into bins[0 .. NB) (L.bins or another array that
+// the solve does not use). `kb` is one LDS word. Ends with a barrier.
+//
+// Slabs 0 and NB - 1 reach past the polygon's x range and stay empty; they
+// cover almost none of it (2^-6 of a slab's width). The x of slab b lie in
+// [x0 + b w (1 - 2^-20), x0 + (b + 1) w (1 + 2^-20)], w = 1 / scale (two
+// float32 roundings move the quotient by less than 2^-22), widened by the
+// rounding of the evaluation here (2^-48 |x0|). The lower chain is convex
+// and the upper one concave, so their values at the two ends bound them on
+// the slab; the evaluation in float64 errs by less than 2^-49 max |y|, and
+// the interval is narrowed by 2^-40 max |y| before it is rounded inwards.
+template <int T, int P>
+__device__ __forceinline__ Slabs build_slabs(const SolveLds<P>& L, int h, float2* bins, int NB, int* kb)
+{
+    const int t = (int)threadIdx.x;
+    auto pt = [&](int r) { return L.xy[L.ring[r >= h ? r - h : r]]; };
+    for (int r = t; r < h; r += T) {
+        const float2 p = pt(r), q = pt(r + 1), o = pt(r + h - 1);
+        const bool after = (p.x > q.x || (p.x == q.x && p.y > q.y)) && (p.x > o.x || (p.x == o.x && p.y > o.y));
+        if (after) *kb = r;  // the lexicographic maximum (one local maximum on a convex ring)
+    }
+    lds_barrier();
+    const int kB = *kb;
+    const float2 A = pt(0);
+    const float xa = A.x, xb = h > 1 ? pt(kB).x : xa;
+    const float ext = xb - xa;
+    Slabs s;
+    s.last = (uint32_t)(NB - 1);
+    s.scale = ((float)(NB - 2) + 0x1p-5f) / ext;
+    const bool ok = h >= 3 && ext > 0x1p-100f && ext < 0x1p100f;
+    if (!ok) {
+        s.scale = 0.0f;
+        s.x0 = 0.0f;
+    } else {
+        s.x0 = (float)((double)xa - (1.0 - 0x1p-6) / (double)s.scale);
+    }
+    const double w = ok ? 1.0 / (double)s.scale : 0.0, x0 = (double)s.x0, ex = fabs(x0) * 0x1p-48;
+    for (int b = t; b < NB; b += T) {
+        float2 v = make_float2(INFINITY, -INFINITY);
+        const double xl = x0 + (double)b * w * (1.0 - 0x1p-20) - ex, xr = x0 + (double)(b + 1) * w * (1.0 + 0x1p-20) + ex;
+        if (ok && xl >= (double)xa && xr < (double)xb) {
+            // the last node of the lower chain (0 .. kB) at or left of xl and
+            // of xr, the last node of the upper chain (kB .. h) at or right of
+            // them: four binary searches in step, their LDS reads together
+            int l[4] = {0, 0, kB, kB}, u[4] = {kB, kB, h, h};
+            for (int k = max(kB, h - kB); k > 1; k = (k + 1) >> 1) {
+                float mx[4];
+                int m[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) m[e] = (l[e] + u[e]) >> 1;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mx[e] = pt(m[e]).x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double x = (e & 1) ? xr : xl;
+                    const bool go = (e < 2) ? ((double)mx[e] <= x) : ((double)mx[e] >= x);
+                    const bool more = u[e] - l[e] > 1;
+                    l[e] = (more & go) ? m[e] : l[e];
+                    u[e] = (more & !go) ? m[e] : u[e];
+                }
+            }
+            double lo = -INFINITY, hi = INFINITY, my = 0.0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float2 p = pt(l[e]), q = pt(l[e] + 1);
+                const double x = (e & 1) ? xr : xl, dx = (double)q.x - (double)p.x;
+                const double y = dx == 0.0 ? (double)p.y
+                                           : (double)p.y + (x - (double)p.x) * ((double)q.y - (double)p.y) / dx;
+                my = fmax(my, fmax(fabs((double)p.y), fabs((double)q.y)));
+                if (e < 2) lo = fmax(lo, y);
+                else hi = fmin(hi, y);
+            }
+            const double m = my * 0x1p-40 + 0x1p-160;
+            v.x = up32(lo + m);
+            v.y = down32(hi - m);
+        }
+        bins[b] = v;
+    }
+    lds_barrier();
+    return s;
+}
+
+// Points i * n / m, i = 0 .. m - 1 (m <= P; all of them if m == n) into
+// positions 0 .. m - 1. Sets L.bad on a non-finite coordinate. Returns m.
+template <int T, int P>
+__device__ __forceinline__ int load_points(SolveLds<P>& L, const float2* xy, int n, int m)
+{
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < P / T; ++r) {
+        const int i = (int)threadIdx.x + T * r;
+        if (i < m) {
+            const int q = m == n ? i : (int)((long long)i * n / m);
+            const float2 v = gld(xy + q);
+            bad |= !((int)isfinite(v.x) & (int)isfinite(v.y));
+            L.xy[i] = v;
+            L.id[i] = q;
+        }
+    }
+    if (__ballot(bad) && lane_id() == 0) L.bad = 1;
+    lds_barrier();
+    return m;
+}
+
+// The hull of a set of n points: its ring in L.ring[0 .. h) (positions; L.id
+// gives the indices). Returns h, kSetDense (more than a quarter of the sample,
+// or more than P / 2 collected points, are vertices of their hull: nothing is
+// written) or kSetBad.
+//
+// Up to P points are solved as they are. A larger set is streamed past the
+// slabs of its sample's hull; the points left are collected in LDS. Should
+// they not fit, the collected points are replaced by their hull, whose slabs
+// then sieve the rest.
+template <int T, int P>
+__device__ __forceinline__ int solve_set(SolveLds<P>& L, const float2* xy, int n, bool f64, Counters& ctr, SolveStats* st)
+{
+    constexpr int U = 8;  // points per thread and step of the stream
+    __shared__ int s_kb;
+    __shared__ int s_tot[3];
+    const int t = (int)threadIdx.x;
+    if (n == 0) return 0;
+    // the sample: a sixteenth of the set, at least T points (a larger one
+    // sieves better but its own hull takes longer)
+    int cnt = load_points<T, P>(L, xy, n, n <= P ? n : min(P, max(T, n >> 4)));
+    bool fin = n <= P, first = true;
+    int pos = 0;
+    for (;;) {
+        if (L.bad) return kSetBad;
+        const int h = solve<T, P>(L, cnt, true, 0, 0, 0, f64, ctr, fin ? st : nullptr);
+        if (fin) return h;
+        // about h / cnt of the points would pass the sieve: a set that keeps
+        // more than a quarter (a ring of points) is not for it
+        if (4 * h > cnt && (first || h > P / 2)) return kSetDense;
+        const Slabs sl = build_slabs<T, P>(L, h, L.bins, T, &s_kb);
+        if (first) {
+            // the sample's vertices come back with the stream
+            first = false;
+            cnt = 0;
+        } else {
+            float2 v[P / 2 / T];
+            int id[P / 2 / T];
+#pragma unroll
+            for (int r = 0; r < P / 2 / T; ++r) {
+                const int i = t + T * r;
+                if (i < h) { v[r] = L.xy[L.ring[i]]; id[r] = L.id[L.ring[i]]; }
+            }
+            lds_barrier();
+#pragma unroll
+            for (int r = 0; r < P / 2 / T; ++r) {
+                const int i = t + T * r;
+                if (i < h) { L.xy[i] = v[r]; L.id[i] = id[r]; }
+            }
+            cnt = h;
+        }
+        if (t < 3) s_tot[t] = 0;
+        lds_barrier();
+        int k = 0;
+        bool small = false, bad = false;
+        float2 nv[U];  // the next step's points, loaded a step ahead
+        auto fetch = [&](int at) {
+            if (at + T * U <= n) {
+                // one uniform base per row, the same lane offset
+#pragma unroll
+                for (int j = 0; j < U; ++j) nv[j] = gld(xy + at + T * j + t);
+            } else {
+#pragma unroll
+                for (int j = 0; j < U; ++j) nv[j] = gld(xy + min(at + t + T * j, n - 1));
+            }
+        };
+        fetch(pos);
+        while (pos < n) {
+            // one step: U rows of T points, or one row where U might not fit
+            const int u = small ? 1 : U;
+            float2 v[U];
+            uint32_t keep = 0u;
+#pragma unroll
+            for (int j = 0; j < U; ++j) v[j] = nv[j];
+            fetch(min(pos + T * u, n - 1));
+            int wc = 0;
+#pragma unroll
+            for (int j = 0; j < U; ++j) keep |= (uint32_t)!slab_inside(sl, L.bins, v[j].x, v[j].y) << j;
+            if (small || pos + T * U > n) {
+#pragma unroll
+                for (int j = 0; j < U; ++j)
+                    if (j >= u || pos + t + T * j >= n) keep &= ~(1u << j);
+            }
+            if (__ballot(keep != 0u)) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    const bool kp = (keep >> j) & 1u;
+                    // (a non-finite coordinate is inside no slab)
+                    bad |= kp & !((int)isfinite(v[j].x) & (int)isfinite(v[j].y));
+                    wc += __popcll(__ballot(kp));
+                }
+            }
+            int base = 0;
+            if (lane_id() == 0 && wc) base = atomicAdd(&s_tot[k], wc);
+            base = __builtin_amdgcn_readfirstlane(base);
+            lds_barrier();
+            const int tot = s_tot[k];
+            if (t == 0) s_tot[k == 0 ? 2 : k - 1] = 0;  // (last read before this barrier, next used after the next one)
+            k = k == 2 ? 0 : k + 1;
+            if (cnt + tot > P) {  // (uniform)
+                if (small) break;
+                small = true;
+                fetch(pos);
+                continue;
+            }
+            int w = cnt + base;
+            if (wc) {
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const bool kp = (keep >> j) & 1u;
+                const uint64_t M = __ballot(kp);
+                if (kp) {
+                    const int d = w + bits_below(M);
+                    L.xy[d] = v[j];
+                    L.id[d] = pos + t + T * j;
+                }
+                w += (int)__popcll(M);
+            }
+            }
+            cnt += tot;
+            pos += T * u;
+        }
+        if (__ballot(bad) && lane_id() == 0) L.bad = 1;
+        fin = pos >= n;
+        lds_barrier();
+    }
+}
+
+}  // namespace sqh
