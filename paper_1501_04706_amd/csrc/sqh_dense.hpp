@@ -1,0 +1,299 @@
+// Rings of points (device code, gfx950): sets of which a large part are hull
+// vertices, so that no polygon sieves them.
+//
+// K vertices v_0 .. v_{K-1} of the sample's hull, evenly spaced along it, cut
+// the plane into K wedges seen from a centre c strictly inside their polygon.
+// A point of wedge k belongs to pocket k if it is strictly right of v_k ->
+// v_{k+1}; the others lie in the triangle c v_k v_{k+1}, and are no hull
+// vertices unless they are copies of v_k (whose lowest index is kept).
+//
+// Most of a ring's points survive most passes of QuickHull, so a pocket is
+// solved by the sort-then-remove of the paper's section 3 instead: a wave
+// sorts its points by angle about c, exactly, and then removes, in rounds and
+// all at once, every point that is not strictly convex between its current
+// neighbours. Such a point lies in the triangle of c and the two neighbours,
+// points of the set, so it is no hull vertex whatever else goes in the same
+// round (copies are removed first). The pockets' chains in order form a
+// polygon that is star-shaped about c; the same rounds over all of it leave a
+// star-shaped polygon with only strictly convex nodes, which is convex: the
+// hull. 150 points take a wave about 1000 instructions, the passes 6000.
+#pragma once
+#include "sqh_solve.hpp"
+
+namespace sqh {
+
+constexpr int kDenseMaxK = 1024;   // pockets of one set
+constexpr int kDenseTarget = 150;  // points per pocket aimed at: most pockets fit a wave's 254 (larger ones go to larger solvers)
+
+// One pocket: its points are slots [off, off + len) of the pocket array
+// (three words each: x, y, index); once solved, the first len of them are its
+// nodes, v_k first.
+struct Pocket {
+    float ax, ay, bx, by;    // v_k, v_{k+1}
+    int aid, off, len, ring;  // index of v_k; its ring
+};
+// A ring of pockets [t0, t0 + k).
+struct DenseSet {
+    int set, t0, k, pad;
+    float cx, cy;  // the centre
+    int pad2[2];
+};
+
+struct DenseLds {
+    float2 v[kDenseMaxK];  // the vertices
+    float2 d[kDenseMaxK];  // fl(v - c)
+    int id[kDenseMaxK];
+    int cnt[kDenseMaxK], cur[kDenseMaxK];
+    float2 c;
+    int half;   // first vertex more than half a turn after v_0
+    int bad;
+};
+
+// Chooses the vertices and the centre from the ring L.ring[0 .. h) of a
+// sample (h >= 8 K >= 16). D must not overlap L.xy, L.id or L.ring.
+// Returns false if the centre is not certified inside (then nothing is usable).
+template <int T, int P>
+__device__ __forceinline__ bool dense_build(const SolveLds<P>& L, int h, int K, DenseLds& D)
+{
+    const int t = (int)threadIdx.x;
+    for (int k = t; k < K; k += T) {
+        const int r = L.ring[(int)((long long)k * h / K)];
+        D.v[k] = L.xy[r];
+        D.id[k] = L.id[r];
+        D.cnt[k] = 0;
+    }
+    if (t == 0) {
+        const float2 p = L.xy[L.ring[0]], q = L.xy[L.ring[h / 3]], r = L.xy[L.ring[2 * h / 3]];
+        D.c.x = (float)(((double)p.x + (double)q.x + (double)r.x) / 3.0);
+        D.c.y = (float)(((double)p.y + (double)q.y + (double)r.y) / 3.0);
+        D.half = K;
+        D.bad = 0;
+    }
+    lds_barrier();
+    for (int k = t; k < K; k += T) {
+        const float2 c = D.c, v = D.v[k], w = D.v[k + 1 < K ? k + 1 : 0];
+        D.d[k] = make_float2(v.x - c.x, v.y - c.y);
+        if (orient_exact(v.x, v.y, w.x, w.y, c.x, c.y) <= 0) D.bad = 1;
+        if (k > 0 && orient_exact(c.x, c.y, D.v[0].x, D.v[0].y, v.x, v.y) < 0) atomicMin(&D.half, k);
+    }
+    lds_barrier();
+    return D.bad == 0;
+}
+
+// The wedge of p by rounded cross products (off by one at most near a ray).
+__device__ __forceinline__ int wedge_guess(const DenseLds& D, int K, float px, float py)
+{
+    const float2 c = D.c;
+    const float x = px - c.x, y = py - c.y;
+    const float2 d0 = D.d[0];
+    const bool first = d0.x * y - d0.y * x >= 0.0f;
+    int lo = first ? 0 : D.half - 1, hi = first ? D.half : K;  // the last ray at or before p is in [lo, hi)
+    const int steps = 32 - __clz(max(D.half, K - D.half + 1));
+    for (int s = 0; s < steps; ++s) {
+        const int m = (lo + hi) >> 1;
+        const float2 d = D.d[m];
+        const bool after = d.x * y - d.y * x >= 0.0f;
+        const bool more = hi - lo > 1;
+        lo = (more & after) ? m : lo;
+        hi = (more & !after) ? m : hi;
+    }
+    return lo;
+}
+
+// Pocket of p: k if p is strictly right of v_k -> v_{k+1} in wedge k, else -1.
+// `id` joins v_k's copies if p is one.
+__device__ __forceinline__ int pocket_of(DenseLds& D, int K, float px, float py, int id, Counters& ctr)
+{
+    int k = wedge_guess(D, K, px, py);
+    const float2 c = D.c;
+    int n = k + 1 < K ? k + 1 : 0;
+    float2 v = D.v[k], w = D.v[n];
+    const Orient32 o0 = orient32p(c.x, c.y, v.x, v.y, px, py), o1 = orient32p(c.x, c.y, w.x, w.y, px, py);
+    const Orient32 oe = orient32p(v.x, v.y, w.x, w.y, px, py);
+    const bool sure = (o0.d > o0.es) & (o1.d < -o1.es) & (fabsf(oe.d) > oe.es);
+    int s = oe.d < 0.0f ? k : -1;
+    ctr.orient += 3;
+    if (__ballot(!sure)) {
+        if (!sure) {
+            // the exact wedge: at or after ray k, before ray k + 1 (the guess
+            // is at most a few wedges off; p = c belongs to none)
+            ctr.orient_exact += 3;
+            int tries = 0;
+            bool in = false;
+            for (; tries <= K; ++tries) {
+                v = D.v[k];
+                n = k + 1 < K ? k + 1 : 0;
+                w = D.v[n];
+                const int a = orient_exact(c.x, c.y, v.x, v.y, px, py), b = orient_exact(c.x, c.y, w.x, w.y, px, py);
+                in = a >= 0 && b < 0;
+                if (in) break;
+                // (a wedge is less than half a turn wide: c is strictly inside the polygon)
+                if (a < 0) k = k > 0 ? k - 1 : K - 1;
+                else k = n;
+            }
+            s = -1;
+            if (in) {
+                if (px == v.x && py == v.y) atomicMin(&D.id[k], id);
+                else if (orient_exact(v.x, v.y, w.x, w.y, px, py) < 0) s = k;
+            }
+        }
+    }
+    return s;
+}
+
+// Exact order about c of two points of one wedge: -1 if p comes before q. On
+// one ray the nearer point comes first, copies by index.
+__device__ __forceinline__ int around(float2 c, float2 p, int pid, float2 q, int qid)
+{
+    const int o = orient_exact(c.x, c.y, p.x, p.y, q.x, q.y);
+    if (o != 0) return o > 0 ? -1 : 1;
+    if (p.x != q.x) return (fabs((double)p.x - (double)c.x) < fabs((double)q.x - (double)c.x)) ? -1 : 1;
+    if (p.y != q.y) return (fabs((double)p.y - (double)c.y) < fabs((double)q.y - (double)c.y)) ? -1 : 1;
+    return pid < qid ? -1 : 1;
+}
+
+__device__ __forceinline__ int orient_of(float2 o, float2 e, float2 p, Counters& ctr)
+{
+    const Orient32 v = orient32p(o.x, o.y, e.x, e.y, p.x, p.y);
+    ++ctr.orient;
+    if (fabsf(v.d) > v.es) return v.d > 0.0f ? 1 : -1;
+    ++ctr.orient_exact;
+    return orient_exact(o.x, o.y, e.x, e.y, p.x, p.y);
+}
+
+// Sorts 64 R keys over the wave, element lane * R + r ascending (bitonic).
+template <int R>
+__device__ __forceinline__ void wave_sort(uint32_t (&k)[R])
+{
+    const int lane = lane_id();
+#pragma unroll
+    for (int size = 2; size <= 64 * R; size <<= 1) {
+#pragma unroll
+        for (int d = size >> 1; d >= 1; d >>= 1) {
+            if (d >= R) {
+                const int ld = d / R;
+                // (every register of a lane sorts the same way here)
+                const bool up = ((lane * R) & size) == 0, low = (lane & ld) == 0;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const uint32_t o = (uint32_t)__shfl_xor((int)k[r], ld);
+                    k[r] = (up == low) ? min(k[r], o) : max(k[r], o);
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    if (r & d) continue;
+                    const bool up = ((lane * R + r) & size) == 0;
+                    const uint32_t a = k[r], b = k[r + d], lo = min(a, b), hi = max(a, b);
+                    k[r] = up ? lo : hi;
+                    k[r + d] = up ? hi : lo;
+                }
+            }
+        }
+    }
+}
+
+constexpr int kWavePts = 256;  // points of a wave's pocket
+struct WaveLds {
+    float2 xy[2][kWavePts];
+    uint8_t at[2][kWavePts];  // each one's place among the pocket's points as loaded
+    int id[kWavePts];
+};
+
+template <int R>
+__device__ __forceinline__ void wave_order(WaveLds& W, int n, float2 c, float2 A, float2 B)
+{
+    const int lane = lane_id();
+    const float ax = A.x - c.x, ay = A.y - c.y, bx = B.x - c.x, by = B.y - c.y;
+    uint32_t key[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = lane + 64 * r;
+        key[r] = 0xffffff00u | (uint32_t)(i & 255);
+        if (i < n) {
+            // 0 at A, 1 at B, increasing with the angle
+            const float2 p = W.xy[0][i];
+            const float x = p.x - c.x, y = p.y - c.y;
+            const float u = ax * y - ay * x, v = x * by - y * bx;
+            const float f = fminf(fmaxf(u / (u + v), 0.0f), 1.0f);  // (NaN becomes 0: any order will do here)
+            key[r] = (min((uint32_t)(f * 16777216.0f), 0xfffffeu) << 8) | (uint32_t)i;
+        }
+    }
+    wave_sort<R>(key);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int e = lane * R + r, q = (int)(key[r] & 255u);
+        if (e < n) {
+            W.xy[1][e] = W.xy[0][q];
+            W.at[1][e] = (uint8_t)q;
+        }
+    }
+}
+
+// One wave: the n <= 256 points W.xy[0], W.id in order about c and without
+// those that are not strictly convex from A to B. Returns how many are left
+// and in which buffer (f).
+__device__ __forceinline__ int wave_chain(WaveLds& W, int n, float2 c, float2 A, float2 B, int& f, Counters& ctr)
+{
+    const int lane = lane_id();
+    if (n <= 64) wave_order<1>(W, n, c, A, B);
+    else if (n <= 128) wave_order<2>(W, n, c, A, B);
+    else wave_order<4>(W, n, c, A, B);
+    wave_sync();
+    // the rounded keys may have misplaced neighbours: exact sweeps until the
+    // order holds
+    bool unsure = false;
+    for (int i = lane; i + 1 < n; i += 64) {
+        const float2 p = W.xy[1][i], q = W.xy[1][i + 1];
+        const Orient32 o = orient32p(c.x, c.y, p.x, p.y, q.x, q.y);
+        unsure |= !(o.d > o.es);
+    }
+    if (__ballot(unsure)) {
+        for (int sweep = 0, still = 0; still < 2 && sweep < 2 * kWavePts + 2; ++sweep) {
+            bool swapped = false;
+            for (int i = 2 * lane + (sweep & 1); i + 1 < n; i += 128) {
+                const float2 p = W.xy[1][i], q = W.xy[1][i + 1];
+                const Orient32 o = orient32p(c.x, c.y, p.x, p.y, q.x, q.y);
+                if (o.d > o.es) continue;
+                const uint8_t pa = W.at[1][i], qa = W.at[1][i + 1];
+                ++ctr.orient_exact;
+                if (around(c, p, W.id[pa], q, W.id[qa]) > 0) {
+                    W.xy[1][i] = q; W.xy[1][i + 1] = p;
+                    W.at[1][i] = qa; W.at[1][i + 1] = pa;
+                    swapped = true;
+                }
+            }
+            wave_sync();
+            still = __ballot(swapped) ? 0 : still + 1;
+        }
+    }
+    f = 1;
+    for (;;) {
+        int m = 0;
+        for (int i0 = 0; i0 < n; i0 += 64) {
+            const int i = i0 + lane;
+            bool keep = false;
+            float2 p = A;
+            if (i < n) {
+                p = W.xy[f][i];
+                const float2 o = i > 0 ? W.xy[f][i - 1] : A, q = i + 1 < n ? W.xy[f][i + 1] : B;
+                // a copy goes; the first of some copies waits for them to go
+                const bool copy = p.x == o.x && p.y == o.y, twin = p.x == q.x && p.y == q.y;
+                keep = !copy && (twin || orient_of(o, p, q, ctr) > 0);
+            }
+            const uint64_t M = __ballot(keep);
+            if (keep) {
+                const int d = m + bits_below(M);
+                W.xy[f ^ 1][d] = p;
+                W.at[f ^ 1][d] = W.at[f][i];
+            }
+            m += (int)__popcll(M);
+        }
+        wave_sync();
+        f ^= 1;
+        if (m == n) return m;
+        n = m;
+    }
+}
+
+}  // namespace sqh

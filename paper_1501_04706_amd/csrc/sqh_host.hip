@@ -173,7 +173,7 @@ struct sqh_ctx {
     HullInfo* hinfo = nullptr;   // ... its info block
     uint32_t* hstats = nullptr;  // ... its counters
     int* herr = nullptr;         // ... its error word
-    LocalStatus* lstat = nullptr;  // pinned status the workgroup-local kernels write
+    LocalStatus* lstat = nullptr;  // ... followed by the status the workgroup-local kernels write
     sqh_stats stats{};
     static constexpr int kMaxTune = 40;
     TuneEntry tune[kMaxTune];
@@ -565,16 +565,56 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
     int reset_grid = 1;
     int rc = setup(ctx, d_xy, N, nsets, d_set_off, d_out, d_out_off, out_cap, d_ws, ws_bytes, tu, a, reset_grid);
     if (rc != SQH_OK) return rc;
+    const bool plain = !a.prefilter && !a.sorted && !ctx->trace;
+    const bool sieve = a.line_ok && !a.fp64;  // static float32 certificates may be used
     // a small set in plain mode: one workgroup, its points in LDS. Up to
     // kLocalPoints points in every precision mode; more, up to kLocalMax,
-    // where the static float32 certificates may be used (the sieve's)
-    if (nsets == 1 && !d_set_off && !a.prefilter && !a.sorted && !ctx->trace &&
-        (N <= kLocalPoints || (N <= kLocalMax && a.line_ok && !a.fp64))) {
-        LocalArgs l{a.xy, (int)N, d_out, out_cap, nullptr, a.fp64, a.line_ok, ctx->lstat};
+    // with the sieve
+    bool ring = false;
+    if (nsets == 1 && !d_set_off && plain && (N <= kLocalPoints || (N <= kLocalMax && sieve))) {
+        LocalArgs l{a.xy, (int)N, d_out, out_cap, nullptr, a.fp64, sieve, ctx->lstat};
         ctx->nl = 0;
         if (time_open(ctx, "k_local_one", st) != SQH_OK) return SQH_EDEVICE;
         HIP_OK(launch_local_one(l, st));
         if (time_close(ctx, "k_local_one", st) != SQH_OK) return SQH_EDEVICE;
+        HIP_OK(hipStreamSynchronize(st));
+        if (!ctx->lstat->left) return collect_local(ctx, N, out_cap, h_total);
+        ring = true;  // a ring of points: the batch kernels cut it into pockets
+    }
+    // several sets: each on a workgroup of its own (4096 sets of 64M points:
+    // 15.9 ms on the persistent kernel, whose every pass streams all sets'
+    // points between two grid barriers, and 1.74 ms so). One large set in a
+    // batch stays with the streaming path.
+    if (plain && N > 0 && ((d_set_off && (nsets > 1 || N < kStreamMin)) || ring)) {
+        BatchArgs b{};
+        b.xy = a.xy;
+        b.set_off = d_set_off;
+        b.N = (int)N;
+        b.G = (int)nsets;
+        b.out = d_out;
+        b.cap = out_cap;
+        b.out_off = d_out_off;
+        b.fp64 = a.fp64;
+        b.sieve = sieve;
+        b.status = ctx->lstat;
+        b.start = a.gstart;
+        b.hcnt = reinterpret_cast<int*>(a.sets);
+        b.order = b.hcnt + nsets;
+        b.hbuf = a.vidx;
+        b.slots = a.X[0];
+        b.pockets = reinterpret_cast<Pocket*>(a.recs);
+        b.pocket_cap = (int)(N / 128 + 4);
+        b.todo[0] = reinterpret_cast<int*>(a.segs[0]);
+        b.todo[1] = reinterpret_cast<int*>(a.segs[1]);
+        b.todo[2] = b.todo[1] + b.pocket_cap;
+        b.slots2 = a.X[1];
+        b.dense = reinterpret_cast<DenseSet*>(a.seg_cid[0]);
+        b.dense_cap = (int)(N / 4096 + 1);
+        b.ctl = reinterpret_cast<BatchCtl*>(a.slots);
+        ctx->nl = 0;
+        if (time_open(ctx, "k_batch", st) != SQH_OK) return SQH_EDEVICE;
+        HIP_OK(launch_batch(b, ctx->cus, st));
+        if (time_close(ctx, "k_batch", st) != SQH_OK) return SQH_EDEVICE;
         HIP_OK(hipStreamSynchronize(st));
         if (!ctx->lstat->left) return collect_local(ctx, N, out_cap, h_total);
     }
@@ -829,15 +869,15 @@ int sqh_create(sqh_ctx** out, int device)
     }
     if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->evk) != hipSuccess ||
         hipEventCreate(&c->ev1) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&c->hstatus), status_offsets().bytes, hipHostMallocDefault) !=
-            hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&c->lstat), sizeof(LocalStatus), hipHostMallocDefault) != hipSuccess) {
+        hipHostMalloc(reinterpret_cast<void**>(&c->hstatus), align_up(status_offsets().bytes) + sizeof(LocalStatus),
+                      hipHostMallocDefault) != hipSuccess) {
         sqh_destroy(c);
         return SQH_EDEVICE;
     }
     {
         const StatusOffsets so = status_offsets();
         c->herr = reinterpret_cast<int*>(c->hstatus);
+        c->lstat = reinterpret_cast<LocalStatus*>(c->hstatus + align_up(so.bytes));
         c->hstats = reinterpret_cast<uint32_t*>(c->hstatus + so.stats);
         c->hinfo = reinterpret_cast<HullInfo*>(c->hstatus + so.info);
     }
@@ -854,7 +894,6 @@ void sqh_destroy(sqh_ctx* c)
     if (c->evk) (void)hipEventDestroy(c->evk);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
     if (c->hstatus) (void)hipHostFree(c->hstatus);
-    if (c->lstat) (void)hipHostFree(c->lstat);
     delete c;
 }
 

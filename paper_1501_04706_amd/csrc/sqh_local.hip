@@ -1,8 +1,11 @@
 // Hulls computed by one workgroup each: small single sets (device and launch
 // code, gfx950).
+#include <algorithm>
+
 #include "sqh_local.hpp"
 #include "sqh_solve.hpp"
 #include "sqh_sieve.hpp"
+#include "sqh_dense.hpp"
 
 namespace sqh {
 
@@ -49,10 +52,11 @@ __global__ __launch_bounds__(T) void k_local_one(LocalArgs a)
     const bool f64 = a.fp64 != 0;
     int h;
     if constexpr (SIEVE) {
-        h = solve_set<T, P>(L, a.xy, a.n, f64, ctr, &st);
+        int sample;
+        h = solve_set<T, P>(L, a.xy, a.n, f64, ctr, &st, &sample);
     } else {
         const int cnt = load_points<T, P>(L, a.xy, a.n, a.n);
-        h = L.bad ? kSetBad : (cnt == 0 ? 0 : solve<T, P>(L, cnt, true, 0, 0, 0, f64, ctr, &st));
+        h = L.bad ? kSetBad : (cnt == 0 ? 0 : solve<T, P, true>(L, cnt, 0, 0, f64, ctr, &st));
     }
     counters_sum(ctr, csum);
     if (h > 0) {
@@ -93,6 +97,583 @@ hipError_t launch_local_one(const LocalArgs& a, hipStream_t st)
     if (a.n <= kSmallP) k_local_one<kSmallT, kSmallP, false><<<1, kSmallT, 0, st>>>(a);
     else if (a.n <= kMidP) k_local_one<kMidT, kMidP, false><<<1, kMidT, 0, st>>>(a);
     else k_local_one<kMidT, kMidP, true><<<1, kMidT, 0, st>>>(a);
+    return hipGetLastError();
+}
+
+// ---- batches ---------------------------------------------------------------
+
+constexpr int kClasses = 6;  // sets of up to 2^10, 2^12, 2^14, 2^16, 2^18, 2^20 points
+constexpr int kTasks = 3;  // pocket solvers: a wave, four waves, sixteen
+constexpr int kTaskT[kTasks] = {64, 256, 1024}, kTaskP[kTasks] = {kWavePts + 2, 1024, kLocalPoints};
+
+struct BatchCtl {
+    int err, left;
+    int n_small, n_big;         // queue lengths: class 0; classes 5 .. 1
+    int head_big, n_task[kTasks];
+    int n_pocket, n_dense;
+    int passes, pass_v[kSolvePasses], pass_s[kSolvePasses];
+    unsigned long long orient, orient_exact, cmp_exact, t0;
+};
+static_assert(sizeof(Pocket) == 32, "pockets fit the child records' space");
+
+size_t batch_ctl_bytes() { return sizeof(BatchCtl); }
+size_t pocket_bytes() { return sizeof(Pocket); }
+size_t dense_bytes() { return sizeof(DenseSet); }
+
+// A workgroup's share of the batch's counters.
+struct BatchAcc {
+    SolveStats st;
+    uint32_t c[3];
+};
+__device__ __forceinline__ void acc_init(BatchAcc& A)
+{
+    stats_clear(A.st);
+    if (threadIdx.x < 3) A.c[threadIdx.x] = 0u;
+    __syncthreads();
+}
+__device__ __forceinline__ void acc_flush(BatchAcc& A, const Counters& ctr, BatchCtl* ctl)
+{
+    counters_sum(ctr, A.c);
+    __syncthreads();
+    const int t = (int)threadIdx.x;
+    if (t < kSolvePasses) {
+        if (A.st.pass_v[t]) atomicAdd(&ctl->pass_v[t], A.st.pass_v[t]);
+        if (A.st.pass_s[t]) atomicAdd(&ctl->pass_s[t], A.st.pass_s[t]);
+    }
+    if (t == 0) {
+        if (A.st.passes) atomicMax(&ctl->passes, A.st.passes);
+        if (A.c[0]) atomicAdd(&ctl->orient, (unsigned long long)A.c[0]);
+        if (A.c[1]) atomicAdd(&ctl->orient_exact, (unsigned long long)A.c[1]);
+        if (A.c[2]) atomicAdd(&ctl->cmp_exact, (unsigned long long)A.c[2]);
+    }
+}
+
+__device__ __forceinline__ int set_class(int n)
+{
+    return n <= 1 << 10 ? 0 : (n <= 1 << 12 ? 1 : (n <= 1 << 14 ? 2 : (n <= 1 << 16 ? 3 : (n <= 1 << 18 ? 4 : 5))));
+}
+
+// The batch's offsets checked and its sets queued by size class, the largest
+// first (one workgroup: a few loads per set).
+__global__ __launch_bounds__(1024) void k_batch_init(BatchArgs a)
+{
+    __shared__ int n[kClasses], at[kClasses], s_err, s_left;
+    const int t = (int)threadIdx.x;
+    BatchCtl* ctl = a.ctl;
+    for (int i = t; i < (int)(sizeof(BatchCtl) / sizeof(int)); i += 1024) reinterpret_cast<int*>(ctl)[i] = 0;
+    if (t < kClasses) n[t] = 0;
+    if (t == 0) { s_err = 0; s_left = 0; }
+    __syncthreads();
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int s = t; s < a.G; s += 1024) {
+            const int64_t v = a.set_off ? gld(a.set_off + s) : 0, w = a.set_off ? gld(a.set_off + s + 1) : a.N;
+            const bool ok = v >= 0 && w >= v && w <= a.N && (s > 0 || v == 0) && (s < a.G - 1 || w == a.N);
+            if (pass == 0) {
+                if (!ok) { s_err = 1; continue; }
+                a.start[s] = (int)v;
+                if (s == a.G - 1) a.start[a.G] = (int)w;
+                const int m = (int)(w - v);
+                a.hcnt[s] = 0;
+                if (m > kBatchSetMax || (m > kLocalPoints && !a.sieve)) s_left = 1;
+                if (m > 0) atomicAdd(&n[set_class(m)], 1);
+            } else {
+                const int m = (int)(w - v);
+                if (m > 0) a.order[atomicAdd(&at[set_class(m)], 1)] = s;
+            }
+        }
+        __syncthreads();
+        if (pass == 0 && (s_err || s_left)) break;
+        if (pass == 0 && t == 0) {
+            // classes 5, 4, .. 1 make the big queue, class 0 the small one
+            int run = 0;
+            for (int c = kClasses - 1; c >= 0; --c) {
+                at[c] = run;
+                run += n[c];
+            }
+            ctl->n_small = n[0];
+            ctl->n_big = run - n[0];
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        ctl->err = s_err ? kErrBounds : 0;
+        ctl->left = (s_left && !s_err) ? 1 : 0;
+        ctl->t0 = wall_clock64();
+    }
+}
+
+__device__ __forceinline__ void put_hull(const BatchArgs& a, int s, int base, int h, const int* id, const uint16_t* ring,
+                                         int T)
+{
+    if (h == kSetBad) {
+        if (threadIdx.x == 0) atomicOr(&a.ctl->err, kErrNonFinite);
+        return;
+    }
+    for (int r = (int)threadIdx.x; r < h; r += T) gst(a.hbuf + base + r, id[ring[r]]);
+    if (threadIdx.x == 0) a.hcnt[s] = h;
+}
+
+// Sets of up to kSmallP points, a workgroup each.
+__global__ __launch_bounds__(kSmallT, 4) void k_batch_small(BatchArgs a)
+{
+    __shared__ SolveLds<kSmallP> L;
+    __shared__ BatchAcc A;
+    const BatchCtl* ctl = a.ctl;
+    if (ctl->err | ctl->left) return;
+    Counters ctr = {0u, 0u, 0u};
+    acc_init(A);
+    const int ns = ctl->n_small, nb = ctl->n_big;
+    for (int i = (int)blockIdx.x; i < ns; i += (int)gridDim.x) {
+        const int s = a.order[nb + i], base = a.start[s], n = a.start[s + 1] - base;
+        if (threadIdx.x == 0) L.bad = 0;
+        lds_barrier();
+        const int cnt = load_points<kSmallT, kSmallP>(L, a.xy + base, n, n);
+        const int h = L.bad ? kSetBad : solve<kSmallT, kSmallP, true>(L, cnt, 0, 0, a.fp64 != 0, ctr, &A.st);
+        put_hull(a, s, base, h, L.id, L.ring, kSmallT);
+        lds_barrier();
+    }
+    acc_flush(A, ctr, a.ctl);
+}
+
+// A ring of points: cut into pockets for the chain solves that follow.
+// False if it cannot be (the general path has to run).
+template <int T, int P>
+__device__ __forceinline__ bool cut_pockets(const BatchArgs& a, SolveLds<P>& L, int h, int s, int base, int n,
+                                            Counters& ctr)
+{
+    static_assert(sizeof(DenseLds) <= sizeof(L.bins), "the tables take the slabs' space");
+    constexpr int U = 4;
+    DenseLds& D = *reinterpret_cast<DenseLds*>(&L.bins[0]);
+    __shared__ int s_t0, s_d, s_q[kTasks];
+    const int t = (int)threadIdx.x;
+    const int K = min(min(max(4, n / kDenseTarget), h / 2), kDenseMaxK);
+    if (K < 4 || K > kDenseMaxK) return false;
+    if (!dense_build<T, P>(L, h, K, D)) return false;
+    const float2* xy = a.xy + base;
+    bool bad = false;
+    // twice over the set: counts, then the points to their pockets
+    for (int ps = 0; ps < 2; ++ps) {
+        for (int q0 = 0; q0 < n; q0 += T * U) {
+            float2 v[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) v[j] = gld(xy + min(q0 + t + T * j, n - 1));
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const int q = q0 + t + T * j;
+                const bool fin = (int)isfinite(v[j].x) & (int)isfinite(v[j].y);
+                bad |= !fin;
+                int k = -1;
+                if (q < n && fin) k = pocket_of(D, K, v[j].x, v[j].y, q, ctr);
+                if (k >= 0) {
+                    if (ps == 0) {
+                        atomicAdd(&D.cnt[k], 1);
+                    } else {
+                        float* d = a.slots + 3 * (size_t)(base + atomicAdd(&D.cur[k], 1));
+                        gst(d, v[j].x);
+                        gst(d + 1, v[j].y);
+                        gst(d + 2, __int_as_float(q));
+                    }
+                }
+            }
+        }
+        if (ps == 0) {
+            if (__ballot(bad) && lane_id() == 0) L.bad = 1;
+            lds_barrier();
+            if (L.bad) return true;
+            // slot ranges (one more than its points for v_k), by one wave
+            if (t < 64) {
+                int run = 0;
+                for (int k0 = 0; k0 < K; k0 += 64) {
+                    const int k = k0 + t, c = k < K ? D.cnt[k] + 1 : 0;
+                    if (c > P - 1) D.bad = 1;
+                    const int inc = wave_incl_sum(c);
+                    if (k < K) D.cur[k] = run + inc - c;
+                    run += __builtin_amdgcn_readlane(inc, 63);
+                }
+                if (t == 0) {
+                    const int d = atomicAdd(&a.ctl->n_dense, 1);
+                    s_t0 = atomicAdd(&a.ctl->n_pocket, K);
+                    if (d >= a.dense_cap || s_t0 + K > a.pocket_cap) D.bad = 1;
+                    else gst(a.dense + d, DenseSet{s, s_t0, K, 0, D.c.x, D.c.y, {0, 0}});
+                    s_d = d;
+                }
+            }
+            lds_barrier();
+            if (D.bad) return false;
+        }
+    }
+    if (t < kTasks) s_q[t] = 0;
+    lds_barrier();
+    // the pockets' records and, by solver size, their places in its list (one
+    // global atomic per list and set)
+    auto size_of = [](int len) { return len + 2 <= kTaskP[0] ? 0 : (len + 2 <= kTaskP[1] ? 1 : 2); };
+    for (int k = t; k < K; k += T)
+        if (D.cnt[k] > 0) atomicAdd(&s_q[size_of(D.cnt[k])], 1);
+    lds_barrier();
+    if (t < kTasks && s_q[t] > 0) s_q[t] = atomicAdd(&a.ctl->n_task[t], s_q[t]);
+    lds_barrier();
+    for (int k = t; k < K; k += T) {
+        const float2 v = D.v[k], w = D.v[k + 1 < K ? k + 1 : 0];
+        const int len = D.cnt[k], off = base + D.cur[k] - len;
+        Pocket p;
+        p.ax = v.x; p.ay = v.y; p.bx = w.x; p.by = w.y;
+        p.aid = D.id[k]; p.off = off; p.len = len; p.ring = s_d;
+        if (len == 0) {
+            // the vertex alone
+            float* d = a.slots + 3 * (size_t)off;
+            gst(d, v.x);
+            gst(d + 1, v.y);
+            gst(d + 2, __int_as_float(p.aid));
+            p.len = 1;
+        } else {
+            const int c = size_of(len);
+            a.todo[c][atomicAdd(&s_q[c], 1)] = s_t0 + k;
+        }
+        gst(a.pockets + s_t0 + k, p);
+    }
+    return true;
+}
+
+// Larger sets, the largest first.
+__global__ __launch_bounds__(kMidT) void k_batch_big(BatchArgs a)
+{
+    __shared__ SolveLds<kMidP> L;
+    __shared__ BatchAcc A;
+    __shared__ int s_i;
+    BatchCtl* ctl = a.ctl;
+    if (ctl->err | ctl->left) return;
+    Counters ctr = {0u, 0u, 0u};
+    acc_init(A);
+    const int nb = ctl->n_big;
+    for (;;) {
+        if (threadIdx.x == 0) {
+            s_i = atomicAdd(&ctl->head_big, 1);
+            L.bad = 0;
+        }
+        lds_barrier();
+        const int i = s_i;
+        if (i >= nb) break;
+        const int s = a.order[i], base = a.start[s], n = a.start[s + 1] - base;
+        int sample = 0;
+        int h = solve_set<kMidT, kMidP>(L, a.xy + base, n, a.fp64 != 0, ctr, &A.st, &sample);
+        if (h == kSetDense) {
+            const bool ok = sample > 0 && cut_pockets<kMidT, kMidP>(a, L, sample, s, base, n, ctr);
+            if (!ok && threadIdx.x == 0) ctl->left = 1;
+            if (L.bad) h = kSetBad;
+        }
+        put_hull(a, s, base, h, L.id, L.ring, kMidT);
+        lds_barrier();
+    }
+    acc_flush(A, ctr, ctl);
+}
+
+__device__ __forceinline__ void put_nodes(float* slot, const float2* xy, const int* id, const uint16_t* ring, int nodes,
+                                          int T)
+{
+    for (int r = (int)threadIdx.x; r < nodes; r += T) {
+        const int q = ring[r];
+        gst(slot + 3 * r, xy[q].x);
+        gst(slot + 3 * r + 1, xy[q].y);
+        gst(slot + 3 * r + 2, __int_as_float(id[q]));
+    }
+}
+
+// The pockets' chains: each pocket's nodes (v_k, then the chain) replace its
+// points. Pockets of up to kWavePts points are a wave's, with no barriers.
+constexpr int kPocketWaves = 4;
+__global__ __launch_bounds__(64 * kPocketWaves) void k_batch_pocket(BatchArgs a)
+{
+    __shared__ WaveLds Ws[kPocketWaves];
+    BatchCtl* ctl = a.ctl;
+    const int nt = ctl->n_task[0];
+    if (nt == 0 || (ctl->err | ctl->left)) return;
+    const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
+    WaveLds& W = Ws[w];
+    Counters ctr = {0u, 0u, 0u};
+    for (int i = (int)blockIdx.x * kPocketWaves + w; i < nt; i += (int)gridDim.x * kPocketWaves) {
+        const int j = gld(a.todo[0] + i);
+        const Pocket p = gld(a.pockets + j);
+        const float2 c = make_float2(gld(&a.dense[p.ring].cx), gld(&a.dense[p.ring].cy));
+        float* slot = a.slots + 3 * (size_t)p.off;
+#pragma unroll
+        for (int r = 0; r < kWavePts / 64; ++r) {
+            const int q = lane + 64 * r;
+            if (q < p.len) {
+                W.xy[0][q] = make_float2(gld(slot + 3 * q), gld(slot + 3 * q + 1));
+                W.id[q] = __float_as_int(gld(slot + 3 * q + 2));
+            }
+        }
+        wave_sync();
+        int f;
+        const int m = wave_chain(W, p.len, c, make_float2(p.ax, p.ay), make_float2(p.bx, p.by), f, ctr);
+        for (int q = lane; q < m; q += 64) {
+            float* d = slot + 3 * (q + 1);
+            gst(d, W.xy[f][q].x);
+            gst(d + 1, W.xy[f][q].y);
+            gst(d + 2, __int_as_float(W.id[W.at[f][q]]));
+        }
+        if (lane == 0) {
+            gst(slot, p.ax);
+            gst(slot + 1, p.ay);
+            gst(slot + 2, __int_as_float(p.aid));
+            gst(&a.pockets[j].len, m + 1);
+        }
+        wave_sync();
+    }
+    const uint32_t v[2] = {(uint32_t)wave_total((int)ctr.orient), (uint32_t)wave_total((int)ctr.orient_exact)};
+    if (lane == 0) {
+        if (v[0]) atomicAdd(&ctl->orient, (unsigned long long)v[0]);
+        if (v[1]) atomicAdd(&ctl->orient_exact, (unsigned long long)v[1]);
+    }
+}
+
+// Larger pockets: the passes.
+template <int C>
+__global__ __launch_bounds__(kTaskT[C], 4) void k_batch_chain(BatchArgs a)
+{
+    constexpr int T = kTaskT[C], P = kTaskP[C];
+    __shared__ SolveLds<P> L;
+    __shared__ BatchAcc A;
+    BatchCtl* ctl = a.ctl;
+    const int nt = ctl->n_task[C];
+    if (nt == 0 || (ctl->err | ctl->left)) return;
+    Counters ctr = {0u, 0u, 0u};
+    acc_init(A);
+    const int t = (int)threadIdx.x;
+    for (int i = (int)blockIdx.x; i < nt; i += (int)gridDim.x) {
+        const int j = a.todo[C][i];
+        const Pocket p = gld(a.pockets + j);
+        float* slot = a.slots + 3 * (size_t)p.off;
+        for (int r = t; r < p.len; r += T) {
+            L.xy[r] = make_float2(gld(slot + 3 * r), gld(slot + 3 * r + 1));
+            L.id[r] = __float_as_int(gld(slot + 3 * r + 2));
+        }
+        if (t == 0) {
+            L.xy[p.len] = make_float2(p.ax, p.ay);
+            L.id[p.len] = p.aid;
+            L.xy[p.len + 1] = make_float2(p.bx, p.by);
+            L.id[p.len + 1] = -1;
+        }
+        lds_barrier();
+        const int nodes = solve<T, P, false>(L, p.len + 2, p.len, p.len + 1, a.fp64 != 0, ctr, &A.st);
+        put_nodes(slot, L.xy, L.id, L.ring, nodes, T);
+        if (t == 0) a.pockets[j].len = nodes;
+        lds_barrier();
+    }
+    acc_flush(A, ctr, ctl);
+}
+
+// The rings: the pockets' nodes as one list, a workgroup per set, and the
+// removal rounds over it until every node is strictly convex; then the hull
+// from its lexicographic minimum.
+constexpr int kRingT = 512, kRingRows = 32;
+__global__ __launch_bounds__(kRingT) void k_batch_ring(BatchArgs a)
+{
+    constexpr int W = kRingT / 64;
+    __shared__ int s_at[kDenseMaxK + 1], s_off[kDenseMaxK];
+    __shared__ int red[W];
+    __shared__ int s_start;
+    __shared__ unsigned long long s_min;
+    BatchCtl* ctl = a.ctl;
+    if (ctl->err | ctl->left) return;
+    Counters ctr = {0u, 0u, 0u};
+    const int t = (int)threadIdx.x, lane = lane_id(), w = t >> 6, nd = ctl->n_dense;
+    for (int i = (int)blockIdx.x; i < nd; i += (int)gridDim.x) {
+        const DenseSet ds = gld(a.dense + i);
+        const int K = ds.k, base = gld(a.start + ds.set), n = gld(a.start + ds.set + 1) - base;
+        for (int k = t; k < K; k += kRingT) {
+            s_at[k] = gld(&a.pockets[ds.t0 + k].len);
+            s_off[k] = gld(&a.pockets[ds.t0 + k].off);
+        }
+        if (t == 0) s_min = ~0ull;
+        __syncthreads();
+        if (w == 0) {
+            int run = 0;
+            for (int k0 = 0; k0 < K; k0 += 64) {
+                const int k = k0 + lane, c = k < K ? s_at[k] : 0;
+                const int in = wave_incl_sum(c);
+                if (k < K) s_at[k] = run + in - c;
+                run += __builtin_amdgcn_readlane(in, 63);
+            }
+            if (lane == 0) s_at[K] = run;
+        }
+        __syncthreads();
+        int m = s_at[K];
+        // two buffers of this set's slots: the list goes from one to the other
+        float* buf[2] = {a.slots2 + 3 * (size_t)base, a.slots + 3 * (size_t)base};
+        for (int k = w; k < K; k += W) {
+            const float* src = a.slots + 3 * (size_t)s_off[k];
+            const int q0 = s_at[k], len = s_at[k + 1] - q0;
+            for (int e = lane; e < 3 * len; e += 64) gst(buf[0] + 3 * q0 + e, gld(src + e));
+        }
+        __syncthreads();
+        int f = 0;
+        for (;;) {
+            // each wave takes a contiguous run of whole rows, kRingRows at a time
+            const float* src = buf[f];
+            float* dst = buf[f ^ 1];
+            int out = 0;  // nodes kept before the block of rows
+            for (int q0 = 0; q0 < m; q0 += kRingT * kRingRows) {
+                const int mb = min(m - q0, kRingT * kRingRows);
+                const int per = (((mb + W - 1) / W) + 63) & ~63;
+                const int wb = q0 + min(w * per, mb), we = q0 + min(w * per + per, mb);
+                uint32_t keep = 0u;
+                int cnt = 0;
+                for (int r = 0; wb + 64 * r < we; ++r) {
+                    const int q = wb + 64 * r + lane;
+                    bool kp = false;
+                    if (q < we) {
+                        const float* p = src + 3 * (size_t)q;
+                        const float* o = src + 3 * (size_t)(q > 0 ? q - 1 : m - 1);
+                        const float* e = src + 3 * (size_t)(q + 1 < m ? q + 1 : 0);
+                        kp = orient_of(make_float2(gld(o), gld(o + 1)), make_float2(gld(p), gld(p + 1)),
+                                       make_float2(gld(e), gld(e + 1)), ctr) > 0;
+                    }
+                    keep |= (uint32_t)kp << r;
+                    cnt += (int)__popcll(__ballot(kp));
+                }
+                __syncthreads();
+                if (lane == 0) red[w] = cnt;
+                __syncthreads();
+                int at = out;
+#pragma unroll
+                for (int u = 0; u < W; ++u) {
+                    at += u < w ? red[u] : 0;
+                    out += red[u];
+                }
+                for (int r = 0; wb + 64 * r < we; ++r) {
+                    const int q = wb + 64 * r + lane;
+                    const bool kp = (keep >> r) & 1u;
+                    const uint64_t M = __ballot(kp);
+                    if (kp) {
+                        float* d = dst + 3 * (size_t)(at + bits_below(M));
+                        const float* p = src + 3 * (size_t)q;
+                        gst(d, gld(p));
+                        gst(d + 1, gld(p + 1));
+                        gst(d + 2, gld(p + 2));
+                    }
+                    at += (int)__popcll(M);
+                }
+            }
+            __syncthreads();
+            f ^= 1;
+            if (out == m) break;  // (uniform)
+            m = out;
+        }
+        const float* src = buf[f];
+        uint64_t lo = ~0ull;
+        auto key = [&](int q) {
+            return ((uint64_t)order_key(gld(src + 3 * (size_t)q) + 0.0f) << 32) | order_key(gld(src + 3 * (size_t)q + 1) + 0.0f);
+        };
+        for (int q = t; q < m; q += kRingT) {
+            const uint64_t v = key(q);
+            lo = v < lo ? v : lo;
+        }
+        lo = wave_min_u64(lo);
+        if (lane == 63) atomicMin(&s_min, (unsigned long long)lo);
+        __syncthreads();
+        for (int q = t; q < m; q += kRingT)
+            if (key(q) == s_min) s_start = q;  // (one node: the ring's positions differ)
+        __syncthreads();
+        const int st = s_start;
+        for (int q = t; q < m; q += kRingT) {
+            const int r = q >= st ? q - st : q - st + m;
+            gst(a.hbuf + base + r, __float_as_int(gld(src + 3 * (size_t)q + 2)));
+        }
+        if (t == 0) a.hcnt[ds.set] = m;
+        __syncthreads();
+    }
+    const uint32_t v[2] = {(uint32_t)wave_total((int)ctr.orient), (uint32_t)wave_total((int)ctr.orient_exact)};
+    if (lane == 0) {
+        if (v[0]) atomicAdd(&ctl->orient, (unsigned long long)v[0]);
+        if (v[1]) atomicAdd(&ctl->orient_exact, (unsigned long long)v[1]);
+    }
+}
+
+// Offsets and hulls to the caller, the status to the host. Workgroup b takes a
+// contiguous share of the sets, kEmitT at a time, and copies their hulls as one
+// run of the output (each thread finds its element's set by bisection, so
+// that one large hull does not hold a wave up).
+constexpr int kEmitT = 256;
+__global__ __launch_bounds__(kEmitT) void k_batch_emit(BatchArgs a)
+{
+    constexpr int W = kEmitT / 64;
+    __shared__ int red[W];
+    __shared__ int s_at[kEmitT], s_src[kEmitT];
+    const BatchCtl* ctl = a.ctl;
+    const int t = (int)threadIdx.x, lane = lane_id(), w = t >> 6, b = (int)blockIdx.x, nb = (int)gridDim.x;
+    const int bad = ctl->err | ctl->left;
+    const int per = (a.G + nb - 1) / nb;
+    const int s0 = min(b * per, a.G), s1 = min(s0 + per, a.G);
+    int run = 0;
+    if (!bad) {
+        int v = 0;
+        for (int s = t; s < s0; s += kEmitT) v += gld(a.hcnt + s);
+        v = wave_total(v);
+        if (lane == 0) red[w] = v;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < W; ++u) run += red[u];
+        for (int c0 = s0; c0 < s1; c0 += kEmitT) {
+            const int s = c0 + t, h = s < s1 ? gld(a.hcnt + s) : 0;
+            const int inc = wave_incl_sum(h);
+            __syncthreads();
+            if (lane == 63) red[w] = inc;
+            __syncthreads();
+            int before = 0, all = 0;
+#pragma unroll
+            for (int u = 0; u < W; ++u) {
+                before += u < w ? red[u] : 0;
+                all += red[u];
+            }
+            s_at[t] = before + inc - h;
+            s_src[t] = s < s1 ? gld(a.start + s) : 0;
+            if (s < s1 && a.out_off) a.out_off[s] = (int64_t)(run + before + inc - h);
+            __syncthreads();
+            for (int o = t; o < all; o += kEmitT) {
+                int l = 0;  // the last set starting at or before o (empty ones share their start with the next)
+#pragma unroll
+                for (int d = kEmitT / 2; d >= 1; d >>= 1)
+                    if (s_at[l + d] <= o) l += d;
+                if (run + o < a.cap) gst(a.out + run + o, gld(a.hbuf + s_src[l] + (o - s_at[l])));
+            }
+            run += all;
+        }
+    }
+    if (b == nb - 1) {
+        LocalStatus* s = a.status;
+        if (t < kSolvePasses) {
+            s->pass_v[t] = ctl->pass_v[t];
+            s->pass_s[t] = ctl->pass_s[t];
+        }
+        if (t == 0) {
+            if (!bad && a.out_off) a.out_off[a.G] = run;
+            s->h = bad ? 0 : run;
+            s->err = ctl->err;
+            s->left = ctl->err ? 0 : ctl->left;
+            s->passes = ctl->passes;
+            s->first_v = ctl->pass_v[0];
+            s->orient = ctl->orient;
+            s->orient_exact = ctl->orient_exact;
+            s->cmp_exact = ctl->cmp_exact;
+            s->t0 = ctl->t0;
+            s->t1 = wall_clock64();
+        }
+    }
+}
+
+hipError_t launch_batch(const BatchArgs& a, int cus, hipStream_t st)
+{
+    k_batch_init<<<1, 1024, 0, st>>>(a);
+    if (a.N > kSmallP) k_batch_big<<<std::min(a.G, cus), kMidT, 0, st>>>(a);
+    k_batch_small<<<std::min(a.G, 4 * cus), kSmallT, 0, st>>>(a);
+    if (a.sieve && a.N > kLocalPoints) {
+        k_batch_chain<2><<<cus, kTaskT[2], 0, st>>>(a);
+        k_batch_chain<1><<<4 * cus, kTaskT[1], 0, st>>>(a);
+        k_batch_pocket<<<6 * cus, 64 * kPocketWaves, 0, st>>>(a);
+        k_batch_ring<<<std::min(a.G, 4 * cus), kRingT, 0, st>>>(a);
+    }
+    k_batch_emit<<<std::min((a.G + 3) / 4, 4 * cus), kEmitT, 0, st>>>(a);
     return hipGetLastError();
 }
 

@@ -157,8 +157,11 @@ __device__ __forceinline__ int load_points(SolveLds<P>& L, const float2* xy, int
 // slabs of its sample's hull; the points left are collected in LDS. Should
 // they not fit, the collected points are replaced by their hull, whose slabs
 // then sieve the rest.
+// On kSetDense for the first reason, with nothing streamed yet, *sample is the
+// ring size of the sample's hull (still in L); else 0.
 template <int T, int P>
-__device__ __forceinline__ int solve_set(SolveLds<P>& L, const float2* xy, int n, bool f64, Counters& ctr, SolveStats* st)
+__device__ __forceinline__ int solve_set(SolveLds<P>& L, const float2* xy, int n, bool f64, Counters& ctr,
+                                         SolveStats* st, int* sample)
 {
     constexpr int U = 8;  // points per thread and step of the stream
     __shared__ int s_kb;
@@ -172,11 +175,14 @@ __device__ __forceinline__ int solve_set(SolveLds<P>& L, const float2* xy, int n
     int pos = 0;
     for (;;) {
         if (L.bad) return kSetBad;
-        const int h = solve<T, P>(L, cnt, true, 0, 0, 0, f64, ctr, fin ? st : nullptr);
+        const int h = solve<T, P, true>(L, cnt, 0, 0, f64, ctr, fin ? st : nullptr);
         if (fin) return h;
         // about h / cnt of the points would pass the sieve: a set that keeps
         // more than a quarter (a ring of points) is not for it
-        if (4 * h > cnt && (first || h > P / 2)) return kSetDense;
+        if (4 * h > cnt && (first || h > P / 2)) {
+            *sample = first ? h : 0;
+            return kSetDense;
+        }
         const Slabs sl = build_slabs<T, P>(L, h, L.bins, T, &s_kb);
         if (first) {
             // the sample's vertices come back with the stream

@@ -82,6 +82,14 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Orders a wave's own LDS accesses across its lanes (they execute in order).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ int bits_below(uint64_t M)
 {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(M >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)M, 0u));
@@ -142,15 +150,15 @@ struct SolveStats {
     int pass_v[kSolvePasses], pass_s[kSolvePasses];
 };
 
-// Solves the points 0 .. cnt-1 of L (cnt >= 1; whole) or the chain of one
-// segment: A at position ia, B at ib (both below cnt, belonging to no
-// segment), its farthest point at ic, every other position live. Returns
-// the number of list nodes: the ring's vertices, or A and the chain's
-// vertices; L.ring[r] is the position of node r (A is node 0). Every thread
-// of the T-thread workgroup calls it; L.xy and L.id must be visible.
-template <int T, int P>
-__device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, bool whole, int ia, int ic, int ib, bool f64,
-                                     Counters& ctr, SolveStats* st)
+// Solves the points 0 .. cnt-1 of L (cnt >= 1; WHOLE) or the chain from A at
+// position ia to B at ib (both below cnt) over every other position, all of
+// them strictly right of A -> B. Returns the number of list nodes: the ring's
+// vertices, or A and the chain's vertices; L.ring[r] is the position of node
+// r (A is node 0). Every thread of the T-thread workgroup calls it; L.xy and
+// L.id must be visible.
+template <int T, int P, bool WHOLE>
+__device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bool f64, Counters& ctr,
+                                     SolveStats* st)
 {
     constexpr int R = P / T, kPair = 2;
     static_assert(R % kPair == 0, "points go in pairs");
@@ -176,7 +184,10 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, bool whole, int ia
         L.map[0] = 0;
     }
     lds_barrier();
-    if (whole) {
+    // the first segment's "farthest point" is B itself: its children are the
+    // sides of A -> B and, for a set, of B -> A
+    int ic = ib;
+    if constexpr (WHOLE) {
         // A and B: the lexicographic extremes, the lowest index among copies
         uint64_t k[R], lo = ~0ull, hi = 0ull;
 #pragma unroll
@@ -223,12 +234,12 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, bool whole, int ia
         L.seg[0][0] = g;
     }
     lds_barrier();
-    int nodes = 1;  // A
+    int nodes = WHOLE ? 1 : 0;  // (pass 0 adds B to a ring, or counts A)
     int pass = 0;
     for (;; ++pass) {
         const int c = pass & 1, S = L.ns[c];
         if (S == 0) break;  // (uniform)
-        const int sp = whole ? pass - 2 : pass;  // (a set's passes 0 and 1 are the split and the first compaction)
+        const int sp = WHOLE ? pass - 2 : pass - 1;  // (a set's passes 0 and 1 are the split and the first compaction)
         if (st && t == 0 && sp >= 0 && sp < kSolvePasses) st->pass_s[sp] += S;
         // 1. each live point: its child and the child's largest lower bound.
         // Points go two at a time without branches, so that their LDS reads
@@ -417,7 +428,7 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, bool whole, int ia
         lds_barrier();
     }
     if (st && t == 0) {
-        const int np = whole ? (pass > 2 ? pass - 2 : 0) : pass;
+        const int np = WHOLE ? (pass > 2 ? pass - 2 : 0) : pass - 1;
         st->passes = np > st->passes ? np : st->passes;
     }
     // ---- ring order: the nodes packed into a list, then each one's distance
@@ -428,7 +439,7 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, bool whole, int ia
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int i = t + T * r;
-        const int nx = i < cnt ? (int)L.next[i] : (int)kNoNext;
+        const int nx = (i < cnt && (WHOLE || i != ib)) ? (int)L.next[i] : (int)kNoNext;
         const uint64_t M = __ballot(nx != kNoNext);
         if (!M) continue;
         int at = 0;
@@ -450,12 +461,12 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, bool whole, int ia
                 const int d2 = L.jd[0][n], n2 = L.jn[0][n];
                 d += d2;
                 n = n2;
-                __builtin_amdgcn_wave_barrier();
+                wave_sync();
                 if (on) {
                     L.jd[0][i] = (uint16_t)d;
                     L.jn[0][i] = (uint16_t)n;
                 }
-                __builtin_amdgcn_wave_barrier();
+                wave_sync();
             }
             if (on) L.ring[nodes - 1 - d] = (uint16_t)i;
         }

@@ -99,3 +99,74 @@ def test_errors_and_capacity(H, n):
     assert rc == sqh.SQH_OK and [int(v) for v in out.cpu().numpy()] == expect + [-7] * 8
     rc, h = sqh.sqh_hull(H.ctx, t, n, out, out.numel(), ws, 16)
     assert rc == sqh.SQH_ENOMEM
+
+
+def rings(n):
+    """Sets most of whose points are hull vertices, and their awkward relatives."""
+    rng = np.random.default_rng(n)
+    c = workloads.circle(n, n)
+    yield "circle", c
+    yield "sorted", c[np.argsort(c[:, 0], kind="stable")]
+    yield "flat", (c * np.float32([1.0, 1e-4])).astype(np.float32)
+    yield "far from the origin", (c + np.float32([31.0, -17.0])).astype(np.float32)
+    yield "copies", workloads.circle(max(1, n // 3), 5)[rng.integers(0, max(1, n // 3), n)]
+    t = rng.integers(0, 5000, n) * 0.00125
+    yield "few directions", np.stack([np.cos(t), np.sin(t)], 1).astype(np.float32)
+    t = np.where(rng.random(n) < 0.8, rng.random(n) * 0.3, rng.random(n) * 6.28)
+    yield "uneven", np.stack([np.cos(t), np.sin(t)], 1).astype(np.float32)
+    x = rng.permutation(n) - n // 2
+    yield "parabola", np.stack([x, x.astype(np.float64) ** 2 / n], 1).astype(np.float32)
+
+
+@pytest.mark.parametrize("n", [4097, 6001, 40_000, 65535])
+def test_single_rings(H, n):
+    for name, xy in rings(n):
+        print(f"[case] ring {name} n={n}", file=sys.stderr, flush=True)
+        assert gpu(H, xy) == [int(v) for v in oracle.c_hull(xy)], name
+
+
+@pytest.mark.parametrize("n", [1024, 4096, 4097, 20_000, 160_000, 700_000])
+def test_batches(H, n):
+    """Every kind of set in one batch, with empty sets and a ragged last one:
+    each size class, rings in pockets, sieved sets."""
+    import torch
+    print(f"[case] batch of sets of about {n}", file=sys.stderr, flush=True)
+    parts = [np.zeros((0, 2), np.float32)] + [xy for _, xy in rings(n)][:8 if n < 500_000 else 2]
+    parts += [workloads.make(k, m, 3) for k in ("square", "disk", "grid") for m in (n, max(1, n // 7))]
+    parts += [workloads.circle(m, 4) for m in (1, 2, 3, 65)] + [np.zeros((0, 2), np.float32)]
+    off = np.zeros(len(parts) + 1, np.int64)
+    off[1:] = np.cumsum([len(p) for p in parts])
+    xy = np.concatenate(parts, 0).astype(np.float32)
+    out, out_off = H.hull_batched(torch.from_numpy(xy).cuda(), torch.from_numpy(off).cuda())
+    out, out_off = out.cpu().numpy(), out_off.cpu().numpy()
+    for s, p in enumerate(parts):
+        assert [int(v) for v in out[out_off[s]:out_off[s + 1]]] == [int(v) for v in oracle.c_hull(p)], s
+
+
+def test_batch_errors(H):
+    import torch
+    parts = [workloads.disk(500, 1), workloads.circle(30_000, 2), workloads.disk(30_000, 3)]
+    off = np.zeros(4, np.int64)
+    off[1:] = np.cumsum([len(p) for p in parts])
+    xy = np.concatenate(parts, 0)
+    off_d = torch.from_numpy(off).cuda()
+    want = [int(v) for p in parts for v in oracle.c_hull(p)]
+    for at in (3, 500 + 17, 30_000, 30_500 + 29_999):  # each kind of set, on and off its sample
+        z = xy.copy()
+        z[at, 0] = np.nan
+        with pytest.raises(sqh.SqhError) as e:
+            H.hull_batched(torch.from_numpy(z).cuda(), off_d)
+        assert e.value.code == sqh.SQH_EINVAL
+    for bad in ([0, 500, 400, len(xy)], [1, 500, 600, len(xy)], [0, 500, 600, len(xy) - 1], [0, -5, 600, len(xy)]):
+        with pytest.raises(sqh.SqhError) as e:
+            H.hull_batched(torch.from_numpy(xy).cuda(), torch.tensor(bad, dtype=torch.int64, device="cuda"))
+        assert e.value.code == sqh.SQH_EINVAL
+    # a short output: the offsets and the total are whole, nothing is written past it
+    ws = H.workspace(len(xy), 3)
+    cap = len(want) - 100
+    out = torch.full((len(want),), -7, dtype=torch.int32, device="cuda")
+    out_off = torch.empty(4, dtype=torch.int64, device="cuda")
+    rc, h = sqh.sqh_hull_batched(H.ctx, torch.from_numpy(xy).cuda(), off_d, 3, len(xy), out, out_off, cap, ws, ws.numel())
+    assert rc == sqh.SQH_ECAPACITY and h == len(want)
+    assert [int(v) for v in out.cpu().numpy()] == want[:cap] + [-7] * 100
+    assert int(out_off[3]) == len(want)
