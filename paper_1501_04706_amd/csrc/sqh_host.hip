@@ -66,6 +66,7 @@ StatusOffsets status_offsets()
 
 bool make_layout(int64_t N, int64_t nsets, Layout& L)
 {
+    static const size_t ctl_bytes = std::max(sieve_ctl_bytes(), batch_ctl_bytes());
     if (N < 0 || nsets < 1 || N > (int64_t)INT32_MAX - 2 || nsets > (int64_t)INT32_MAX / 8) return false;
     L.N = N;
     L.nsets = nsets;
@@ -97,7 +98,8 @@ bool make_layout(int64_t N, int64_t nsets, Layout& L)
     L.vcap = std::min<int64_t>(N + 8, kSmallHull);
     L.vlist = take(sizeof(int2) * (size_t)L.vcap);
     L.wprefix = take(sizeof(int) * (size_t)L.W);
-    L.slots = take(sizeof(ChunkSlot<8>) * (size_t)kMaxGrid);
+    // (also the control block of the workgroup-local kernels)
+    L.slots = take(std::max(sizeof(ChunkSlot<8>) * (size_t)kMaxGrid, ctl_bytes));
     L.ctab = take(sizeof(Pair) * (size_t)kMaxGrid);
     L.bar = take(sizeof(GridBar));
     L.err = take(sizeof(int));
@@ -526,6 +528,12 @@ void phase_times(const HullInfo& hi, sqh_stats& S)
     }
 }
 
+int launch_mark(void* c, const char* name, int open, hipStream_t st)
+{
+    auto* ctx = static_cast<sqh_ctx*>(c);
+    return open ? time_open(ctx, name, st) : time_close(ctx, name, st);
+}
+
 // The counters and return code of a call that the workgroup-local kernels
 // finished (their status is in pinned memory; the stream is synchronised).
 int collect_local(sqh_ctx* ctx, int64_t N, int64_t out_cap, int64_t* h_total)
@@ -567,19 +575,54 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
     if (rc != SQH_OK) return rc;
     const bool plain = !a.prefilter && !a.sorted && !ctx->trace;
     const bool sieve = a.line_ok && !a.fp64;  // static float32 certificates may be used
-    // a small set in plain mode: one workgroup, its points in LDS. Up to
-    // kLocalPoints points in every precision mode; more, up to kLocalMax,
-    // with the sieve
+    // one set in plain mode. Up to kLocalPoints points: one workgroup, the
+    // points in LDS, in every precision mode. More: past the sieve, unless
+    // the sample shows a ring of points, which the batch kernels cut into
+    // pockets (below 2^16 points) or the streaming path takes. (From 2^16
+    // points the streaming switch and a tuned path still choose.)
     bool ring = false;
-    if (nsets == 1 && !d_set_off && plain && (N <= kLocalPoints || (N <= kLocalMax && sieve))) {
-        LocalArgs l{a.xy, (int)N, d_out, out_cap, nullptr, a.fp64, sieve, ctx->lstat};
+    const bool whole = nsets == 1 && !d_set_off && plain;
+    if (whole && N <= kLocalPoints) {
+        LocalArgs l{a.xy, (int)N, d_out, out_cap, a.fp64, ctx->lstat};
         ctx->nl = 0;
         if (time_open(ctx, "k_local_one", st) != SQH_OK) return SQH_EDEVICE;
         HIP_OK(launch_local_one(l, st));
         if (time_close(ctx, "k_local_one", st) != SQH_OK) return SQH_EDEVICE;
         HIP_OK(hipStreamSynchronize(st));
-        if (!ctx->lstat->left) return collect_local(ctx, N, out_cap, h_total);
-        ring = true;  // a ring of points: the batch kernels cut it into pockets
+        return collect_local(ctx, N, out_cap, h_total);
+    }
+    if (whole && sieve && (N < kStreamMin || a.stream)) {
+        SieveArgs v{};
+        v.xy = a.xy;
+        v.n = (int)N;
+        v.out = d_out;
+        v.cap = out_cap;
+        v.status = ctx->lstat;
+        for (int b = 0; b < 2; ++b) {
+            v.X[b] = a.X[b];
+            v.Y[b] = a.Y[b];
+            v.I[b] = a.I[b];
+        }
+        v.lxy = a.xy2;
+        v.lid = a.ids2;
+        v.lcnt = a.wprefix;
+        v.ctl = reinterpret_cast<SieveCtl*>(a.slots);
+        ctx->nl = 0;
+        HIP_OK(launch_sieve(v, ctx->cus, st, launch_mark, ctx));
+        HIP_OK(hipStreamSynchronize(st));
+        if (ctx->lstat->left == 2) {
+            HIP_OK(launch_rest(v, ctx->cus, st, launch_mark, ctx));
+            HIP_OK(hipStreamSynchronize(st));
+        }
+        if (!ctx->lstat->left) {
+            rc = collect_local(ctx, N, out_cap, h_total);
+            if (a.stream) {
+                ctx->stats.stream_path = 1;
+                ctx->stats.line_filter = ctx->lstat->line;
+            }
+            return rc;
+        }
+        ring = N < kStreamMin;
     }
     // several sets: each on a workgroup of its own (4096 sets of 64M points:
     // 15.9 ms on the persistent kernel, whose every pass streams all sets'

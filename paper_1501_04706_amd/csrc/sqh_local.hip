@@ -34,9 +34,13 @@ __device__ __forceinline__ void counters_sum(const Counters& ctr, uint32_t* c)
     }
 }
 
-// One set of n points, the hull to out (first cap vertices), the status to
-// the host. Sets of more than P points go through the sieve.
-template <int T, int P, bool SIEVE>
+}  // namespace sqh
+#include "sqh_sieve_large.hpp"
+namespace sqh {
+
+// One set of at most P points, the hull to out (first cap vertices), the
+// status to the host.
+template <int T, int P>
 __global__ __launch_bounds__(T) void k_local_one(LocalArgs a)
 {
     __shared__ SolveLds<P> L;
@@ -49,20 +53,11 @@ __global__ __launch_bounds__(T) void k_local_one(LocalArgs a)
     if (t < 3) csum[t] = 0u;
     if (t == 0) L.bad = 0;
     __syncthreads();
-    const bool f64 = a.fp64 != 0;
-    int h;
-    if constexpr (SIEVE) {
-        int sample;
-        h = solve_set<T, P>(L, a.xy, a.n, f64, ctr, &st, &sample);
-    } else {
-        const int cnt = load_points<T, P>(L, a.xy, a.n, a.n);
-        h = L.bad ? kSetBad : (cnt == 0 ? 0 : solve<T, P, true>(L, cnt, 0, 0, f64, ctr, &st));
-    }
+    const int cnt = load_points<T, P>(L, a.xy, a.n, a.n);
+    const int h = L.bad ? kSetBad : (cnt == 0 ? 0 : solve<T, P, true>(L, cnt, 0, 0, a.fp64 != 0, ctr, &st));
     counters_sum(ctr, csum);
-    if (h > 0) {
-        for (int r = t; r < h; r += T)
-            if (r < a.cap) gst(a.out + r, L.id[L.ring[r]]);
-    }
+    for (int r = t; r < h; r += T)
+        if (r < a.cap) gst(a.out + r, L.id[L.ring[r]]);
     __syncthreads();
     LocalStatus* s = a.status;
     if (t < kSolvePasses) {
@@ -72,31 +67,26 @@ __global__ __launch_bounds__(T) void k_local_one(LocalArgs a)
     if (t == 0) {
         s->h = h > 0 ? h : 0;
         s->err = h == kSetBad ? kErrNonFinite : 0;
-        s->left = h == kSetDense ? 1 : 0;
+        s->left = 0;
         s->passes = st.passes;
         s->first_v = st.pass_v[0];
+        s->line = 0;
         s->orient = csum[0];
         s->orient_exact = csum[1];
         s->cmp_exact = csum[2];
         s->t0 = t0;
         s->t1 = wall_clock64();
-        if (a.out_off && h >= 0) {
-            a.out_off[0] = 0;
-            a.out_off[1] = h;
-        }
     }
 }
 
-// Up to 1024 points four waves hold the set, up to 4096 sixteen; more go past
-// the sieve first. One ordinary launch, status straight to host memory: 124 us
-// a call before (a reset, a cooperative launch of every compute unit and a
-// copy back) and 32 us now for 1000 points of a square (15 us on the device),
-// 242 and 68 us for 20,011 points of a disk.
+// Up to 1024 points four waves hold the set, up to 4096 sixteen. One ordinary
+// launch, status straight to host memory: 124 us a call before (a reset, a
+// cooperative launch of every compute unit and a copy back) and 32 us now for
+// 1000 points of a square (15 us on the device).
 hipError_t launch_local_one(const LocalArgs& a, hipStream_t st)
 {
-    if (a.n <= kSmallP) k_local_one<kSmallT, kSmallP, false><<<1, kSmallT, 0, st>>>(a);
-    else if (a.n <= kMidP) k_local_one<kMidT, kMidP, false><<<1, kMidT, 0, st>>>(a);
-    else k_local_one<kMidT, kMidP, true><<<1, kMidT, 0, st>>>(a);
+    if (a.n <= kSmallP) k_local_one<kSmallT, kSmallP><<<1, kSmallT, 0, st>>>(a);
+    else k_local_one<kMidT, kMidP><<<1, kMidT, 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -653,6 +643,7 @@ __global__ __launch_bounds__(kEmitT) void k_batch_emit(BatchArgs a)
             s->left = ctl->err ? 0 : ctl->left;
             s->passes = ctl->passes;
             s->first_v = ctl->pass_v[0];
+            s->line = 0;
             s->orient = ctl->orient;
             s->orient_exact = ctl->orient_exact;
             s->cmp_exact = ctl->cmp_exact;
@@ -674,6 +665,49 @@ hipError_t launch_batch(const BatchArgs& a, int cus, hipStream_t st)
         k_batch_ring<<<std::min(a.G, 4 * cus), kRingT, 0, st>>>(a);
     }
     k_batch_emit<<<std::min((a.G + 3) / 4, 4 * cus), kEmitT, 0, st>>>(a);
+    return hipGetLastError();
+}
+
+size_t sieve_ctl_bytes() { return sizeof(SieveCtl); }
+
+// Up to kSieveSmall points one workgroup's sample of 1024 leaves few enough
+// points (3.3 % of a disk); the larger sample of up to 128K points leaves
+// 0.13 % plus the polygon's own 0.04 %, so up to kSieveMid the sieve's last
+// workgroup can solve them, and from there the second polygon is expected.
+// The sieve's workgroups take at least 2048 points each. *rest: what k_rest
+// needs if the status asks for it (left == 2).
+constexpr int kSieveSmall = 100'000, kSieveMid = 1'500'000;
+hipError_t launch_sieve(const SieveArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx)
+{
+    const int npairs = a.n >> 1;
+    const bool mid = a.n <= kSieveMid;
+    const int ns = std::max(1, std::min({mid ? cus : 2 * cus, kSieveGrid, npairs / 1024}));
+    const int share = 2 * ((((npairs + ns - 1) / ns) + 63) & ~63);
+    auto timed = [&](const char* name, auto&& launch) {
+        mark(ctx, name, 1, st);
+        launch();
+        mark(ctx, name, 0, st);
+    };
+    const int ne = a.n <= kSieveSmall ? 0 : std::min(kExtremeGrid, cus);
+    if (ne) timed("k_extreme", [&] { k_extreme<<<ne, kExtremeT, 0, st>>>(a); });
+    timed("k_polygon", [&] { k_polygon<<<1, 1024, 0, st>>>(a, ne); });
+    if (mid) {
+        timed("k_sieve_solve", [&] { k_sieve_solve<<<ns, kMidT, 0, st>>>(a, share); });
+    } else {
+        timed("k_sieve", [&] { k_sieve<<<ns, kSieveT, 0, st>>>(a); });
+        timed("k_rest", [&] { k_rest<<<std::min(64, cus), kMidT, 0, st>>>(a, ns, share, 1); });
+    }
+    return hipGetLastError();
+}
+// The points k_sieve_solve found too many (their second polygon is not there:
+// kLocalPoints at a time).
+hipError_t launch_rest(const SieveArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx)
+{
+    const int npairs = a.n >> 1, ns = std::max(1, std::min({cus, kSieveGrid, npairs / 1024}));
+    const int share = 2 * ((((npairs + ns - 1) / ns) + 63) & ~63);
+    mark(ctx, "k_rest", 1, st);
+    k_rest<<<cus, kMidT, 0, st>>>(a, ns, share, 0);
+    mark(ctx, "k_rest", 0, st);
     return hipGetLastError();
 }
 

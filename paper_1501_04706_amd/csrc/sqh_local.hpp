@@ -12,28 +12,50 @@ constexpr int kLocalStatPasses = 64;  // passes whose sizes are noted
 struct LocalStatus {
     int h;      // hull vertices (all sets)
     int err;    // kErr* flags
-    int left;   // 1: nothing was written, the general path has to run
+    int left;   // 1: nothing was written, the general path has to run; 2: launch_rest has to
     int passes;
     int first_v;
+    int line;   // the sieve's edges took the static line filter
     unsigned long long orient, orient_exact, cmp_exact;
     unsigned long long t0, t1;  // device clock (100 MHz) at the call's start and end
     int pass_v[kLocalStatPasses], pass_s[kLocalStatPasses];
 };
 
+// Called before (open) and after every launch of a call.
+typedef int (*LaunchMark)(void* ctx, const char* name, int open, hipStream_t st);
+
+// One set of at most kLocalPoints points on one workgroup.
 struct LocalArgs {
     const float2* xy;
     int n;
     int32_t* out;
     int64_t cap;
-    int64_t* out_off;  // null, or {0, h} of a batch of one set
     int fp64;
-    int sieve;         // larger sets: the sieve may be used
     LocalStatus* status;
 };
-
-// One set of at most kLocalMax points on one workgroup.
-constexpr int kLocalMax = 65535;
 hipError_t launch_local_one(const LocalArgs& a, hipStream_t st);
+
+// One set of more than kLocalPoints points past the sieve: the polygon of a
+// sample's extreme points, every point against its slabs and edges, and the
+// hull of the points left.
+struct SieveCtl;
+struct SieveArgs {
+    const float2* xy;
+    int n;
+    int32_t* out;
+    int64_t cap;
+    LocalStatus* status;
+    float* X[2];       // n each: points past the slabs, points past the edges
+    float* Y[2];
+    int* I[2];
+    float2* lxy;       // n: chunk hulls
+    int* lid;
+    int* lcnt;         // n / 64 or more: their sizes
+    SieveCtl* ctl;
+};
+size_t sieve_ctl_bytes();
+hipError_t launch_sieve(const SieveArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx);
+hipError_t launch_rest(const SieveArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx);
 
 // A batch of sets (at most kBatchSetMax points each; larger ones leave the
 // whole batch to the general path).
@@ -56,10 +78,10 @@ struct BatchArgs {
     int* order;        // G: sets by size class
     int* hbuf;         // N: each set's hull from its first slot
     float* slots;      // 3 N words: pocket points
+    float* slots2;     // 3 N words: ring nodes
     Pocket* pockets;   // pocket records ...
     int* todo[3];      // ... and their indices by solver size
     int pocket_cap;
-    float* slots2;     // 3 N words: ring nodes
     DenseSet* dense;
     int dense_cap;
     BatchCtl* ctl;

@@ -200,6 +200,8 @@ __device__ __forceinline__ double orient64(float ox, float oy, float ex, float e
 // (the _inl form is for code that must not contain calls)
 __device__ __forceinline__ int orient_exact_inl(float ox, float oy, float ex, float ey, float px, float py)
 {
+    // both products vanish (axis-parallel edges, copies of an end point)
+    if ((ex == ox || py == oy) && (ey == oy || px == ox)) return 0;
     double bound;
     const double d = orient64(ox, oy, ex, ey, px, py, bound);
     if (d > bound) return 1;

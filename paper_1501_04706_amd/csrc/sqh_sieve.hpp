@@ -43,9 +43,9 @@ __device__ __forceinline__ float up32(double v)
     return (double)f < v ? nextafterf(f, INFINITY) : f;
 }
 
-// Slabs of the convex polygon L.ring[0 .. h) (counter-clockwise from its
-// lexicographic minimum) into bins[0 .. NB) (L.bins or another array that
-// the solve does not use). `kb` is one LDS word. Ends with a barrier.
+// Slabs of the convex polygon v[0 .. h) (LDS, counter-clockwise from its
+// lexicographic minimum; h < 3 gives empty slabs) into bins[0 .. NB). *kb (an
+// LDS word) receives the place of its maximum. Starts and ends with a barrier.
 //
 // Slabs 0 and NB - 1 reach past the polygon's x range and stay empty; they
 // cover almost none of it (2^-6 of a slab's width). The x of slab b lie in
@@ -55,25 +55,28 @@ __device__ __forceinline__ float up32(double v)
 // and the upper one concave, so their values at the two ends bound them on
 // the slab; the evaluation in float64 errs by less than 2^-49 max |y|, and
 // the interval is narrowed by 2^-40 max |y| before it is rounded inwards.
-template <int T, int P>
-__device__ __forceinline__ Slabs build_slabs(const SolveLds<P>& L, int h, float2* bins, int NB, int* kb)
+template <int T>
+__device__ __forceinline__ Slabs build_slabs(const float2* v, int h, float2* bins, int NB, int* kb)
 {
     const int t = (int)threadIdx.x;
-    auto pt = [&](int r) { return L.xy[L.ring[r >= h ? r - h : r]]; };
-    for (int r = t; r < h; r += T) {
-        const float2 p = pt(r), q = pt(r + 1), o = pt(r + h - 1);
-        const bool after = (p.x > q.x || (p.x == q.x && p.y > q.y)) && (p.x > o.x || (p.x == o.x && p.y > o.y));
-        if (after) *kb = r;  // the lexicographic maximum (one local maximum on a convex ring)
+    lds_barrier();
+    if (t == 0 && h < 3) *kb = 0;
+    if (h >= 3) {
+        for (int r = t; r < h; r += T) {
+            const float2 p = v[r], q = v[r + 1 < h ? r + 1 : 0], o = v[r > 0 ? r - 1 : h - 1];
+            const bool after = (p.x > q.x || (p.x == q.x && p.y > q.y)) && (p.x > o.x || (p.x == o.x && p.y > o.y));
+            if (after) *kb = r;  // the lexicographic maximum (one local maximum on a convex ring)
+        }
     }
     lds_barrier();
     const int kB = *kb;
-    const float2 A = pt(0);
-    const float xa = A.x, xb = h > 1 ? pt(kB).x : xa;
+    auto pt = [&](int r) { return v[r >= h ? r - h : r]; };
+    const float xa = h >= 3 ? v[0].x : 0.0f, xb = h >= 3 ? v[kB].x : 0.0f;
     const float ext = xb - xa;
     Slabs s;
     s.last = (uint32_t)(NB - 1);
     s.scale = ((float)(NB - 2) + 0x1p-5f) / ext;
-    const bool ok = h >= 3 && ext > 0x1p-100f && ext < 0x1p100f;
+    const bool ok = ext > 0x1p-100f && ext < 0x1p100f;
     if (!ok) {
         s.scale = 0.0f;
         s.x0 = 0.0f;
@@ -82,7 +85,7 @@ __device__ __forceinline__ Slabs build_slabs(const SolveLds<P>& L, int h, float2
     }
     const double w = ok ? 1.0 / (double)s.scale : 0.0, x0 = (double)s.x0, ex = fabs(x0) * 0x1p-48;
     for (int b = t; b < NB; b += T) {
-        float2 v = make_float2(INFINITY, -INFINITY);
+        float2 iv = make_float2(INFINITY, -INFINITY);
         const double xl = x0 + (double)b * w * (1.0 - 0x1p-20) - ex, xr = x0 + (double)(b + 1) * w * (1.0 + 0x1p-20) + ex;
         if (ok && xl >= (double)xa && xr < (double)xb) {
             // the last node of the lower chain (0 .. kB) at or left of xl and
@@ -117,13 +120,64 @@ __device__ __forceinline__ Slabs build_slabs(const SolveLds<P>& L, int h, float2
                 else hi = fmin(hi, y);
             }
             const double m = my * 0x1p-40 + 0x1p-160;
-            v.x = up32(lo + m);
-            v.y = down32(hi - m);
+            iv.x = up32(lo + m);
+            iv.y = down32(hi - m);
         }
-        bins[b] = v;
+        bins[b] = iv;
     }
     lds_barrier();
     return s;
+}
+
+// The same polygon as two x-sorted chains, exactly: true if p is in the closed
+// polygon and at none of its vertices (so that it is no hull vertex; a copy of
+// a vertex stays). The lower and the upper edge over its x are certified by
+// the static line filter where it applies (line), else by the semi-static one;
+// the points neither certifies, long collinear runs on the border among them,
+// are settled exactly.
+__device__ __forceinline__ bool chain_inside(const float2* v, int h, int kB, bool line, float Mx, float My, float x,
+                                             float y, uint32_t& n_exact)
+{
+    const float2 A = v[0], B = v[kB];
+    if (!(x >= A.x && x <= B.x)) return false;
+    // the last node of 0 .. kB - 1 at or left of x, of kB .. h - 1 at or right of it
+    int l0 = 0, u0 = kB, l1 = kB, u1 = h;
+    for (int k = max(kB, h - kB); k > 1; k = (k + 1) >> 1) {
+        const int m0 = (l0 + u0) >> 1, m1 = (l1 + u1) >> 1;
+        const float x0 = v[m0].x, x1 = v[m1].x;
+        const bool g0 = x0 <= x, g1 = x1 >= x, o0 = u0 - l0 > 1, o1 = u1 - l1 > 1;
+        l0 = (o0 & g0) ? m0 : l0;
+        u0 = (o0 & !g0) ? m0 : u0;
+        l1 = (o1 & g1) ? m1 : l1;
+        u1 = (o1 & !g1) ? m1 : u1;
+    }
+    const float2 o[2] = {v[l0], v[l1]}, e[2] = {v[l0 + 1], v[l1 + 1 < h ? l1 + 1 : 0]};
+    bool sure = x > A.x && x < B.x, out = false;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const float dx = e[k].x - o[k].x, dy = e[k].y - o[k].y;
+        float d, m;
+        if (line) {
+            const float c = dy * o[k].x - dx * o[k].y;
+            m = (fabsf(dx) * My + fabsf(dy) * Mx) * 0x1p-19f + kFilterTau;
+            d = fmaf(-dy, x, fmaf(dx, y, c));
+            if (!(fabsf(y) <= My)) d = 0.0f;  // (past the polygon's extent: not certified)
+        } else {
+            const Orient32 w = orient32p(o[k].x, o[k].y, e[k].x, e[k].y, x, y);
+            d = w.d; m = w.es;
+        }
+        out |= d < -m;
+        sure &= d > m;
+    }
+    if (out || sure) return sure && !out;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        ++n_exact;
+        if (orient_exact(o[k].x, o[k].y, e[k].x, e[k].y, x, y) < 0) return false;
+        if (o[k].x == e[k].x && !(y >= fminf(o[k].y, e[k].y) && y <= fmaxf(o[k].y, e[k].y))) return false;
+        if ((x == o[k].x && y == o[k].y) || (x == e[k].x && y == e[k].y)) return false;
+    }
+    return true;
 }
 
 // Points i * n / m, i = 0 .. m - 1 (m <= P; all of them if m == n) into
@@ -183,7 +237,10 @@ __device__ __forceinline__ int solve_set(SolveLds<P>& L, const float2* xy, int n
             *sample = first ? h : 0;
             return kSetDense;
         }
-        const Slabs sl = build_slabs<T, P>(L, h, L.bins, T, &s_kb);
+        // (the ring's coordinates past the slabs, in order)
+        static_assert(T + P / 2 <= P, "slabs and ring share the keys' space");
+        for (int r = t; r < h; r += T) L.bins[T + r] = L.xy[L.ring[r]];
+        const Slabs sl = build_slabs<T>(L.bins + T, h, L.bins, T, &s_kb);
         if (first) {
             // the sample's vertices come back with the stream
             first = false;

@@ -160,7 +160,7 @@ template <int T, int P, bool WHOLE>
 __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bool f64, Counters& ctr,
                                      SolveStats* st)
 {
-    constexpr int R = P / T, kPair = 2;
+    constexpr int R = P / T, kPair = R > 1 ? 2 : 1;
     static_assert(R % kPair == 0, "points go in pairs");
     static_assert(P % T == 0 && P <= 0xfff0, "positions are 16-bit");
     const int t = (int)threadIdx.x, lane = lane_id();

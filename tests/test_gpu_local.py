@@ -1,7 +1,8 @@
-"""GPU parity of the workgroup-local hulls (sets of up to 65535 points on one
-workgroup) against the oracle: at the sizes where a thread, a workgroup or
-the LDS is exactly full, on inputs the sample does not represent, and on the
-error paths. Hull index lists are integer results: the bar is equality."""
+"""GPU parity of the workgroup-local kernels (small sets in LDS, sets past the
+sieve, batches, rings in pockets) against the oracle: at the sizes where a
+thread, a workgroup, the LDS or a launch shape is exactly full, on inputs the
+sample does not represent, and on the error paths. Hull index lists are
+integer results: the bar is equality."""
 import sys
 
 import numpy as np
@@ -99,6 +100,31 @@ def test_errors_and_capacity(H, n):
     assert rc == sqh.SQH_OK and [int(v) for v in out.cpu().numpy()] == expect + [-7] * 8
     rc, h = sqh.sqh_hull(H.ctx, t, n, out, out.numel(), ws, 16)
     assert rc == sqh.SQH_ENOMEM
+
+
+@pytest.mark.parametrize("n", [100_000, 100_001, 1_500_000, 1_500_001])
+def test_sieve_sizes(H, n):
+    """Both sides of the sieve's launch shapes; what its sample misses, keeps
+    whole (copies) or cannot use (flat sets), more points left than one
+    workgroup takes, and non-finite coordinates wherever they are."""
+    rng = np.random.default_rng(n)
+    cases = [c for c in shapes(n) if c[0] not in ("parabola", "large", "tiny")]
+    tri = np.float32([[0, 0], [1, 0], [0.25, 1]])
+    cases += [("copies of three points", tri[rng.integers(0, 3, n)]),
+              ("flat", (workloads.disk(n, 2) * np.float32([1.0, 1e-6])).astype(np.float32)),
+              ("outer tenth copied", np.where((rng.random(n) < 0.1)[:, None], tri[rng.integers(0, 3, n)],
+                                              workloads.disk(n, 3) * np.float32(0.1) + np.float32(0.4)).astype(np.float32)),
+              ("grid", workloads.grid(n, 4, side=64))]
+    for name, xy in cases:
+        print(f"[case] sieve {name} n={n}", file=sys.stderr, flush=True)
+        assert gpu(H, xy) == [int(v) for v in oracle.c_hull(xy)], name
+    d = workloads.disk(n, 5) * np.float32(0.5)
+    for at in (0, n // 3, n - 1):
+        z = d.copy()
+        z[at, 1] = np.nan
+        with pytest.raises(sqh.SqhError) as e:
+            gpu(H, z)
+        assert e.value.code == sqh.SQH_EINVAL
 
 
 def rings(n):
