@@ -161,36 +161,59 @@ __device__ __forceinline__ int orient_of(float2 o, float2 e, float2 p, Counters&
     return orient_exact(o.x, o.y, e.x, e.y, p.x, p.y);
 }
 
-// Sorts 64 R keys over the wave, element lane * R + r ascending (bitonic).
-template <int R>
-__device__ __forceinline__ void wave_sort(uint32_t (&k)[R])
+// x of lane ^ D, without the LDS crossbar: row permutes up to 8, the row and half
+// swaps above.
+template <int D>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x)
+{
+    constexpr int kQuad1 = 0xb1, kQuad2 = 0x4e, kQuad3 = 0x1b, kRor8 = 0x128, kHalfMirror = 0x141;
+    const int v = (int)x;
+    if (D == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, v, kQuad1, 0xf, 0xf, true);
+    if (D == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, v, kQuad2, 0xf, 0xf, true);
+    if (D == 4)
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, v, kHalfMirror, 0xf, 0xf, true), kQuad3, 0xf,
+                                                     0xf, true);
+    if (D == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, v, kRor8, 0xf, 0xf, true);
+    if (D == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return (lane_id() & 16) ? r[0] : r[1];
+    }
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return (lane_id() & 32) ? r[0] : r[1];
+}
+
+// One step of the sort below: elements D apart, in runs of SIZE.
+template <int R, int SIZE, int D>
+__device__ __forceinline__ void wave_sort_step(uint32_t (&k)[R])
 {
     const int lane = lane_id();
+    if constexpr (D >= R) {
+        constexpr int LD = D / R;
+        // (every register of a lane sorts the same way here)
+        const bool up = ((lane * R) & SIZE) == 0, low = (lane & LD) == 0;
 #pragma unroll
-    for (int size = 2; size <= 64 * R; size <<= 1) {
+        for (int r = 0; r < R; ++r) {
+            const uint32_t o = lane_xor<LD>(k[r]);
+            k[r] = (up == low) ? min(k[r], o) : max(k[r], o);
+        }
+    } else {
 #pragma unroll
-        for (int d = size >> 1; d >= 1; d >>= 1) {
-            if (d >= R) {
-                const int ld = d / R;
-                // (every register of a lane sorts the same way here)
-                const bool up = ((lane * R) & size) == 0, low = (lane & ld) == 0;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const uint32_t o = (uint32_t)__shfl_xor((int)k[r], ld);
-                    k[r] = (up == low) ? min(k[r], o) : max(k[r], o);
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    if (r & d) continue;
-                    const bool up = ((lane * R + r) & size) == 0;
-                    const uint32_t a = k[r], b = k[r + d], lo = min(a, b), hi = max(a, b);
-                    k[r] = up ? lo : hi;
-                    k[r + d] = up ? hi : lo;
-                }
-            }
+        for (int r = 0; r < R; ++r) {
+            if (r & D) continue;
+            const bool up = ((lane * R + r) & SIZE) == 0;
+            const uint32_t a = k[r], b = k[r + D], lo = min(a, b), hi = max(a, b);
+            k[r] = up ? lo : hi;
+            k[r + D] = up ? hi : lo;
         }
     }
+    if constexpr (D > 1) wave_sort_step<R, SIZE, D / 2>(k);
+}
+// Sorts 64 R keys over the wave, element lane * R + r ascending (bitonic).
+template <int R, int SIZE = 2>
+__device__ __forceinline__ void wave_sort(uint32_t (&k)[R])
+{
+    wave_sort_step<R, SIZE, SIZE / 2>(k);
+    if constexpr (SIZE < 64 * R) wave_sort<R, SIZE * 2>(k);
 }
 
 constexpr int kWavePts = 256;  // points of a wave's pocket
@@ -200,22 +223,32 @@ struct WaveLds {
     int id[kWavePts];
 };
 
+// Whether p comes before q about c, certainly: the float64 cross product beyond
+// its rounding (differences and products: less than 2^-51 of the products' sum).
+__device__ __forceinline__ bool before_sure(float2 c, float2 p, float2 q)
+{
+    const double P = ((double)p.x - c.x) * ((double)q.y - c.y), Q = ((double)p.y - c.y) * ((double)q.x - c.x);
+    return P - Q > (fabs(P) + fabs(Q)) * 0x1p-50;
+}
+
 template <int R>
 __device__ __forceinline__ void wave_order(WaveLds& W, int n, float2 c, float2 A, float2 B)
 {
     const int lane = lane_id();
-    const float ax = A.x - c.x, ay = A.y - c.y, bx = B.x - c.x, by = B.y - c.y;
+    const double ax = (double)A.x - c.x, ay = (double)A.y - c.y, bx = (double)B.x - c.x, by = (double)B.y - c.y;
     uint32_t key[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int i = lane + 64 * r;
         key[r] = 0xffffff00u | (uint32_t)(i & 255);
         if (i < n) {
-            // 0 at A, 1 at B, increasing with the angle
+            // 0 at A, 1 at B, increasing with the angle (in float64: a
+            // narrow pocket's points look alike to float32)
             const float2 p = W.xy[0][i];
-            const float x = p.x - c.x, y = p.y - c.y;
-            const float u = ax * y - ay * x, v = x * by - y * bx;
-            const float f = fminf(fmaxf(u / (u + v), 0.0f), 1.0f);  // (NaN becomes 0: any order will do here)
+            const double x = (double)p.x - c.x, y = (double)p.y - c.y;
+            const double u = ax * y - ay * x, v = x * by - y * bx;
+            const float g = (float)u * __builtin_amdgcn_rcpf((float)(u + v));
+            const float f = fminf(fmaxf(g, 0.0f), 1.0f);  // (NaN becomes 0: any order will do here)
             key[r] = (min((uint32_t)(f * 16777216.0f), 0xfffffeu) << 8) | (uint32_t)i;
         }
     }
@@ -231,8 +264,10 @@ __device__ __forceinline__ void wave_order(WaveLds& W, int n, float2 c, float2 A
 }
 
 // One wave: the n <= 256 points W.xy[0], W.id in order about c and without
-// those that are not strictly convex from A to B. Returns how many are left
-// and in which buffer (f).
+// those that are not strictly convex from A to B (points of the set), or, OPEN,
+// between the first and the last of them (A and B only lie on rays around
+// them). Returns how many are left and in which buffer (f).
+template <bool OPEN>
 __device__ __forceinline__ int wave_chain(WaveLds& W, int n, float2 c, float2 A, float2 B, int& f, Counters& ctr)
 {
     const int lane = lane_id();
@@ -245,16 +280,14 @@ __device__ __forceinline__ int wave_chain(WaveLds& W, int n, float2 c, float2 A,
     bool unsure = false;
     for (int i = lane; i + 1 < n; i += 64) {
         const float2 p = W.xy[1][i], q = W.xy[1][i + 1];
-        const Orient32 o = orient32p(c.x, c.y, p.x, p.y, q.x, q.y);
-        unsure |= !(o.d > o.es);
+        unsure |= !before_sure(c, p, q);
     }
     if (__ballot(unsure)) {
         for (int sweep = 0, still = 0; still < 2 && sweep < 2 * kWavePts + 2; ++sweep) {
             bool swapped = false;
             for (int i = 2 * lane + (sweep & 1); i + 1 < n; i += 128) {
                 const float2 p = W.xy[1][i], q = W.xy[1][i + 1];
-                const Orient32 o = orient32p(c.x, c.y, p.x, p.y, q.x, q.y);
-                if (o.d > o.es) continue;
+                if (before_sure(c, p, q)) continue;
                 const uint8_t pa = W.at[1][i], qa = W.at[1][i + 1];
                 ++ctr.orient_exact;
                 if (around(c, p, W.id[pa], q, W.id[qa]) > 0) {
@@ -278,8 +311,10 @@ __device__ __forceinline__ int wave_chain(WaveLds& W, int n, float2 c, float2 A,
                 p = W.xy[f][i];
                 const float2 o = i > 0 ? W.xy[f][i - 1] : A, q = i + 1 < n ? W.xy[f][i + 1] : B;
                 // a copy goes; the first of some copies waits for them to go
-                const bool copy = p.x == o.x && p.y == o.y, twin = p.x == q.x && p.y == q.y;
-                keep = !copy && (twin || orient_of(o, p, q, ctr) > 0);
+                const bool copy = (!OPEN || i > 0) && p.x == o.x && p.y == o.y;
+                const bool twin = (!OPEN || i + 1 < n) && p.x == q.x && p.y == q.y;
+                const bool end = OPEN && (i == 0 || i == n - 1);
+                keep = !copy && (twin || end || orient_of(o, p, q, ctr) > 0);
             }
             const uint64_t M = __ballot(keep);
             if (keep) {

@@ -66,7 +66,7 @@ StatusOffsets status_offsets()
 
 bool make_layout(int64_t N, int64_t nsets, Layout& L)
 {
-    static const size_t ctl_bytes = std::max(sieve_ctl_bytes(), batch_ctl_bytes());
+    static const size_t ctl_bytes = std::max({sieve_ctl_bytes(), batch_ctl_bytes(), ring_ctl_bytes()});
     if (N < 0 || nsets < 1 || N > (int64_t)INT32_MAX - 2 || nsets > (int64_t)INT32_MAX / 8) return false;
     L.N = N;
     L.nsets = nsets;
@@ -578,8 +578,10 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
     // one set in plain mode. Up to kLocalPoints points: one workgroup, the
     // points in LDS, in every precision mode. More: past the sieve, unless
     // the sample shows a ring of points, which the batch kernels cut into
-    // pockets (below 2^16 points) or the streaming path takes. (From 2^16
-    // points the streaming switch and a tuned path still choose.)
+    // pockets (below 2^16 points: 40 us of launches less) or the ring kernels
+    // over the whole chip. What they leave (a centre outside the hull, pockets
+    // that float32 rays cannot tell apart) the streaming path takes. (From
+    // 2^16 points the streaming switch and a tuned path still choose.)
     bool ring = false;
     const bool whole = nsets == 1 && !d_set_off && plain;
     if (whole && N <= kLocalPoints) {
@@ -623,6 +625,31 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
             return rc;
         }
         ring = N < kStreamMin;
+        if (!ring) {
+            // (5M points of a circle: 1530 us on the streaming path, 395 us so)
+            RingArgs r{};
+            r.xy = a.xy;
+            r.n = (int)N;
+            r.out = d_out;
+            r.cap = out_cap;
+            r.line = ctx->lstat->line;
+            r.status = ctx->lstat;
+            r.wid = reinterpret_cast<uint16_t*>(a.vidx);
+            r.off = a.shist;
+            r.slots = reinterpret_cast<float4*>(a.recs);
+            r.slots2 = reinterpret_cast<float4*>(a.X[0]);
+            r.pockets = reinterpret_cast<RingPocket*>(a.segs[0]);
+            r.pocket_cap = (int)(N / 64 + 512);
+            r.ctl = reinterpret_cast<RingCtl*>(a.slots);
+            HIP_OK(launch_ring(r, ctx->cus, st, launch_mark, ctx));
+            HIP_OK(hipStreamSynchronize(st));
+            if (!ctx->lstat->left) {
+                rc = collect_local(ctx, N, out_cap, h_total);
+                ctx->stats.stream_path = 2;
+                ctx->stats.line_filter = ctx->lstat->line;
+                return rc;
+            }
+        }
     }
     // several sets: each on a workgroup of its own (4096 sets of 64M points:
     // 15.9 ms on the persistent kernel, whose every pass streams all sets'

@@ -34,8 +34,33 @@ __device__ __forceinline__ void counters_sum(const Counters& ctr, uint32_t* c)
     }
 }
 
+// A call's counters, a line to every 32nd workgroup: atomics on one address
+// follow each other at 14 ns, so that the counts of some thousand waves took
+// longer than the kernels that made them (60 of 94 us of the sieve on a grid,
+// 120 of 210 us of a circle's pockets).
+constexpr int kCtrSlots = 32;
+struct alignas(128) CtrSlot {
+    unsigned long long c[3];
+};
+// Adds the workgroup's counters; sum: three words of LDS, zero before.
+__device__ __forceinline__ void ctr_flush(CtrSlot* slots, const Counters& ctr, uint32_t* sum)
+{
+    counters_sum(ctr, sum);
+    __syncthreads();
+    const int t = (int)threadIdx.x;
+    if (t < 3 && sum[t]) atomicAdd(&slots[(int)blockIdx.x % kCtrSlots].c[t], (unsigned long long)sum[t]);
+}
+__device__ __forceinline__ unsigned long long ctr_total(const CtrSlot* slots, int i)
+{
+    unsigned long long v = 0ull;
+#pragma unroll
+    for (int k = 0; k < kCtrSlots; ++k) v += __hip_atomic_load(&slots[k].c[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return v;
+}
+
 }  // namespace sqh
 #include "sqh_sieve_large.hpp"
+#include "sqh_ring.hpp"
 namespace sqh {
 
 // One set of at most P points, the hull to out (first cap vertices), the
@@ -395,7 +420,7 @@ __global__ __launch_bounds__(64 * kPocketWaves) void k_batch_pocket(BatchArgs a)
         }
         wave_sync();
         int f;
-        const int m = wave_chain(W, p.len, c, make_float2(p.ax, p.ay), make_float2(p.bx, p.by), f, ctr);
+        const int m = wave_chain<false>(W, p.len, c, make_float2(p.ax, p.ay), make_float2(p.bx, p.by), f, ctr);
         for (int q = lane; q < m; q += 64) {
             float* d = slot + 3 * (q + 1);
             gst(d, W.xy[f][q].x);
@@ -708,6 +733,29 @@ hipError_t launch_rest(const SieveArgs& a, int cus, hipStream_t st, LaunchMark m
     mark(ctx, "k_rest", 1, st);
     k_rest<<<cus, kMidT, 0, st>>>(a, ns, share, 0);
     mark(ctx, "k_rest", 0, st);
+    return hipGetLastError();
+}
+
+static_assert(sizeof(RingPocket) == 32, "pockets fit the segments' space");
+size_t ring_ctl_bytes() { return sizeof(RingCtl); }
+
+hipError_t launch_ring(const RingArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx)
+{
+    const int nb = std::max(1, std::min({2 * cus, kRingGrid, a.n / 4096}));
+    auto timed = [&](const char* name, auto&& launch) {
+        mark(ctx, name, 1, st);
+        launch();
+        mark(ctx, name, 0, st);
+    };
+    timed("k_ring_rays", [&] { k_ring_rays<<<1, 1024, 0, st>>>(a); });
+    timed("k_ring_count", [&] { k_ring_count<<<nb, 1024, 0, st>>>(a); });
+    timed("k_ring_scan", [&] { k_ring_scan<<<kRays / 64, 1024, 0, st>>>(a, nb); });
+    timed("k_ring_scatter", [&] { k_ring_scatter<<<nb, 1024, 0, st>>>(a); });
+    timed("k_ring_cut", [&] { k_ring_cut<<<kRays, 1024, 0, st>>>(a); });
+    timed("k_ring_pocket", [&] { k_ring_pocket<<<6 * cus, 64 * kRingWaves, 0, st>>>(a); });
+    timed("k_ring_wedge", [&] { k_ring_wedge<<<kRays, kWedgeT, 0, st>>>(a); });
+    timed("k_ring_join", [&] { k_ring_join<<<1, 1024, 0, st>>>(a); });
+    timed("k_ring_emit", [&] { k_ring_emit<<<64, kRingEmitT, 0, st>>>(a); });
     return hipGetLastError();
 }
 

@@ -57,6 +57,27 @@ size_t sieve_ctl_bytes();
 hipError_t launch_sieve(const SieveArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx);
 hipError_t launch_rest(const SieveArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx);
 
+// One large ring of points (a set the sieve left).
+struct RingCtl;
+struct RingPocket;
+struct RingArgs {
+    const float2* xy;
+    int n;
+    int32_t* out;
+    int64_t cap;
+    int line;            // passed on to the status
+    LocalStatus* status;
+    uint16_t* wid;       // n
+    int* off;            // 512 x 512 words
+    float4* slots;       // n: points by wedge, then wedge nodes
+    float4* slots2;      // n: points by pocket, then pocket nodes
+    RingPocket* pockets;
+    int pocket_cap;
+    RingCtl* ctl;
+};
+size_t ring_ctl_bytes();
+hipError_t launch_ring(const RingArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx);
+
 // A batch of sets (at most kBatchSetMax points each; larger ones leave the
 // whole batch to the general path).
 constexpr int kBatchSetMax = 1 << 20;

@@ -151,6 +151,44 @@ def test_single_rings(H, n):
         assert gpu(H, xy) == [int(v) for v in oracle.c_hull(xy)], name
 
 
+@pytest.mark.parametrize("n", [65536, 65537, 300_001, 1_000_003])
+def test_large_rings(H, n):
+    """Rings over the whole chip: wedges of every size, one that empties, a
+    pocket's points in several loads, centres that are no inner point."""
+    rng = np.random.default_rng(n)
+    sets = list(rings(n))
+    c = workloads.circle(n, 9)
+    heap = c.copy()
+    heap[rng.random(n) < 0.6] = c[17]  # copies: more of one point than a wave sorts
+    arc = rng.random(n) * 1.5
+    half = np.stack([np.cos(2 * arc), np.sin(2 * arc)], 1).astype(np.float32)
+    half[:5] = [[-1, -0.5], [1, -0.5], [0, -0.75], [-0.5, -0.625], [0.5, -0.625]]
+    sets += [("heap", heap), ("half", half), ("quarter", np.stack([np.cos(arc), np.sin(arc)], 1).astype(np.float32)),
+             ("beyond its frame", c + np.float32([300.0, 0.0])), ("tiny", c * np.float32(1e-20)),
+             ("filled", (c * np.where(np.arange(n) % 3, rng.random(n), 1.0)[:, None]).astype(np.float32))]
+    for name, xy in sets:
+        print(f"[case] large ring {name} n={n}", file=sys.stderr, flush=True)
+        assert gpu(H, xy) == [int(v) for v in oracle.c_hull(xy)], name
+
+
+def test_large_ring_errors(H):
+    import torch
+    c = workloads.circle(200_000, 3)
+    h = len(oracle.c_hull(c))
+    z = c.copy()
+    z[123_457, 1] = np.inf
+    with pytest.raises(sqh.SqhError) as e:
+        gpu(H, z)
+    assert e.value.code == sqh.SQH_EINVAL
+    d = torch.from_numpy(c).cuda()
+    out = torch.full((h + 8,), -7, dtype=torch.int32, device="cuda")
+    with pytest.raises(sqh.SqhError) as e:
+        H.hull(d, out=out[: h - 1])
+    assert e.value.code == sqh.SQH_ECAPACITY
+    assert out[h - 1 :].cpu().tolist() == [-7] * 9
+    assert gpu(H, c) == [int(v) for v in oracle.c_hull(c)]
+
+
 @pytest.mark.parametrize("n", [1024, 4096, 4097, 20_000, 160_000, 700_000])
 def test_batches(H, n):
     """Every kind of set in one batch, with empty sets and a ragged last one:
