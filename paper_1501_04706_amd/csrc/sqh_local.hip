@@ -121,19 +121,23 @@ constexpr int kClasses = 6;  // sets of up to 2^10, 2^12, 2^14, 2^16, 2^18, 2^20
 constexpr int kTasks = 3;  // pocket solvers: a wave, four waves, sixteen
 constexpr int kTaskT[kTasks] = {64, 256, 1024}, kTaskP[kTasks] = {kWavePts + 2, 1024, kLocalPoints};
 
+// The solvers' passes, a line or more to every 8th workgroup (as the counters).
+constexpr int kStatLines = 8;
+struct alignas(128) BatchStats {
+    int passes, pass_v[kSolvePasses], pass_s[kSolvePasses];
+};
 struct BatchCtl {
     int err, left;
     int n_small, n_big;         // queue lengths: class 0; classes 5 .. 1
     int head_big, n_task[kTasks];
     int n_pocket, n_dense;
-    int passes, pass_v[kSolvePasses], pass_s[kSolvePasses];
-    unsigned long long orient, orient_exact, cmp_exact, t0;
+    unsigned long long t0;
+    CtrSlot ctr[kCtrSlots];
+    BatchStats st[kStatLines];
 };
 static_assert(sizeof(Pocket) == 32, "pockets fit the child records' space");
 
 size_t batch_ctl_bytes() { return sizeof(BatchCtl); }
-size_t pocket_bytes() { return sizeof(Pocket); }
-size_t dense_bytes() { return sizeof(DenseSet); }
 
 // A workgroup's share of the batch's counters.
 struct BatchAcc {
@@ -148,19 +152,14 @@ __device__ __forceinline__ void acc_init(BatchAcc& A)
 }
 __device__ __forceinline__ void acc_flush(BatchAcc& A, const Counters& ctr, BatchCtl* ctl)
 {
-    counters_sum(ctr, A.c);
-    __syncthreads();
+    ctr_flush(ctl->ctr, ctr, A.c);
     const int t = (int)threadIdx.x;
+    BatchStats& S = ctl->st[(int)blockIdx.x % kStatLines];
     if (t < kSolvePasses) {
-        if (A.st.pass_v[t]) atomicAdd(&ctl->pass_v[t], A.st.pass_v[t]);
-        if (A.st.pass_s[t]) atomicAdd(&ctl->pass_s[t], A.st.pass_s[t]);
+        if (A.st.pass_v[t]) atomicAdd(&S.pass_v[t], A.st.pass_v[t]);
+        if (A.st.pass_s[t]) atomicAdd(&S.pass_s[t], A.st.pass_s[t]);
     }
-    if (t == 0) {
-        if (A.st.passes) atomicMax(&ctl->passes, A.st.passes);
-        if (A.c[0]) atomicAdd(&ctl->orient, (unsigned long long)A.c[0]);
-        if (A.c[1]) atomicAdd(&ctl->orient_exact, (unsigned long long)A.c[1]);
-        if (A.c[2]) atomicAdd(&ctl->cmp_exact, (unsigned long long)A.c[2]);
-    }
+    if (t == 0 && A.st.passes) atomicMax(&S.passes, A.st.passes);
 }
 
 __device__ __forceinline__ int set_class(int n)
@@ -399,9 +398,12 @@ constexpr int kPocketWaves = 4;
 __global__ __launch_bounds__(64 * kPocketWaves) void k_batch_pocket(BatchArgs a)
 {
     __shared__ WaveLds Ws[kPocketWaves];
+    __shared__ uint32_t csum[3];
     BatchCtl* ctl = a.ctl;
     const int nt = ctl->n_task[0];
     if (nt == 0 || (ctl->err | ctl->left)) return;
+    if (threadIdx.x < 3) csum[threadIdx.x] = 0u;
+    __syncthreads();
     const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
     WaveLds& W = Ws[w];
     Counters ctr = {0u, 0u, 0u};
@@ -435,11 +437,7 @@ __global__ __launch_bounds__(64 * kPocketWaves) void k_batch_pocket(BatchArgs a)
         }
         wave_sync();
     }
-    const uint32_t v[2] = {(uint32_t)wave_total((int)ctr.orient), (uint32_t)wave_total((int)ctr.orient_exact)};
-    if (lane == 0) {
-        if (v[0]) atomicAdd(&ctl->orient, (unsigned long long)v[0]);
-        if (v[1]) atomicAdd(&ctl->orient_exact, (unsigned long long)v[1]);
-    }
+    ctr_flush(ctl->ctr, ctr, csum);
 }
 
 // Larger pockets: the passes.
@@ -489,8 +487,11 @@ __global__ __launch_bounds__(kRingT) void k_batch_ring(BatchArgs a)
     __shared__ int red[W];
     __shared__ int s_start;
     __shared__ unsigned long long s_min;
+    __shared__ uint32_t csum[3];
     BatchCtl* ctl = a.ctl;
     if (ctl->err | ctl->left) return;
+    if (threadIdx.x < 3) csum[threadIdx.x] = 0u;
+    __syncthreads();
     Counters ctr = {0u, 0u, 0u};
     const int t = (int)threadIdx.x, lane = lane_id(), w = t >> 6, nd = ctl->n_dense;
     for (int i = (int)blockIdx.x; i < nd; i += (int)gridDim.x) {
@@ -598,11 +599,7 @@ __global__ __launch_bounds__(kRingT) void k_batch_ring(BatchArgs a)
         if (t == 0) a.hcnt[ds.set] = m;
         __syncthreads();
     }
-    const uint32_t v[2] = {(uint32_t)wave_total((int)ctr.orient), (uint32_t)wave_total((int)ctr.orient_exact)};
-    if (lane == 0) {
-        if (v[0]) atomicAdd(&ctl->orient, (unsigned long long)v[0]);
-        if (v[1]) atomicAdd(&ctl->orient_exact, (unsigned long long)v[1]);
-    }
+    ctr_flush(ctl->ctr, ctr, csum);
 }
 
 // Offsets and hulls to the caller, the status to the host. Workgroup b takes a
@@ -658,20 +655,29 @@ __global__ __launch_bounds__(kEmitT) void k_batch_emit(BatchArgs a)
     if (b == nb - 1) {
         LocalStatus* s = a.status;
         if (t < kSolvePasses) {
-            s->pass_v[t] = ctl->pass_v[t];
-            s->pass_s[t] = ctl->pass_s[t];
+            int v = 0, g = 0, most = 0;
+#pragma unroll
+            for (int k = 0; k < kStatLines; ++k) {
+                v += ctl->st[k].pass_v[t];
+                g += ctl->st[k].pass_s[t];
+                most = max(most, ctl->st[k].passes);
+            }
+            s->pass_v[t] = v;
+            s->pass_s[t] = g;
+            if (t == 0) {
+                s->first_v = v;
+                s->passes = most;
+            }
         }
         if (t == 0) {
             if (!bad && a.out_off) a.out_off[a.G] = run;
             s->h = bad ? 0 : run;
             s->err = ctl->err;
             s->left = ctl->err ? 0 : ctl->left;
-            s->passes = ctl->passes;
-            s->first_v = ctl->pass_v[0];
             s->line = 0;
-            s->orient = ctl->orient;
-            s->orient_exact = ctl->orient_exact;
-            s->cmp_exact = ctl->cmp_exact;
+            s->orient = ctr_total(ctl->ctr, 0);
+            s->orient_exact = ctr_total(ctl->ctr, 1);
+            s->cmp_exact = ctr_total(ctl->ctr, 2);
             s->t0 = ctl->t0;
             s->t1 = wall_clock64();
         }

@@ -108,8 +108,6 @@ struct BatchArgs {
     BatchCtl* ctl;
 };
 size_t batch_ctl_bytes();
-size_t pocket_bytes();
-size_t dense_bytes();
 hipError_t launch_batch(const BatchArgs& a, int cus, hipStream_t st);
 
 }  // namespace sqh

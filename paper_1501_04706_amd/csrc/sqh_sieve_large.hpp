@@ -33,24 +33,14 @@ struct SieveCtl {
     float Mx, My;
     float x0, y0, sx, sy;  // directions are taken of ((x - x0) sx, (y - y0) sy)
     Slabs slabs;
-    unsigned long long t0, orient, orient_exact, cmp_exact;
+    unsigned long long t0;
+    CtrSlot ctr[kCtrSlots];
     int cnt2[kSieveGrid];  // points each sieve workgroup left
     unsigned long long best2[kDirs2];
     float2 bins[kSlabs];
     float2 ring[kDirs];
     unsigned long long best[kExtremeGrid][kDirs];
 };
-
-__device__ __forceinline__ void sieve_counters(SieveCtl* c, const Counters& ctr, uint32_t* sum)
-{
-    counters_sum(ctr, sum);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        atomicAdd(&c->orient, (unsigned long long)sum[0]);
-        if (sum[1]) atomicAdd(&c->orient_exact, (unsigned long long)sum[1]);
-        if (sum[2]) atomicAdd(&c->cmp_exact, (unsigned long long)sum[2]);
-    }
-}
 
 // Direction j of K as (cos, sin) of 2 pi j / K, scaled. Rounding does not
 // matter: the polygon's vertices are points of the set whichever are chosen.
@@ -144,9 +134,9 @@ __device__ __forceinline__ void sieve_ctl_init(SieveCtl* ctl, const Frame& f)
     if (t == 0) {
         ctl->left = 0; ctl->err = 0; ctl->done = 0u;
         ctl->x0 = f.x0; ctl->y0 = f.y0; ctl->sx = f.sx; ctl->sy = f.sy;
-        ctl->orient = 0ull; ctl->orient_exact = 0ull; ctl->cmp_exact = 0ull;
     }
     if (t < kDirs2) ctl->best2[t] = 0ull;
+    if (t < 3 * kCtrSlots) ctl->ctr[t / 3].c[t % 3] = 0ull;
 }
 
 // The extremes of a sample of 64 points per wave.
@@ -461,7 +451,6 @@ __device__ __forceinline__ void rest_finish(const SieveArgs& a, SolveLds<P>& L, 
         s->pass_s[t] = st.pass_s[t];
     }
     if (t == 0) {
-        auto sum = [](unsigned long long* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
         s->h = hh;
         s->err = err;
         s->left = (!err && left) ? 1 : 0;
@@ -469,9 +458,9 @@ __device__ __forceinline__ void rest_finish(const SieveArgs& a, SolveLds<P>& L, 
         s->first_v = M;
         s->line = ctl->line;
         // one side test per point of the sieve
-        s->orient = sum(&ctl->orient) + csum[0] + (unsigned long long)a.n;
-        s->orient_exact = sum(&ctl->orient_exact) + csum[1];
-        s->cmp_exact = sum(&ctl->cmp_exact) + csum[2];
+        s->orient = ctr_total(ctl->ctr, 0) + csum[0] + (unsigned long long)a.n;
+        s->orient_exact = ctr_total(ctl->ctr, 1) + csum[1];
+        s->cmp_exact = ctr_total(ctl->ctr, 2) + csum[2];
         s->t0 = ctl->t0;
         s->t1 = wall_clock64();
     }
@@ -522,7 +511,7 @@ __device__ __forceinline__ void sieve_share(const SieveArgs& a, SieveLds& S, int
     for (int i = t; i < kSlabs; i += T) S.bins[i] = gld(ctl->bins + i);
     if (t < h) S.ring[t] = gld(ctl->ring + t);
     if (t < kDirs2) S.best[t] = 0ull;
-    if (t < 3) s_cnt[t] = 0;  // points past the slabs, past the edges; non-finite
+    if (t < 4) s_cnt[t] = 0;  // points past the slabs, past the edges; non-finite; exact tests
     uint32_t n_exact = 0u;
     __syncthreads();
     bool bad = false;
@@ -600,9 +589,10 @@ __device__ __forceinline__ void sieve_share(const SieveArgs& a, SieveLds& S, int
         }
     }
     n_exact = (uint32_t)wave_total((int)n_exact);
-    if (lane == 0 && n_exact) atomicAdd(&ctl->orient_exact, (unsigned long long)n_exact);
+    if (lane == 0 && n_exact) atomicAdd(&s_cnt[3], (int)n_exact);
     __syncthreads();
     if (t == 0) {
+        if (s_cnt[3]) atomicAdd(&ctl->ctr[b % kCtrSlots].c[1], (unsigned long long)s_cnt[3]);
         __hip_atomic_store(&ctl->cnt2[b], s_cnt[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (s_cnt[2]) atomicOr(&ctl->err, kErrNonFinite);
     }
@@ -613,7 +603,7 @@ __device__ __forceinline__ void sieve_share(const SieveArgs& a, SieveLds& S, int
 __global__ __launch_bounds__(kSieveT, 4) void k_sieve(SieveArgs a)
 {
     __shared__ SieveLds S;
-    __shared__ int s_cnt[3];
+    __shared__ int s_cnt[4];
     SieveCtl* ctl = a.ctl;
     if (ctl->left) return;
     sieve_share<kSieveT>(a, S, s_cnt);
@@ -669,7 +659,7 @@ __global__ __launch_bounds__(kMidT) void k_sieve_solve(SieveArgs a, int per)
     __shared__ SolveLds<kMidP> L;
     __shared__ SolveStats st;
     __shared__ uint32_t csum[3];
-    __shared__ int s_cnt[3], s_last;
+    __shared__ int s_cnt[4], s_last;
     static_assert(sizeof(SieveLds) <= sizeof(L.bins), "the tables take the solve's keys' space");
     const int t = (int)threadIdx.x, nb = (int)gridDim.x;
     SieveCtl* ctl = a.ctl;
@@ -790,7 +780,7 @@ __global__ __launch_bounds__(kMidT) void k_rest(SieveArgs a, int ns, int per, in
             if (t == 0) gst(a.lcnt + c, h);
         }
     }
-    sieve_counters(ctl, ctr, csum);
+    ctr_flush(ctl->ctr, ctr, csum);
     ctr = Counters{0u, 0u, 0u};
     if (!finishes_last(&ctl->done, nb, &s_last)) return;
     if (t < 3) csum[t] = 0u;
