@@ -66,7 +66,7 @@ StatusOffsets status_offsets()
 
 bool make_layout(int64_t N, int64_t nsets, Layout& L)
 {
-    static const size_t ctl_bytes = std::max({sieve_ctl_bytes(), batch_ctl_bytes(), ring_ctl_bytes()});
+    static const size_t ctl_bytes = std::max({sieve_ctl_bytes(), batch_ctl_bytes(), ring_ctl_bytes(), pre_ctl_bytes()});
     if (N < 0 || nsets < 1 || N > (int64_t)INT32_MAX - 2 || nsets > (int64_t)INT32_MAX / 8) return false;
     L.N = N;
     L.nsets = nsets;
@@ -565,6 +565,70 @@ int collect_local(sqh_ctx* ctx, int64_t N, int64_t out_cap, int64_t* h_total)
     return L.h > out_cap ? SQH_ECAPACITY : SQH_OK;
 }
 
+// The local kernels on n points of a call's workspace, xy with indices ids
+// (null: their places), up to the end of the stream.
+hipError_t run_local(sqh_ctx* ctx, const HullArgs& a, const float2* xy, const int* ids, int n, int32_t* d_out,
+                     int64_t out_cap, hipStream_t st)
+{
+    LocalArgs l{xy, ids, n, d_out, out_cap, a.fp64, ctx->lstat};
+    launch_mark(ctx, "k_local_one", 1, st);
+    hipError_t e = launch_local_one(l, st);
+    launch_mark(ctx, "k_local_one", 0, st);
+    return e != hipSuccess ? e : hipStreamSynchronize(st);
+}
+// (leaves lstat->left if the sieve is not for the set)
+hipError_t run_sieve(sqh_ctx* ctx, const HullArgs& a, const float2* xy, const int* ids, int n, int32_t* d_out,
+                     int64_t out_cap, hipStream_t st)
+{
+    SieveArgs v{};
+    v.xy = xy;
+    v.ids = ids;
+    v.all = a.xy;
+    v.n = n;
+    v.out = d_out;
+    v.cap = out_cap;
+    v.status = ctx->lstat;
+    for (int b = 0; b < 2; ++b) {
+        v.X[b] = a.X[b];
+        v.Y[b] = a.Y[b];
+        v.I[b] = a.I[b];
+    }
+    // (the child records' space holds 42 bytes a point; xy2 may be the input)
+    v.lxy = reinterpret_cast<float2*>(a.recs);
+    v.lid = reinterpret_cast<int*>(v.lxy + n);
+    v.lcnt = a.wprefix;
+    v.ctl = reinterpret_cast<SieveCtl*>(a.slots);
+    hipError_t e = launch_sieve(v, ctx->cus, st, launch_mark, ctx);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess && ctx->lstat->left == 2) {
+        e = launch_rest(v, ctx->cus, st, launch_mark, ctx);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+    }
+    return e;
+}
+// (leaves lstat->left if the set is no ring around its centre)
+hipError_t run_ring(sqh_ctx* ctx, const HullArgs& a, const float2* xy, const int* ids, int n, int32_t* d_out,
+                    int64_t out_cap, hipStream_t st)
+{
+    RingArgs r{};
+    r.xy = xy;
+    r.ids = ids;
+    r.n = n;
+    r.out = d_out;
+    r.cap = out_cap;
+    r.line = ctx->lstat->line;
+    r.status = ctx->lstat;
+    r.wid = reinterpret_cast<uint16_t*>(a.vidx);
+    r.off = a.shist;
+    r.slots = reinterpret_cast<float4*>(a.recs);
+    r.slots2 = reinterpret_cast<float4*>(a.X[0]);
+    r.pockets = reinterpret_cast<RingPocket*>(a.segs[0]);
+    r.pocket_cap = n / 64 + 512;
+    r.ctl = reinterpret_cast<RingCtl*>(a.slots);
+    const hipError_t e = launch_ring(r, ctx->cus, st, launch_mark, ctx);
+    return e != hipSuccess ? e : hipStreamSynchronize(st);
+}
+
 int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const int64_t* d_set_off, int32_t* d_out,
               int64_t* d_out_off, int64_t out_cap, int64_t* h_total, void* d_ws, size_t ws_bytes, hipStream_t st,
               const TuneEntry& tu)
@@ -577,78 +641,69 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
     const bool sieve = a.line_ok && !a.fp64;  // static float32 certificates may be used
     // one set in plain mode. Up to kLocalPoints points: one workgroup, the
     // points in LDS, in every precision mode. More: past the sieve, unless
-    // the sample shows a ring of points, which the batch kernels cut into
-    // pockets (below 2^16 points: 40 us of launches less) or the ring kernels
-    // over the whole chip. What they leave (a centre outside the hull, pockets
-    // that float32 rays cannot tell apart) the streaming path takes. (From
-    // 2^16 points the streaming switch and a tuned path still choose.)
+    // the sample shows a ring of points, which the ring kernels take over the
+    // whole chip. What they leave (a centre outside the hull, points closer to
+    // a ray than float64 can tell) goes to the batch kernels below 2^16 points
+    // and to the streaming path above. (From 2^16 points the streaming switch
+    // and a tuned path still choose.)
     bool ring = false;
-    const bool whole = nsets == 1 && !d_set_off && plain;
-    if (whole && N <= kLocalPoints) {
-        LocalArgs l{a.xy, (int)N, d_out, out_cap, a.fp64, ctx->lstat};
+    const bool whole = nsets == 1 && !d_set_off && !a.sorted && !ctx->trace;
+    if (whole && !a.prefilter && N <= kLocalPoints) {
         ctx->nl = 0;
-        if (time_open(ctx, "k_local_one", st) != SQH_OK) return SQH_EDEVICE;
-        HIP_OK(launch_local_one(l, st));
-        if (time_close(ctx, "k_local_one", st) != SQH_OK) return SQH_EDEVICE;
-        HIP_OK(hipStreamSynchronize(st));
+        HIP_OK(run_local(ctx, a, a.xy, nullptr, (int)N, d_out, out_cap, st));
         return collect_local(ctx, N, out_cap, h_total);
     }
-    if (whole && sieve && (N < kStreamMin || a.stream)) {
-        SieveArgs v{};
-        v.xy = a.xy;
-        v.n = (int)N;
-        v.out = d_out;
-        v.cap = out_cap;
-        v.status = ctx->lstat;
-        for (int b = 0; b < 2; ++b) {
-            v.X[b] = a.X[b];
-            v.Y[b] = a.Y[b];
-            v.I[b] = a.I[b];
-        }
-        v.lxy = a.xy2;
-        v.lid = a.ids2;
-        v.lcnt = a.wprefix;
-        v.ctl = reinterpret_cast<SieveCtl*>(a.slots);
+    if (whole && !a.prefilter && sieve && (N < kStreamMin || a.stream)) {
         ctx->nl = 0;
-        HIP_OK(launch_sieve(v, ctx->cus, st, launch_mark, ctx));
-        HIP_OK(hipStreamSynchronize(st));
-        if (ctx->lstat->left == 2) {
-            HIP_OK(launch_rest(v, ctx->cus, st, launch_mark, ctx));
-            HIP_OK(hipStreamSynchronize(st));
+        HIP_OK(run_sieve(ctx, a, a.xy, nullptr, (int)N, d_out, out_cap, st));
+        const bool by_ring = ctx->lstat->left != 0;
+        if (by_ring) {
+            // (5M points of a circle: 1530 us on the streaming path, 440 us so;
+            // 30000: 350 us with one workgroup cutting the ring, as a batch's)
+            HIP_OK(run_ring(ctx, a, a.xy, nullptr, (int)N, d_out, out_cap, st));
+            ring = ctx->lstat->left && N < kStreamMin;
         }
         if (!ctx->lstat->left) {
             rc = collect_local(ctx, N, out_cap, h_total);
             if (a.stream) {
-                ctx->stats.stream_path = 1;
+                ctx->stats.stream_path = by_ring ? 2 : 1;
                 ctx->stats.line_filter = ctx->lstat->line;
             }
             return rc;
         }
-        ring = N < kStreamMin;
-        if (!ring) {
-            // (5M points of a circle: 1530 us on the streaming path, 395 us so)
-            RingArgs r{};
-            r.xy = a.xy;
-            r.n = (int)N;
-            r.out = d_out;
-            r.cap = out_cap;
-            r.line = ctx->lstat->line;
-            r.status = ctx->lstat;
-            r.wid = reinterpret_cast<uint16_t*>(a.vidx);
-            r.off = a.shist;
-            r.slots = reinterpret_cast<float4*>(a.recs);
-            r.slots2 = reinterpret_cast<float4*>(a.X[0]);
-            r.pockets = reinterpret_cast<RingPocket*>(a.segs[0]);
-            r.pocket_cap = (int)(N / 64 + 512);
-            r.ctl = reinterpret_cast<RingCtl*>(a.slots);
-            HIP_OK(launch_ring(r, ctx->cus, st, launch_mark, ctx));
-            HIP_OK(hipStreamSynchronize(st));
-            if (!ctx->lstat->left) {
-                rc = collect_local(ctx, N, out_cap, h_total);
-                ctx->stats.stream_path = 2;
-                ctx->stats.line_filter = ctx->lstat->line;
-                return rc;
-            }
+    }
+    // the pre-filter, then the same on its subset, of which the host has to
+    // know the size (10 us; 5M points of a disk: 700 us by the cooperative
+    // pre-filter and the persistent kernel).
+    if (whole && a.prefilter && sieve && N > 0) {
+        PreArgs p{};
+        p.xy = a.xy;
+        p.n = (int)N;
+        p.quad = a.prefilter == SQH_PREFILTER_QUAD;
+        p.out_xy = a.xy2;
+        p.out_id = a.ids2;
+        p.status = ctx->lstat;
+        p.ctl = reinterpret_cast<PreCtl*>(a.slots);
+        ctx->nl = 0;
+        HIP_OK(launch_pre(p, ctx->cus, st, launch_mark, ctx));
+        HIP_OK(hipStreamSynchronize(st));
+        const int n2 = ctx->lstat->pre_n;
+        if (n2 < 0) return collect_local(ctx, N, out_cap, h_total);
+        if (n2 <= kLocalPoints) {
+            HIP_OK(run_local(ctx, a, a.xy2, a.ids2, n2, d_out, out_cap, st));
+        } else {
+            HIP_OK(run_sieve(ctx, a, a.xy2, a.ids2, n2, d_out, out_cap, st));
+            if (ctx->lstat->left) HIP_OK(run_ring(ctx, a, a.xy2, a.ids2, n2, d_out, out_cap, st));
+        }
+        if (!ctx->lstat->left) {
+            rc = collect_local(ctx, N, out_cap, h_total);
+            const LocalStatus& L = *ctx->lstat;
+            sqh_stats& S = ctx->stats;
+            S.prefilter_points = n2;
+            S.orient_evals += L.pre_orient;
+            S.ms_prefilter = (double)(L.pre_t1 - L.pre_t0) * 1e-5;
+            S.ms_total = S.ms_kernel = (double)(L.t1 - L.pre_t0) * 1e-5;
+            return rc;
         }
     }
     // several sets: each on a workgroup of its own (4096 sets of 64M points:

@@ -61,6 +61,7 @@ __device__ __forceinline__ unsigned long long ctr_total(const CtrSlot* slots, in
 }  // namespace sqh
 #include "sqh_sieve_large.hpp"
 #include "sqh_ring.hpp"
+#include "sqh_subset.hpp"
 namespace sqh {
 
 // One set of at most P points, the hull to out (first cap vertices), the
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(T) void k_local_one(LocalArgs a)
     if (t < 3) csum[t] = 0u;
     if (t == 0) L.bad = 0;
     __syncthreads();
-    const int cnt = load_points<T, P>(L, a.xy, a.n, a.n);
+    const int cnt = load_points<T, P>(L, a.xy, a.n, a.n, a.ids);
     const int h = L.bad ? kSetBad : (cnt == 0 ? 0 : solve<T, P, true>(L, cnt, 0, 0, a.fp64 != 0, ctr, &st));
     counters_sum(ctr, csum);
     for (int r = t; r < h; r += T)
@@ -739,6 +740,20 @@ hipError_t launch_rest(const SieveArgs& a, int cus, hipStream_t st, LaunchMark m
     mark(ctx, "k_rest", 1, st);
     k_rest<<<cus, kMidT, 0, st>>>(a, ns, share, 0);
     mark(ctx, "k_rest", 0, st);
+    return hipGetLastError();
+}
+
+size_t pre_ctl_bytes() { return sizeof(PreCtl); }
+hipError_t launch_pre(const PreArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx)
+{
+    // (workgroups of at least 2048 points)
+    const int nb = std::max(1, std::min({2 * cus, kPreGrid, a.n / 2048}));
+    mark(ctx, "k_pre_extremes", 1, st);
+    k_pre_extremes<<<nb, kPreT, 0, st>>>(a);
+    mark(ctx, "k_pre_extremes", 0, st);
+    mark(ctx, "k_pre_keep", 1, st);
+    k_pre_keep<<<nb, kPreT, 0, st>>>(a, nb);
+    mark(ctx, "k_pre_keep", 0, st);
     return hipGetLastError();
 }
 

@@ -19,6 +19,9 @@ struct LocalStatus {
     unsigned long long orient, orient_exact, cmp_exact;
     unsigned long long t0, t1;  // device clock (100 MHz) at the call's start and end
     int pass_v[kLocalStatPasses], pass_s[kLocalStatPasses];
+    // launch_pre
+    int pre_n;  // points kept (-1: a coordinate is not finite)
+    unsigned long long pre_orient, pre_t0, pre_t1;
 };
 
 // Called before (open) and after every launch of a call.
@@ -27,6 +30,7 @@ typedef int (*LaunchMark)(void* ctx, const char* name, int open, hipStream_t st)
 // One set of at most kLocalPoints points on one workgroup.
 struct LocalArgs {
     const float2* xy;
+    const int* ids;  // the points' indices (null: their places)
     int n;
     int32_t* out;
     int64_t cap;
@@ -41,6 +45,8 @@ hipError_t launch_local_one(const LocalArgs& a, hipStream_t st);
 struct SieveCtl;
 struct SieveArgs {
     const float2* xy;
+    const int* ids;    // the points' indices (null: their places) ...
+    const float2* all; // ... in this array (else xy)
     int n;
     int32_t* out;
     int64_t cap;
@@ -57,11 +63,26 @@ size_t sieve_ctl_bytes();
 hipError_t launch_sieve(const SieveArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx);
 hipError_t launch_rest(const SieveArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx);
 
+// The pre-filter of a single set: its subset to out_xy, out_id (n each).
+struct PreCtl;
+struct PreArgs {
+    const float2* xy;
+    int n;
+    int quad;  // the extremes in x and y only
+    float2* out_xy;
+    int* out_id;
+    LocalStatus* status;
+    PreCtl* ctl;
+};
+size_t pre_ctl_bytes();
+hipError_t launch_pre(const PreArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx);
+
 // One large ring of points (a set the sieve left).
 struct RingCtl;
 struct RingPocket;
 struct RingArgs {
     const float2* xy;
+    const int* ids;      // the points' indices (null: their places)
     int n;
     int32_t* out;
     int64_t cap;

@@ -359,7 +359,8 @@ __global__ __launch_bounds__(1024) void k_ring_scatter(RingArgs a)
         for (int j = 0; j < U; ++j) {
             const int i = q + t + 1024 * j;
             if (i < q1 && k[j] < kRays)
-                gst(a.slots + atomicAdd(&cur[k[j]], 1), make_float4(v[j].x, v[j].y, __int_as_float(i), 0.0f));
+                gst(a.slots + atomicAdd(&cur[k[j]], 1),
+                    make_float4(v[j].x, v[j].y, __int_as_float(a.ids ? gld(a.ids + i) : i), 0.0f));
         }
     }
 }
@@ -426,7 +427,7 @@ __global__ __launch_bounds__(1024) void k_ring_cut(RingArgs a)
     int all, K;
     const int h = hist[t], at = block_prefix<1024>(h, red, &all);
     const int was = t > 0 ? hist[t - 1] : 0;
-    const bool on = t == 0 || (all > 0 && (long long)at * want / all != (long long)(at - was) * want / all);
+    const bool on = t == 0 || (at < all && (long long)at * want / all != (long long)(at - was) * want / all);
     const int k0 = block_prefix<1024>(on ? 1 : 0, red, &K) + (on ? 1 : 0) - 1;  // (K <= want)
     lut[t] = (uint16_t)k0;
     if (on) {

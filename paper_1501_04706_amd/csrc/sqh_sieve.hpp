@@ -183,7 +183,7 @@ __device__ __forceinline__ bool chain_inside(const float2* v, int h, int kB, boo
 // Points i * n / m, i = 0 .. m - 1 (m <= P; all of them if m == n) into
 // positions 0 .. m - 1. Sets L.bad on a non-finite coordinate. Returns m.
 template <int T, int P>
-__device__ __forceinline__ int load_points(SolveLds<P>& L, const float2* xy, int n, int m)
+__device__ __forceinline__ int load_points(SolveLds<P>& L, const float2* xy, int n, int m, const int* ids = nullptr)
 {
     bool bad = false;
 #pragma unroll
@@ -194,7 +194,7 @@ __device__ __forceinline__ int load_points(SolveLds<P>& L, const float2* xy, int
             const float2 v = gld(xy + q);
             bad |= !((int)isfinite(v.x) & (int)isfinite(v.y));
             L.xy[i] = v;
-            L.id[i] = q;
+            L.id[i] = ids ? gld(ids + q) : q;
         }
     }
     if (__ballot(bad) && lane_id() == 0) L.bad = 1;

@@ -550,7 +550,8 @@ __device__ __forceinline__ void sieve_share(const SieveArgs& a, SieveLds& S, int
                 const int d = at + bits_below(M);
                 gst(a.X[0] + d, x);
                 gst(a.Y[0] + d, y);
-                gst(a.I[0] + d, 2 * (p + T * (j >> 1) + t) + (j & 1));
+                const int q = 2 * (p + T * (j >> 1) + t) + (j & 1);
+                gst(a.I[0] + d, a.ids ? gld(a.ids + q) : q);
             }
             at += (int)__popcll(M);
         }
@@ -562,7 +563,7 @@ __device__ __forceinline__ void sieve_share(const SieveArgs& a, SieveLds& S, int
             const int d = first + atomicAdd(&s_cnt[0], 1);
             gst(a.X[0] + d, v.x);
             gst(a.Y[0] + d, v.y);
-            gst(a.I[0] + d, n - 1);
+            gst(a.I[0] + d, a.ids ? gld(a.ids + n - 1) : n - 1);
         }
     }
     if (__ballot(bad) && lane == 0) s_cnt[2] = 1;
@@ -717,9 +718,10 @@ __global__ __launch_bounds__(kMidT) void k_rest(SieveArgs a, int ns, int per, in
         // workgroup b's share against the second polygon
         nc = nb;
         float2* v = L.bins;  // (free between solves)
+        const float2* all = a.ids ? a.all : a.xy;
         if (t < 64) {
 #pragma unroll
-            for (int k = 0; k < kDirs2 / 64; ++k) v[lane + 64 * k] = gld(a.xy + (uint32_t)ctl->best2[lane + 64 * k]);
+            for (int k = 0; k < kDirs2 / 64; ++k) v[lane + 64 * k] = gld(all + (uint32_t)ctl->best2[lane + 64 * k]);
             wave_sync();
             const int p = wave_polygon(v, v + kDirs2, kDirs2, v + 2 * kDirs2, ctr);
             float mx, my, ext;

@@ -189,6 +189,28 @@ def test_large_ring_errors(H):
     assert gpu(H, c) == [int(v) for v in oracle.c_hull(c)]
 
 
+@pytest.mark.parametrize("n", [1, 2, 255, 2047, 4097, 8193, 30_001, 65_537, 400_003])
+@pytest.mark.parametrize("mode", [sqh.SQH_PREFILTER_QUAD, sqh.SQH_PREFILTER_OCTAGON])
+def test_prefiltered_subsets(H, n, mode):
+    """The subset by every route (one workgroup, the sieve, the ring kernels),
+    its indices, and copies whose lowest index must win."""
+    rng = np.random.default_rng(n)
+    sets = [(k, workloads.make(k, n, n + 3)) for k in ("square", "disk", "grid", "circle")]
+    sets += [("copies", workloads.circle(max(1, n // 3), 7)[rng.integers(0, max(1, n // 3), n)]),
+             ("line", np.stack([np.arange(n)] * 2, 1).astype(np.float32)[rng.permutation(n)]),
+             ("overflow", workloads.square(n, 2) * np.float32(3e38)),
+             ("half and half", np.concatenate([workloads.circle(n - n // 2, 3), workloads.disk(n // 2, 4) * np.float32(1.01)])
+              .astype(np.float32)[rng.permutation(n)])]
+    H.set_prefilter(mode)
+    try:
+        for name, xy in sets:
+            print(f"[case] pre-filtered {name} n={n} mode={mode}", file=sys.stderr, flush=True)
+            assert gpu(H, xy) == want(xy), name
+            assert 0 <= H.stats()["prefilter_points"] <= n
+    finally:
+        H.set_prefilter(sqh.SQH_PREFILTER_NONE)
+
+
 @pytest.mark.parametrize("n", [1024, 4096, 4097, 20_000, 160_000, 700_000])
 def test_batches(H, n):
     """Every kind of set in one batch, with empty sets and a ragged last one:
