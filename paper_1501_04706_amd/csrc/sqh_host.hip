@@ -739,6 +739,7 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
         ctx->nl = 0;
         if (time_open(ctx, "k_batch", st) != SQH_OK) return SQH_EDEVICE;
         HIP_OK(launch_batch(b, ctx->cus, st));
+        HIP_OK(launch_batch_emit(b, ctx->cus, st));
         if (time_close(ctx, "k_batch", st) != SQH_OK) return SQH_EDEVICE;
         HIP_OK(hipStreamSynchronize(st));
         if (!ctx->lstat->left) return collect_local(ctx, N, out_cap, h_total);
@@ -808,7 +809,7 @@ struct EngLayout {
     int64_t K, R, SC, scap, rcap;
     size_t x[2], y[2], id[2], segs[2], seg_cid[2], vstart[2];
     size_t bitmap, vidx, hout, recs, rec_cid, sets, gstart, sbase, bad, res_base, res_n, res_alive, res_h;
-    size_t stage, vlist, slots, ctab, bar, err, stats, sv, info;
+    size_t stage, vlist, slots, ctab, bar, err, stats, sv, info, shist;
     size_t bytes;
 };
 
@@ -848,13 +849,14 @@ bool make_eng_layout(int64_t K, int64_t R, int64_t SC, EngLayout& L)
     L.res_h = take(sizeof(int) * (size_t)R);
     L.stage = take(sizeof(float2) * (size_t)(2 * SC));  // two halves: one per step in flight
     L.vlist = take(sizeof(int2));
-    L.slots = take(sizeof(ChunkSlot<8>) * (size_t)kMaxGrid);
+    L.slots = take(std::max({sizeof(ChunkSlot<8>) * (size_t)kMaxGrid, sieve_ctl_bytes(), ring_ctl_bytes()}));
     L.ctab = take(sizeof(Pair) * (size_t)kMaxGrid);
     L.bar = take(sizeof(GridBar));
     L.err = take(sizeof(int));
     L.stats = take(sizeof(uint32_t) * 4 * kStatSlots);
     L.sv = take(sizeof(int) * 4);
-    L.info = take(sizeof(HullInfo));
+    L.info = take(std::max(sizeof(HullInfo), batch_ctl_bytes()));
+    L.shist = take(sizeof(int) * (size_t)kSortBuckets * (size_t)kMaxGrid);
     L.bytes = o;
     return true;
 }
@@ -893,6 +895,9 @@ struct sqh_engine {
     int32_t* h_bounce = nullptr;
     int64_t bounce_cap = 0;
     HullInfo* h_info = nullptr;
+    LocalStatus* h_local = nullptr;  // pinned: the local kernels' status of a step, then of each of its large requests
+    bool local = false;              // the launched step runs on the local kernels
+    int max_passes = 0;              // of the launched step
     hipEvent_t ev_admit = nullptr, ev_done = nullptr;
     hipStream_t step_stream = nullptr;
     int64_t steps = 0;
@@ -937,6 +942,243 @@ void eng_free(sqh_engine* e, int64_t base, int64_t alloc)
             e->free_ranges.erase(it);
         }
     }
+}
+
+}  // namespace
+
+namespace {
+
+constexpr int kLocalStepPasses = 16;  // (a circle of 5M points takes 16)
+
+int no_mark(void*, const char*, int, hipStream_t) { return SQH_OK; }
+
+// The launched step (step_new, step_all) on the resident segment table: N
+// points in staging half `side`.
+int eng_general(sqh_engine* e, int side, int64_t N, hipStream_t st)
+{
+    sqh_ctx* c = e->ctx;
+    const EngLayout& L = e->L;
+    const int64_t R = L.R;
+    const int G = (int)e->step_new.size(), nres = (int)e->step_all.size();
+    const int max_passes = e->max_passes;
+    const int* up_gstart = e->h_up;
+    const int* up_sbase = e->h_up + (R + 1);
+    const int* up_rbase = e->h_up + (2 * R + 1);
+    const int* up_rn = e->h_up + (3 * R + 1);
+    char* A = e->arena;
+    auto at = [&](size_t off) { return static_cast<void*>(A + off); };
+    HIP_OK(hipMemcpyAsync(at(L.gstart), up_gstart, sizeof(int) * (size_t)(G + 1), hipMemcpyHostToDevice, st));
+    if (G > 0) HIP_OK(hipMemcpyAsync(at(L.sbase), up_sbase, sizeof(int) * (size_t)G, hipMemcpyHostToDevice, st));
+    HIP_OK(hipMemcpyAsync(at(L.res_base), up_rbase, sizeof(int) * (size_t)nres, hipMemcpyHostToDevice, st));
+    HIP_OK(hipMemcpyAsync(at(L.res_n), up_rn, sizeof(int) * (size_t)nres, hipMemcpyHostToDevice, st));
+
+    // An engine step leaves 1/8 of the compute units free by default: the
+    // copies of the next step's admissions run as copy kernels, which cannot
+    // start while the persistent kernel holds every compute unit.
+    TuneEntry tu = pick_tuning(c, N > 0 ? N : 1);
+    tu.grid = c->engine_grid > 0 ? std::min(c->engine_grid, c->max_grid)
+                                 : std::max(1, c->max_grid - c->max_grid / 8);
+    HullArgs a{};
+    a.xy = reinterpret_cast<const float2*>(A + L.stage) + (size_t)side * L.SC;
+    a.N = (int)N;
+    a.G = G;
+    for (int b = 0; b < 2; ++b) {
+        a.X[b] = static_cast<float*>(at(L.x[b]));
+        a.Y[b] = static_cast<float*>(at(L.y[b]));
+        a.I[b] = static_cast<int*>(at(L.id[b]));
+        a.segs[b] = static_cast<Seg*>(at(L.segs[b]));
+        a.seg_cid[b] = static_cast<int*>(at(L.seg_cid[b]));
+        a.vstart[b] = static_cast<int*>(at(L.vstart[b]));
+    }
+    a.gstart = static_cast<int*>(at(L.gstart));
+    a.sets = static_cast<SetInfo*>(at(L.sets));
+    a.recs = static_cast<Seg*>(at(L.recs));
+    a.rec_cid = static_cast<int*>(at(L.rec_cid));
+    a.sv = static_cast<int*>(at(L.sv));
+    a.bitmap = static_cast<uint64_t*>(at(L.bitmap));
+    a.vidx = static_cast<int*>(at(L.vidx));
+    a.vlist = static_cast<int2*>(at(L.vlist));
+    a.vcap = 0;
+    a.slots = at(L.slots);
+    a.ctab = static_cast<Pair*>(at(L.ctab));
+    a.bar = static_cast<GridBar*>(at(L.bar));
+    a.err = static_cast<int*>(at(L.err));
+    a.stats = static_cast<uint32_t*>(at(L.stats));
+    a.info = static_cast<HullInfo*>(at(L.info));
+    a.fp64 = c->fp64;
+    a.timing = 1;
+    a.tail_points = tu.tail;
+    a.sbase = static_cast<const int*>(at(L.sbase));
+    a.cur0 = e->cur;
+    a.max_passes = max_passes;
+    a.nres = nres;
+    a.res_base = static_cast<const int*>(at(L.res_base));
+    a.res_n = static_cast<const int*>(at(L.res_n));
+    a.res_alive = static_cast<int*>(at(L.res_alive));
+    a.res_h = static_cast<int*>(at(L.res_h));
+    a.hout = static_cast<int*>(at(L.hout));
+    a.bad = static_cast<int*>(at(L.bad));
+
+    HIP_OK(hipEventRecord(c->ev0, st));
+    k_engine_reset<<<std::max(1, std::min(1024, std::max(G, nres / 256 + 1))), 256, 0, st>>>(a);
+    HIP_OK(hipGetLastError());
+    HIP_OK(hipEventRecord(c->evk, st));
+    void* argv[] = {static_cast<void*>(&a)};
+    HIP_OK(hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_engine_step), dim3(tu.grid), dim3(kBlock),
+                                      argv, 0, st));
+    HIP_OK(hipEventRecord(c->ev1, st));
+    int* dn_alive = e->h_down;
+    int* dn_h = e->h_down + R;
+    int* dn_bad = e->h_down + 2 * R;
+    int* dn_err = e->h_down + 3 * R;
+    HIP_OK(hipMemcpyAsync(dn_alive, at(L.res_alive), sizeof(int) * (size_t)nres, hipMemcpyDeviceToHost, st));
+    HIP_OK(hipMemcpyAsync(dn_h, at(L.res_h), sizeof(int) * (size_t)nres, hipMemcpyDeviceToHost, st));
+    if (G > 0) HIP_OK(hipMemcpyAsync(dn_bad, at(L.bad), sizeof(int) * (size_t)G, hipMemcpyDeviceToHost, st));
+    HIP_OK(hipMemcpyAsync(dn_err, at(L.err), sizeof(int), hipMemcpyDeviceToHost, st));
+    HIP_OK(hipMemcpyAsync(e->h_info, at(L.info), offsetof(HullInfo, trace), hipMemcpyDeviceToHost, st));
+    HIP_OK(hipMemcpyAsync(c->hstats, at(L.stats), sizeof(uint32_t) * 4 * kStatSlots, hipMemcpyDeviceToHost, st));
+    HIP_OK(hipEventRecord(e->ev_done, st));
+    return SQH_OK;
+}
+
+// The launched step on the local kernels (no resident segments): its requests
+// as a batch, those of more than kBatchSetMax points past the sieve one after
+// another, with what the sieve leaves decided on the device; the hulls and
+// their sizes straight to pinned memory.
+int eng_local(sqh_engine* e, int side, int64_t N, hipStream_t st)
+{
+    sqh_ctx* c = e->ctx;
+    const EngLayout& L = e->L;
+    const int64_t R = L.R;
+    const int G = (int)e->step_new.size();
+    char* A = e->arena;
+    auto at = [&](size_t off) { return static_cast<void*>(A + off); };
+    const float2* stage = reinterpret_cast<const float2*>(A + L.stage) + (size_t)side * L.SC;
+    BatchArgs b{};
+    b.xy = stage;
+    b.N = (int)N;
+    b.G = G;
+    b.sieve = 1;
+    b.out = e->h_bounce;
+    b.cap = e->bounce_cap;
+    b.status = e->h_local;
+    b.start = static_cast<int*>(at(L.gstart));
+    b.hcnt = static_cast<int*>(at(L.res_h));
+    b.order = static_cast<int*>(at(L.res_alive));
+    b.hbuf = static_cast<int*>(at(L.hout));
+    b.slots = static_cast<float*>(at(L.x[0]));
+    b.slots2 = static_cast<float*>(at(L.x[1]));
+    b.pockets = static_cast<Pocket*>(at(L.recs));
+    b.pocket_cap = (int)(N / 128 + 4);
+    b.todo[0] = static_cast<int*>(at(L.segs[0]));
+    b.todo[1] = static_cast<int*>(at(L.segs[1]));
+    b.todo[2] = b.todo[1] + b.pocket_cap;
+    b.dense = static_cast<DenseSet*>(at(L.seg_cid[0]));
+    b.dense_cap = (int)(N / 4096 + 1);
+    b.ctl = static_cast<BatchCtl*>(at(L.info));
+    b.off32 = e->h_up;
+    b.hpos_src = e->h_up + (R + 1);
+    b.hpos = static_cast<int*>(at(L.sbase));
+    b.bad = static_cast<int*>(at(L.bad));
+    b.h_host = e->h_down + R;
+    b.bad_host = e->h_down + 2 * R;
+    HIP_OK(launch_batch(b, c->cus, st));
+    int big = 0;
+    for (int g = 0; g < G; ++g) {
+        const EngReq& q = e->step_new[g];
+        if (q.n <= kBatchSetMax) continue;
+        LocalStatus* status = e->h_local + 1 + big++;
+        SieveArgs v{};
+        v.xy = stage + q.stage_at;
+        v.all = v.xy;
+        v.n = (int)q.n;
+        v.out = b.hbuf + q.base;
+        v.cap = q.n;
+        v.status = status;
+        for (int k = 0; k < 2; ++k) {
+            v.X[k] = static_cast<float*>(at(L.x[k]));
+            v.Y[k] = static_cast<float*>(at(L.y[k]));
+            v.I[k] = static_cast<int*>(at(L.id[k]));
+        }
+        v.lxy = static_cast<float2*>(at(L.recs));
+        v.lid = reinterpret_cast<int*>(v.lxy + q.n);
+        v.lcnt = static_cast<int*>(at(L.bitmap));
+        v.ctl = static_cast<SieveCtl*>(at(L.slots));
+        v.h_dev = b.hcnt + g;
+        v.bad_dev = b.bad + g;
+        v.gate = static_cast<int*>(at(L.ctab));
+        HIP_OK(launch_sieve(v, c->cus, st, no_mark, nullptr));
+        RingArgs r{};
+        r.xy = v.xy;
+        r.n = v.n;
+        r.out = v.out;
+        r.cap = v.cap;
+        r.status = status;
+        r.wid = static_cast<uint16_t*>(at(L.vidx));
+        r.off = static_cast<int*>(at(L.shist));
+        r.slots = static_cast<float4*>(at(L.recs));  // (42 bytes a slot)
+        r.slots2 = r.slots + q.n;
+        r.pockets = static_cast<RingPocket*>(at(L.segs[0]));
+        r.pocket_cap = (int)(q.n / 64 + 512);
+        r.ctl = static_cast<RingCtl*>(at(L.slots));
+        r.h_dev = v.h_dev;
+        r.bad_dev = v.bad_dev;
+        r.gate = v.gate;
+        HIP_OK(launch_ring(r, c->cus, st, no_mark, nullptr));
+    }
+    HIP_OK(launch_batch_emit(b, c->cus, st));
+    HIP_OK(hipEventRecord(e->ev_done, st));
+    return SQH_OK;
+}
+
+}  // namespace
+
+namespace {
+
+// Collects a step that the local kernels finished: `count` status blocks.
+int eng_collect_local(sqh_engine* e, int count)
+{
+    sqh_ctx* c = e->ctx;
+    const EngLayout& L = e->L;
+    const int G = (int)e->step_new.size();
+    const int* dn_h = e->h_down + L.R;
+    const int* dn_bad = e->h_down + 2 * L.R;
+    ++e->steps;
+    sqh_stats& S = c->stats;
+    S = sqh_stats{};
+    S.points = up_points(e);
+    S.prefilter_points = -1;
+    S.sorted_points = -1;
+    for (int i = 0; i < count; ++i) {
+        const LocalStatus& s = e->h_local[i];
+        S.passes = std::max<int64_t>(S.passes, s.passes);
+        S.orient_evals += s.orient;
+        S.orient_exact += s.orient_exact;
+        S.cmp_exact += s.cmp_exact;
+    }
+    S.ms_total = S.ms_kernel = (double)(e->h_local[0].t1 - e->h_local[0].t0) * 1e-5;
+    int64_t off = 0;
+    for (int g = 0; g < G; ++g) {
+        const EngReq& q = e->step_new[g];
+        const int64_t h = dn_h[g];
+        EngDone d{q.tag, SQH_OK, {}};
+        if (dn_bad[g]) {
+            d.status = SQH_EINVAL;
+        } else if (off + h <= e->bounce_cap) {
+            d.hull.assign(e->h_bounce + off, e->h_bounce + off + h);
+        } else {
+            // the step's hulls are larger than the bounce buffer
+            d.hull.resize((size_t)h);
+            HIP_OK(hipMemcpy(d.hull.data(), e->arena + L.hout + sizeof(int) * (size_t)q.base, sizeof(int) * (size_t)h,
+                             hipMemcpyDeviceToHost));
+        }
+        off += h;
+        e->done.push_back(std::move(d));
+        eng_free(e, q.base, q.alloc);
+    }
+    e->step_new.clear();
+    e->step_all.clear();
+    return G;
 }
 
 }  // namespace
@@ -1351,6 +1593,8 @@ int sqh_engine_create(sqh_ctx* c, void* d_arena, size_t arena_bytes, int64_t slo
         hipHostMalloc(reinterpret_cast<void**>(&e->h_bounce), sizeof(int32_t) * (size_t)e->bounce_cap,
                       hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&e->h_info), sizeof(HullInfo), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&e->h_local), sizeof(LocalStatus) * (size_t)(2 + stage_points / kBatchSetMax),
+                      hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&e->ev_admit, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&e->ev_done, hipEventDisableTiming) != hipSuccess) {
         sqh_engine_destroy(e);
@@ -1375,6 +1619,7 @@ void sqh_engine_destroy(sqh_engine* e)
     if (e->h_down) (void)hipHostFree(e->h_down);
     if (e->h_bounce) (void)hipHostFree(e->h_bounce);
     if (e->h_info) (void)hipHostFree(e->h_info);
+    if (e->h_local) (void)hipHostFree(e->h_local);
     if (e->ev_admit) (void)hipEventDestroy(e->ev_admit);
     if (e->ev_done) (void)hipEventDestroy(e->ev_done);
     delete e;
@@ -1442,81 +1687,16 @@ int sqh_engine_launch(sqh_engine* e, int max_passes, void* stream)
         up_rbase[r] = (int)e->step_all[r].base;
         up_rn[r] = (int)e->step_all[r].n;
     }
-    char* A = e->arena;
-    auto at = [&](size_t off) { return static_cast<void*>(A + off); };
     if (e->admitted) HIP_OK(hipStreamWaitEvent(st, e->ev_admit, 0));  // staged points have arrived
     e->admitted = false;
-    HIP_OK(hipMemcpyAsync(at(L.gstart), up_gstart, sizeof(int) * (size_t)(G + 1), hipMemcpyHostToDevice, st));
-    if (G > 0) HIP_OK(hipMemcpyAsync(at(L.sbase), up_sbase, sizeof(int) * (size_t)G, hipMemcpyHostToDevice, st));
-    HIP_OK(hipMemcpyAsync(at(L.res_base), up_rbase, sizeof(int) * (size_t)nres, hipMemcpyHostToDevice, st));
-    HIP_OK(hipMemcpyAsync(at(L.res_n), up_rn, sizeof(int) * (size_t)nres, hipMemcpyHostToDevice, st));
-
-    // An engine step leaves 1/8 of the compute units free by default: the
-    // copies of the next step's admissions run as copy kernels, which cannot
-    // start while the persistent kernel holds every compute unit.
-    TuneEntry tu = pick_tuning(c, e->stage_used > 0 ? e->stage_used : 1);
-    tu.grid = c->engine_grid > 0 ? std::min(c->engine_grid, c->max_grid)
-                                 : std::max(1, c->max_grid - c->max_grid / 8);
-    HullArgs a{};
-    a.xy = reinterpret_cast<const float2*>(A + L.stage) + (size_t)e->side * L.SC;
-    a.N = (int)e->stage_used;
-    a.G = G;
-    for (int b = 0; b < 2; ++b) {
-        a.X[b] = static_cast<float*>(at(L.x[b]));
-        a.Y[b] = static_cast<float*>(at(L.y[b]));
-        a.I[b] = static_cast<int*>(at(L.id[b]));
-        a.segs[b] = static_cast<Seg*>(at(L.segs[b]));
-        a.seg_cid[b] = static_cast<int*>(at(L.seg_cid[b]));
-        a.vstart[b] = static_cast<int*>(at(L.vstart[b]));
-    }
-    a.gstart = static_cast<int*>(at(L.gstart));
-    a.sets = static_cast<SetInfo*>(at(L.sets));
-    a.recs = static_cast<Seg*>(at(L.recs));
-    a.rec_cid = static_cast<int*>(at(L.rec_cid));
-    a.sv = static_cast<int*>(at(L.sv));
-    a.bitmap = static_cast<uint64_t*>(at(L.bitmap));
-    a.vidx = static_cast<int*>(at(L.vidx));
-    a.vlist = static_cast<int2*>(at(L.vlist));
-    a.vcap = 0;
-    a.slots = at(L.slots);
-    a.ctab = static_cast<Pair*>(at(L.ctab));
-    a.bar = static_cast<GridBar*>(at(L.bar));
-    a.err = static_cast<int*>(at(L.err));
-    a.stats = static_cast<uint32_t*>(at(L.stats));
-    a.info = static_cast<HullInfo*>(at(L.info));
-    a.fp64 = c->fp64;
-    a.timing = 1;
-    a.tail_points = tu.tail;
-    a.sbase = static_cast<const int*>(at(L.sbase));
-    a.cur0 = e->cur;
-    a.max_passes = max_passes;
-    a.nres = nres;
-    a.res_base = static_cast<const int*>(at(L.res_base));
-    a.res_n = static_cast<const int*>(at(L.res_n));
-    a.res_alive = static_cast<int*>(at(L.res_alive));
-    a.res_h = static_cast<int*>(at(L.res_h));
-    a.hout = static_cast<int*>(at(L.hout));
-    a.bad = static_cast<int*>(at(L.bad));
-
-    HIP_OK(hipEventRecord(c->ev0, st));
-    k_engine_reset<<<std::max(1, std::min(1024, std::max(G, nres / 256 + 1))), 256, 0, st>>>(a);
-    HIP_OK(hipGetLastError());
-    HIP_OK(hipEventRecord(c->evk, st));
-    void* argv[] = {static_cast<void*>(&a)};
-    HIP_OK(hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_engine_step), dim3(tu.grid), dim3(kBlock),
-                                      argv, 0, st));
-    HIP_OK(hipEventRecord(c->ev1, st));
-    int* dn_alive = e->h_down;
-    int* dn_h = e->h_down + R;
-    int* dn_bad = e->h_down + 2 * R;
-    int* dn_err = e->h_down + 3 * R;
-    HIP_OK(hipMemcpyAsync(dn_alive, at(L.res_alive), sizeof(int) * (size_t)nres, hipMemcpyDeviceToHost, st));
-    HIP_OK(hipMemcpyAsync(dn_h, at(L.res_h), sizeof(int) * (size_t)nres, hipMemcpyDeviceToHost, st));
-    if (G > 0) HIP_OK(hipMemcpyAsync(dn_bad, at(L.bad), sizeof(int) * (size_t)G, hipMemcpyDeviceToHost, st));
-    HIP_OK(hipMemcpyAsync(dn_err, at(L.err), sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_OK(hipMemcpyAsync(e->h_info, at(L.info), offsetof(HullInfo, trace), hipMemcpyDeviceToHost, st));
-    HIP_OK(hipMemcpyAsync(c->hstats, at(L.stats), sizeof(uint32_t) * 4 * kStatSlots, hipMemcpyDeviceToHost, st));
-    HIP_OK(hipEventRecord(e->ev_done, st));
+    // A step of many passes finishes its requests anyway: without residents it
+    // runs on the local kernels (a serving step of 16M points: 4 ms on the
+    // segment table and 1 ms so). Fewer passes ask for short steps in which
+    // old and new requests share the table.
+    e->max_passes = max_passes;
+    e->local = max_passes >= kLocalStepPasses && G > 0 && e->resident.empty() && c->line && !c->fp64;
+    const int rc = e->local ? eng_local(e, e->side, e->stage_used, st) : eng_general(e, e->side, e->stage_used, st);
+    if (rc != SQH_OK) return rc;
     // later admissions fill the other staging half
     e->side ^= 1;
     e->stage_used = 0;
@@ -1544,6 +1724,22 @@ int sqh_engine_finish(sqh_engine* e)
     int* dn_h = e->h_down + R;
     int* dn_bad = e->h_down + 2 * R;
     int* dn_err = e->h_down + 3 * R;
+    if (e->local) {
+        bool left = false;
+        int big = 1;
+        for (const EngReq& q : e->step_new)
+            if (q.n > kBatchSetMax) left |= e->h_local[big++].left != 0;
+        left |= e->h_local[0].left != 0;
+        if (!left) return eng_collect_local(e, big);
+        // a request that the local kernels do not take: the whole step again
+        // on the segment table
+        e->local = false;
+        int64_t N = 0;
+        for (const EngReq& q : e->step_new) N += q.n;
+        const int rc = eng_general(e, e->side ^ 1, N, st);
+        if (rc != SQH_OK) return rc;
+        HIP_OK(hipEventSynchronize(e->ev_done));
+    }
     if (*dn_err & (kErrSpin | kErrBounds)) {
         e->broken = true;
         return SQH_EDEVICE;

@@ -181,7 +181,8 @@ __global__ __launch_bounds__(1024) void k_batch_init(BatchArgs a)
     __syncthreads();
     for (int pass = 0; pass < 2; ++pass) {
         for (int s = t; s < a.G; s += 1024) {
-            const int64_t v = a.set_off ? gld(a.set_off + s) : 0, w = a.set_off ? gld(a.set_off + s + 1) : a.N;
+            const int64_t v = a.off32 ? a.off32[s] : (a.set_off ? gld(a.set_off + s) : 0);
+            const int64_t w = a.off32 ? a.off32[s + 1] : (a.set_off ? gld(a.set_off + s + 1) : a.N);
             const bool ok = v >= 0 && w >= v && w <= a.N && (s > 0 || v == 0) && (s < a.G - 1 || w == a.N);
             if (pass == 0) {
                 if (!ok) { s_err = 1; continue; }
@@ -189,11 +190,16 @@ __global__ __launch_bounds__(1024) void k_batch_init(BatchArgs a)
                 if (s == a.G - 1) a.start[a.G] = (int)w;
                 const int m = (int)(w - v);
                 a.hcnt[s] = 0;
+                if (a.bad) {
+                    a.bad[s] = 0;
+                    a.hpos[s] = a.hpos_src[s];
+                    if (m > kBatchSetMax) continue;
+                }
                 if (m > kBatchSetMax || (m > kLocalPoints && !a.sieve)) s_left = 1;
                 if (m > 0) atomicAdd(&n[set_class(m)], 1);
             } else {
                 const int m = (int)(w - v);
-                if (m > 0) a.order[atomicAdd(&at[set_class(m)], 1)] = s;
+                if (m > 0 && m <= kBatchSetMax) a.order[atomicAdd(&at[set_class(m)], 1)] = s;
             }
         }
         __syncthreads();
@@ -221,10 +227,14 @@ __device__ __forceinline__ void put_hull(const BatchArgs& a, int s, int base, in
                                          int T)
 {
     if (h == kSetBad) {
-        if (threadIdx.x == 0) atomicOr(&a.ctl->err, kErrNonFinite);
+        if (threadIdx.x == 0) {
+            if (a.bad) a.bad[s] = 1;
+            else atomicOr(&a.ctl->err, kErrNonFinite);
+        }
         return;
     }
-    for (int r = (int)threadIdx.x; r < h; r += T) gst(a.hbuf + base + r, id[ring[r]]);
+    int* out = a.hbuf + (a.hpos ? a.hpos[s] : base);
+    for (int r = (int)threadIdx.x; r < h; r += T) gst(out + r, id[ring[r]]);
     if (threadIdx.x == 0) a.hcnt[s] = h;
 }
 
@@ -593,9 +603,10 @@ __global__ __launch_bounds__(kRingT) void k_batch_ring(BatchArgs a)
             if (key(q) == s_min) s_start = q;  // (one node: the ring's positions differ)
         __syncthreads();
         const int st = s_start;
+        int* out = a.hbuf + (a.hpos ? gld(a.hpos + ds.set) : base);
         for (int q = t; q < m; q += kRingT) {
             const int r = q >= st ? q - st : q - st + m;
-            gst(a.hbuf + base + r, __float_as_int(gld(src + 3 * (size_t)q + 2)));
+            gst(out + r, __float_as_int(gld(src + 3 * (size_t)q + 2)));
         }
         if (t == 0) a.hcnt[ds.set] = m;
         __syncthreads();
@@ -640,7 +651,11 @@ __global__ __launch_bounds__(kEmitT) void k_batch_emit(BatchArgs a)
                 all += red[u];
             }
             s_at[t] = before + inc - h;
-            s_src[t] = s < s1 ? gld(a.start + s) : 0;
+            s_src[t] = s < s1 ? gld((a.hpos ? a.hpos : a.start) + s) : 0;
+            if (s < s1 && a.h_host) {
+                a.h_host[s] = h;
+                a.bad_host[s] = gld(a.bad + s);
+            }
             if (s < s1 && a.out_off) a.out_off[s] = (int64_t)(run + before + inc - h);
             __syncthreads();
             for (int o = t; o < all; o += kEmitT) {
@@ -696,6 +711,10 @@ hipError_t launch_batch(const BatchArgs& a, int cus, hipStream_t st)
         k_batch_pocket<<<6 * cus, 64 * kPocketWaves, 0, st>>>(a);
         k_batch_ring<<<std::min(a.G, 4 * cus), kRingT, 0, st>>>(a);
     }
+    return hipGetLastError();
+}
+hipError_t launch_batch_emit(const BatchArgs& a, int cus, hipStream_t st)
+{
     k_batch_emit<<<std::min((a.G + 3) / 4, 4 * cus), kEmitT, 0, st>>>(a);
     return hipGetLastError();
 }
@@ -725,6 +744,7 @@ hipError_t launch_sieve(const SieveArgs& a, int cus, hipStream_t st, LaunchMark 
     timed("k_polygon", [&] { k_polygon<<<1, 1024, 0, st>>>(a, ne); });
     if (mid) {
         timed("k_sieve_solve", [&] { k_sieve_solve<<<ns, kMidT, 0, st>>>(a, share); });
+        if (a.gate) k_rest<<<cus, kMidT, 0, st>>>(a, ns, share, 0);
     } else {
         timed("k_sieve", [&] { k_sieve<<<ns, kSieveT, 0, st>>>(a); });
         timed("k_rest", [&] { k_rest<<<std::min(64, cus), kMidT, 0, st>>>(a, ns, share, 1); });

@@ -58,6 +58,9 @@ struct SieveArgs {
     int* lid;
     int* lcnt;         // n / 64 or more: their sizes
     SieveCtl* ctl;
+    // one of an engine's requests (else null): its hull size and bad flag, and
+    // what follows (0: nothing, 1: the ring kernels, 2: k_rest)
+    int *h_dev, *bad_dev, *gate;
 };
 size_t sieve_ctl_bytes();
 hipError_t launch_sieve(const SieveArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx);
@@ -95,6 +98,8 @@ struct RingArgs {
     RingPocket* pockets;
     int pocket_cap;
     RingCtl* ctl;
+    int *h_dev, *bad_dev;  // as the sieve's
+    const int* gate;       // run only if this is 1
 };
 size_t ring_ctl_bytes();
 hipError_t launch_ring(const RingArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx);
@@ -127,8 +132,15 @@ struct BatchArgs {
     DenseSet* dense;
     int dense_cap;
     BatchCtl* ctl;
+    // an engine's requests (null for a batch): offsets in place of set_off,
+    // where each hull goes in hbuf, a flag for each set with a non-finite
+    // coordinate, and the host's copies of sizes and flags. Sets of more than
+    // kBatchSetMax points are left out.
+    const int *off32, *hpos_src;
+    int *hpos, *bad, *h_host, *bad_host;
 };
 size_t batch_ctl_bytes();
 hipError_t launch_batch(const BatchArgs& a, int cus, hipStream_t st);
+hipError_t launch_batch_emit(const BatchArgs& a, int cus, hipStream_t st);
 
 }  // namespace sqh

@@ -64,6 +64,8 @@ struct RingCtl {
     int turns, bad, ticket, pad;
 };
 
+__device__ __forceinline__ bool gate_shut(const RingArgs& a) { return a.gate && *a.gate != 1; }
+
 // The bin of a direction: 1024 to a quadrant, by the share of |y| in |x| + |y|
 // (turning counter-clockwise). near: closer to a bin's border than the rounding
 // of x, y (scaled by the extents) and of this may have moved it, or the border:
@@ -115,6 +117,7 @@ __global__ __launch_bounds__(1024) void k_ring_rays(RingArgs a)
     __shared__ float2 ray[kRays];
     __shared__ int bin[kRays];
     RingCtl* ctl = a.ctl;
+    if (gate_shut(a)) return;
     const int t = (int)threadIdx.x, lane = lane_id(), n = a.n;
     constexpr int U = kRingSample / 1024;
     if (t == 0) {
@@ -263,6 +266,7 @@ __global__ __launch_bounds__(1024) void k_ring_count(RingArgs a)
     __shared__ int cnt[kRays], s_bad;
     __shared__ uint32_t csum[3];
     RingCtl* ctl = a.ctl;
+    if (gate_shut(a)) return;
     if (ctl->left) return;
     const int t = (int)threadIdx.x, b = (int)blockIdx.x;
     for (int k = t; k <= ctl->nr; k += 1024) ray[k] = gld(ctl->ray + k);
@@ -307,6 +311,7 @@ __global__ __launch_bounds__(1024) void k_ring_scan(RingArgs a, int nb)
 {
     __shared__ int part[16][64];
     RingCtl* ctl = a.ctl;
+    if (gate_shut(a)) return;
     if (ctl->left | ctl->err) return;
     const int lane = lane_id(), w = (int)(threadIdx.x >> 6), k = (int)blockIdx.x * 64 + lane;
     const int per = (nb + 15) / 16, b0 = min(w * per, nb), b1 = min(b0 + per, nb);
@@ -334,6 +339,7 @@ __global__ __launch_bounds__(1024) void k_ring_scatter(RingArgs a)
     constexpr int U = 4;
     __shared__ int cur[kRays], red[16];
     RingCtl* ctl = a.ctl;
+    if (gate_shut(a)) return;
     if (ctl->left | ctl->err) return;
     const int t = (int)threadIdx.x, b = (int)blockIdx.x;
     int all;
@@ -384,6 +390,7 @@ __global__ __launch_bounds__(1024) void k_ring_cut(RingArgs a)
     __shared__ uint16_t lut[kSubBins];
     __shared__ int hist[kSubBins], cnt[kSubRays], cur[kSubRays], start[kSubRays + 1], red[16], s_p0, s_bad;
     RingCtl* ctl = a.ctl;
+    if (gate_shut(a)) return;
     const int t = (int)threadIdx.x, w = (int)blockIdx.x;
     if ((ctl->left | ctl->err) || w >= ctl->nr) return;
     const int off = ctl->wedge[w].off, len = ctl->wedge[w].len;
@@ -463,6 +470,7 @@ __global__ __launch_bounds__(64 * kRingWaves) void k_ring_pocket(RingArgs a)
     __shared__ WaveLds Ws[kRingWaves];
     __shared__ uint32_t csum[3];
     RingCtl* ctl = a.ctl;
+    if (gate_shut(a)) return;
     if (ctl->left | ctl->err) return;
     const int lane = lane_id(), w = (int)(threadIdx.x >> 6), np = ctl->n_pocket;
     const float2 c = ctl->c;
@@ -594,6 +602,7 @@ __global__ __launch_bounds__(kWedgeT) void k_ring_wedge(RingArgs a)
     __shared__ float4 s_list[2][kWedgeLds];
     __shared__ uint32_t csum[3];
     RingCtl* ctl = a.ctl;
+    if (gate_shut(a)) return;
     const int t = (int)threadIdx.x, w = (int)blockIdx.x;
     if ((ctl->left | ctl->err) || w >= ctl->nr) return;
     const int first = ctl->wedge[w].first, K = ctl->wedge[w].cnt, off = ctl->wedge[w].off;
@@ -668,6 +677,7 @@ __global__ __launch_bounds__(1024) void k_ring_join(RingArgs a)
     __shared__ unsigned long long s_min;
     __shared__ uint32_t csum[3];
     RingCtl* ctl = a.ctl;
+    if (gate_shut(a)) return;
     const int t = (int)threadIdx.x, lane = lane_id(), w = t >> 6;
     if (ctl->left | ctl->err) return;
     int K;
@@ -814,6 +824,7 @@ __global__ __launch_bounds__(kRingEmitT) void k_ring_emit(RingArgs a)
     __shared__ int s_last;
     __shared__ uint32_t csum[3];
     RingCtl* ctl = a.ctl;
+    if (gate_shut(a)) return;
     LocalStatus* st = a.status;
     const int t = (int)threadIdx.x, b = (int)blockIdx.x, nb = (int)gridDim.x;
     if (ctl->left | ctl->err) {
@@ -821,6 +832,10 @@ __global__ __launch_bounds__(kRingEmitT) void k_ring_emit(RingArgs a)
             st->h = 0;
             st->err = ctl->err;
             st->left = ctl->err ? 0 : 1;
+            if (a.gate) {
+                *a.h_dev = 0;
+                *a.bad_dev = ctl->err != 0;
+            }
         }
         return;
     }
@@ -871,6 +886,10 @@ __global__ __launch_bounds__(kRingEmitT) void k_ring_emit(RingArgs a)
         st->h = good ? h : 0;
         st->err = 0;
         st->left = good ? 0 : 1;
+        if (a.gate) {
+            *a.h_dev = good ? h : 0;
+            *a.bad_dev = 0;
+        }
         st->passes = 0;
         st->first_v = a.n;
         st->line = a.line;

@@ -463,6 +463,11 @@ __device__ __forceinline__ void rest_finish(const SieveArgs& a, SolveLds<P>& L, 
         s->cmp_exact = ctr_total(ctl->ctr, 2) + csum[2];
         s->t0 = ctl->t0;
         s->t1 = wall_clock64();
+        if (a.gate) {
+            *a.h_dev = hh;
+            *a.bad_dev = err != 0;
+            *a.gate = (!err && left) ? 1 : 0;
+        }
     }
 }
 
@@ -668,6 +673,7 @@ __global__ __launch_bounds__(kMidT) void k_sieve_solve(SieveArgs a, int per)
         if (blockIdx.x == 0 && t == 0) {
             a.status->left = 1;
             a.status->err = 0;
+            if (a.gate) *a.gate = 1;
         }
         return;
     }
@@ -687,6 +693,7 @@ __global__ __launch_bounds__(kMidT) void k_sieve_solve(SieveArgs a, int per)
     if (t == 0 && M > kMidP) {
         ctl->done = 0u;
         a.status->left = 2;  // k_rest takes them
+        if (a.gate) *a.gate = 2;
     }
 }
 
@@ -702,6 +709,7 @@ __global__ __launch_bounds__(kMidT) void k_rest(SieveArgs a, int ns, int per, in
     __shared__ float s_m[2];
     SieveCtl* ctl = a.ctl;
     const int t = (int)threadIdx.x, lane = lane_id(), b = (int)blockIdx.x, nb = (int)gridDim.x;
+    if (a.gate && !second && *a.gate != 2) return;
     const int none = ctl->left | ctl->err;
     stats_clear(st);
     if (t < 3) csum[t] = 0u;

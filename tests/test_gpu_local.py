@@ -256,3 +256,60 @@ def test_batch_errors(H):
     assert rc == sqh.SQH_ECAPACITY and h == len(want)
     assert [int(v) for v in out.cpu().numpy()] == want[:cap] + [-7] * 100
     assert int(out_off[3]) == len(want)
+
+
+def serve(E, reqs, passes, per_step=10 ** 6):
+    """Admits as room allows, per_step requests at most before each step."""
+    import torch
+    copy = torch.cuda.Stream()
+    got, nxt, inflight = {}, 0, False
+    for _ in range(1000):
+        for _ in range(per_step):
+            if nxt == len(reqs) or not E.admit(reqs[nxt], nxt, stream=copy):
+                break
+            nxt += 1
+        if inflight:
+            E.finish()
+            for tag, hull in iter(E.poll, None):
+                got[tag] = hull
+        if len(got) >= len(reqs):
+            return got
+        inflight = E.launch(passes)
+    raise AssertionError("the engine does not finish")
+
+
+@pytest.mark.parametrize("hi,per_step", [(3000, 7), (90_000, 10 ** 6), (1_400_000, 4)])
+def test_engine_steps_of_many_passes(H, hi, per_step):
+    """Steps on the local kernels: every size class, requests of more than a
+    million points, bad and empty ones, one that the local kernels leave
+    (a quarter of a circle), and a step of few passes in between."""
+    rng = np.random.default_rng(hi)
+    sizes = [1, 2, 63, 64, 65, 1024, 1025, 4096, 4097, hi, hi - 1] + [int(v) for v in rng.integers(1, hi, 14)]
+    kinds = ("square", "disk", "circle", "grid")
+    reqs = [workloads.make(kinds[i % 4], n, i) for i, n in enumerate(sizes)]
+    if hi > 1 << 20:
+        reqs += [workloads.circle((1 << 20) + 1, 3), workloads.disk((1 << 20) + 2, 4), workloads.square(1_600_001, 5)]
+    bad = workloads.disk(hi, 6)
+    bad[hi // 2, 1] = np.nan
+    t = rng.random(hi) * 1.5
+    reqs += [bad, np.zeros((0, 2), np.float32), workloads.disk(777, 8), np.stack([np.cos(t), np.sin(t)], 1).astype(np.float32)]
+    for left in (False, True):
+        rs = reqs if left else reqs[:-1]
+        want_ = [None if not np.all(np.isfinite(xy)) else [int(v) for v in oracle.c_hull(xy)] for xy in rs]
+        E = H.engine(1 << 23, 64, 1 << 22)
+        try:
+            for passes in (32, 16, 2):
+                print(f"[case] engine hi={hi} passes={passes} left={left}", file=sys.stderr, flush=True)
+                got = serve(E, rs, passes, per_step)
+                for i, w in enumerate(want_):
+                    assert (got[i] is None) if w is None else ([int(v) for v in got[i]] == w), (passes, i, len(rs[i]))
+                st = E.status()
+                assert st["free_slots"] == E.slots and st["resident"] == 0
+            # a request in the table from a step of few passes, then local steps
+            assert E.admit(workloads.circle(100_000, 1), 900)
+            E.step(1)
+            assert E.status()["resident"] == 1
+            got = serve(E, rs[:9], 32)
+            assert 900 in got and [int(v) for v in got[8]] == want_[8]
+        finally:
+            E.close()
