@@ -39,65 +39,125 @@ struct DenseSet {
     int pad2[2];
 };
 
+constexpr int kRingBins = 4096;        // bins of the angle
+constexpr float kRingNear = 0x1p-10f;  // (a share of a bin)
+
+// The bin of a direction: 1024 to a quadrant, by the share of |y| in |x| + |y|
+// (turning counter-clockwise). near: closer to a bin's border than the rounding
+// of x, y (scaled by the extents) and of this may have moved it, or the border:
+// together less than half of kRingNear where the centre is within 64 extents of 0.
+__device__ __forceinline__ int ring_bin(float x, float y, bool& near)
+{
+    constexpr int Q = kRingBins / 4;
+    const float a = fabsf(x), b = fabsf(y), s = a + b;
+    const bool l = x < 0.0f, d = y < 0.0f;
+    const float f = (l == d ? b : a) * __builtin_amdgcn_rcpf(s) * (float)Q;
+    const int j = min(max((int)f, 0), Q - 1);
+    const float r = f - (float)j;
+    near = !((int)(r >= kRingNear) & (int)(r <= 1.0f - kRingNear) & (int)(s > 0x1p-100f));
+    return (d ? (l ? 2 : 3) : (l ? 1 : 0)) * Q + j;
+}
+
 struct DenseLds {
     float2 v[kDenseMaxK];  // the vertices
-    float2 d[kDenseMaxK];  // fl(v - c)
     int id[kDenseMaxK];
     int cnt[kDenseMaxK], cur[kDenseMaxK];
-    float2 c;
-    int half;   // first vertex more than half a turn after v_0
+    uint16_t lut[kRingBins];  // the last vertex at or before a bin's start, but for rounding
+    float2 c, inv;  // the centre; 1 / half extents
+    unsigned int lo[2], hi[2];
     int bad;
 };
 
 // Chooses the vertices and the centre from the ring L.ring[0 .. h) of a
-// sample (h >= 8 K >= 16). D must not overlap L.xy, L.id or L.ring.
+// sample (h >= 2 K >= 8). D may overlap everything of L but L.bad.
 // Returns false if the centre is not certified inside (then nothing is usable).
 template <int T, int P>
 __device__ __forceinline__ bool dense_build(const SolveLds<P>& L, int h, int K, DenseLds& D)
 {
+    constexpr int E = kDenseMaxK / T;
     const int t = (int)threadIdx.x;
-    for (int k = t; k < K; k += T) {
-        const int r = L.ring[(int)((long long)k * h / K)];
-        D.v[k] = L.xy[r];
-        D.id[k] = L.id[r];
-        D.cnt[k] = 0;
+    float2 v[E];
+    int id[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int k = t + T * e;
+        if (k < K) {
+            const int r = L.ring[(int)((long long)k * h / K)];
+            v[e] = L.xy[r];
+            id[e] = L.id[r];
+        }
     }
+    const float2 p = L.xy[L.ring[0]], q = L.xy[L.ring[h / 3]], r = L.xy[L.ring[2 * h / 3]];
+    lds_barrier();
     if (t == 0) {
-        const float2 p = L.xy[L.ring[0]], q = L.xy[L.ring[h / 3]], r = L.xy[L.ring[2 * h / 3]];
         D.c.x = (float)(((double)p.x + (double)q.x + (double)r.x) / 3.0);
         D.c.y = (float)(((double)p.y + (double)q.y + (double)r.y) / 3.0);
-        D.half = K;
         D.bad = 0;
     }
+    if (t < 2) { D.lo[t] = ~0u; D.hi[t] = 0u; }
+    for (int b = t; b < kRingBins; b += T) D.lut[b] = 0;
     lds_barrier();
+    uint32_t box[4] = {~0u, ~0u, 0u, 0u};
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int k = t + T * e;
+        if (k < K) {
+            D.v[k] = v[e];
+            D.id[k] = id[e];
+            D.cnt[k] = 0;
+            const uint32_t x = order_key(v[e].x), y = order_key(v[e].y);
+            box[0] = min(box[0], x); box[1] = min(box[1], y);
+            box[2] = max(box[2], x); box[3] = max(box[3], y);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint64_t mn = wave_min_u64(box[i]), mx = wave_max_u64(box[2 + i]);
+        if (lane_id() == 63) {
+            atomicMin(&D.lo[i], (unsigned int)mn);
+            atomicMax(&D.hi[i], (unsigned int)mx);
+        }
+    }
+    lds_barrier();
+    auto back = [](uint32_t u) { return __uint_as_float((u & 0x80000000u) ? u ^ 0x80000000u : ~u); };
+    const float ex = back(D.hi[0]) - back(D.lo[0]), ey = back(D.hi[1]) - back(D.lo[1]);
+    const float2 c = D.c, inv = make_float2((ex > 0.0f && ex < INFINITY) ? 2.0f / ex : 1.0f, (ey > 0.0f && ey < INFINITY) ? 2.0f / ey : 1.0f);
+    if (t == 0) D.inv = inv;
     for (int k = t; k < K; k += T) {
-        const float2 c = D.c, v = D.v[k], w = D.v[k + 1 < K ? k + 1 : 0];
-        D.d[k] = make_float2(v.x - c.x, v.y - c.y);
-        if (orient_exact(v.x, v.y, w.x, w.y, c.x, c.y) <= 0) D.bad = 1;
-        if (k > 0 && orient_exact(c.x, c.y, D.v[0].x, D.v[0].y, v.x, v.y) < 0) atomicMin(&D.half, k);
+        const float2 a = D.v[k], b = D.v[k + 1 < K ? k + 1 : 0];
+        if (orient_exact(a.x, a.y, b.x, b.y, c.x, c.y) <= 0) D.bad = 1;
+        bool near;
+        const int i = ring_bin((a.x - c.x) * inv.x, (a.y - c.y) * inv.y, near);
+        const int n = (ring_bin((b.x - c.x) * inv.x, (b.y - c.y) * inv.y, near) - i) & (kRingBins - 1);
+        // (a wedge is less than half a turn; more is a rounded step back)
+        if (n <= kRingBins / 2 + 1)
+            for (int j = 1; j <= n; ++j) D.lut[(i + j) & (kRingBins - 1)] = (uint16_t)k;
     }
     lds_barrier();
     return D.bad == 0;
 }
 
-// The wedge of p by rounded cross products (off by one at most near a ray).
+// The wedge of p, but for rounding: from the bin's first vertex by bisection
+// among the bin's (of 1024 even wedges a bin holds one in four, and ten steps
+// of bisection over all of them took half of the cut's time).
 __device__ __forceinline__ int wedge_guess(const DenseLds& D, int K, float px, float py)
 {
-    const float2 c = D.c;
+    const float2 c = D.c, inv = D.inv;
     const float x = px - c.x, y = py - c.y;
-    const float2 d0 = D.d[0];
-    const bool first = d0.x * y - d0.y * x >= 0.0f;
-    int lo = first ? 0 : D.half - 1, hi = first ? D.half : K;  // the last ray at or before p is in [lo, hi)
-    const int steps = 32 - __clz(max(D.half, K - D.half + 1));
-    for (int s = 0; s < steps; ++s) {
-        const int m = (lo + hi) >> 1;
-        const float2 d = D.d[m];
-        const bool after = d.x * y - d.y * x >= 0.0f;
-        const bool more = hi - lo > 1;
-        lo = (more & after) ? m : lo;
-        hi = (more & !after) ? m : hi;
+    bool near;
+    const int b = ring_bin(x * inv.x, y * inv.y, near);
+    int k = D.lut[b], span = (int)D.lut[(b + 1) & (kRingBins - 1)] - k;
+    span = span < 0 ? span + K : span;  // vertices in the bin
+    while (span > 0) {
+        const int half = (span + 1) >> 1;
+        int m = k + half;
+        m = m >= K ? m - K : m;
+        const float2 v = D.v[m];
+        const bool after = (v.x - c.x) * y - (v.y - c.y) * x >= 0.0f;
+        k = after ? m : k;
+        span = after ? span - half : half - 1;
     }
-    return lo;
+    return k;
 }
 
 // Pocket of p: k if p is strictly right of v_k -> v_{k+1} in wedge k, else -1.

@@ -565,6 +565,17 @@ int collect_local(sqh_ctx* ctx, int64_t N, int64_t out_cap, int64_t* h_total)
     return L.h > out_cap ? SQH_ECAPACITY : SQH_OK;
 }
 
+// A batch's pockets in the space of the child records (42 bytes a point) and of
+// the two segment tables (21 each).
+void batch_space(BatchArgs& b, void* recs, void* segs0, void* segs1)
+{
+    b.slots = static_cast<float4*>(recs);
+    b.slots2 = b.slots + b.N;
+    b.pockets = static_cast<Pocket*>(segs0);
+    b.pocket_cap = b.N / 128 + 4;
+    for (int c = 0; c < 3; ++c) b.todo[c] = static_cast<int*>(segs1) + (size_t)c * b.pocket_cap;
+}
+
 // The local kernels on n points of a call's workspace, xy with indices ids
 // (null: their places), up to the end of the stream.
 hipError_t run_local(sqh_ctx* ctx, const HullArgs& a, const float2* xy, const int* ids, int n, int32_t* d_out,
@@ -726,13 +737,7 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
         b.hcnt = reinterpret_cast<int*>(a.sets);
         b.order = b.hcnt + nsets;
         b.hbuf = a.vidx;
-        b.slots = a.X[0];
-        b.pockets = reinterpret_cast<Pocket*>(a.recs);
-        b.pocket_cap = (int)(N / 128 + 4);
-        b.todo[0] = reinterpret_cast<int*>(a.segs[0]);
-        b.todo[1] = reinterpret_cast<int*>(a.segs[1]);
-        b.todo[2] = b.todo[1] + b.pocket_cap;
-        b.slots2 = a.X[1];
+        batch_space(b, a.recs, a.segs[0], a.segs[1]);
         b.dense = reinterpret_cast<DenseSet*>(a.seg_cid[0]);
         b.dense_cap = (int)(N / 4096 + 1);
         b.ctl = reinterpret_cast<BatchCtl*>(a.slots);
@@ -1042,7 +1047,7 @@ int eng_general(sqh_engine* e, int side, int64_t N, hipStream_t st)
 }
 
 // The launched step on the local kernels (no resident segments): its requests
-// as a batch, those of more than kBatchSetMax points past the sieve one after
+// as a batch, those of more than kEngineSetMax points past the sieve one after
 // another, with what the sieve leaves decided on the device; the hulls and
 // their sizes straight to pinned memory.
 int eng_local(sqh_engine* e, int side, int64_t N, hipStream_t st)
@@ -1066,13 +1071,7 @@ int eng_local(sqh_engine* e, int side, int64_t N, hipStream_t st)
     b.hcnt = static_cast<int*>(at(L.res_h));
     b.order = static_cast<int*>(at(L.res_alive));
     b.hbuf = static_cast<int*>(at(L.hout));
-    b.slots = static_cast<float*>(at(L.x[0]));
-    b.slots2 = static_cast<float*>(at(L.x[1]));
-    b.pockets = static_cast<Pocket*>(at(L.recs));
-    b.pocket_cap = (int)(N / 128 + 4);
-    b.todo[0] = static_cast<int*>(at(L.segs[0]));
-    b.todo[1] = static_cast<int*>(at(L.segs[1]));
-    b.todo[2] = b.todo[1] + b.pocket_cap;
+    batch_space(b, at(L.recs), at(L.segs[0]), at(L.segs[1]));
     b.dense = static_cast<DenseSet*>(at(L.seg_cid[0]));
     b.dense_cap = (int)(N / 4096 + 1);
     b.ctl = static_cast<BatchCtl*>(at(L.info));
@@ -1086,7 +1085,7 @@ int eng_local(sqh_engine* e, int side, int64_t N, hipStream_t st)
     int big = 0;
     for (int g = 0; g < G; ++g) {
         const EngReq& q = e->step_new[g];
-        if (q.n <= kBatchSetMax) continue;
+        if (q.n <= kEngineSetMax) continue;
         LocalStatus* status = e->h_local + 1 + big++;
         SieveArgs v{};
         v.xy = stage + q.stage_at;
@@ -1593,7 +1592,7 @@ int sqh_engine_create(sqh_ctx* c, void* d_arena, size_t arena_bytes, int64_t slo
         hipHostMalloc(reinterpret_cast<void**>(&e->h_bounce), sizeof(int32_t) * (size_t)e->bounce_cap,
                       hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&e->h_info), sizeof(HullInfo), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&e->h_local), sizeof(LocalStatus) * (size_t)(2 + stage_points / kBatchSetMax),
+        hipHostMalloc(reinterpret_cast<void**>(&e->h_local), sizeof(LocalStatus) * (size_t)(2 + stage_points / kEngineSetMax),
                       hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&e->ev_admit, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&e->ev_done, hipEventDisableTiming) != hipSuccess) {
@@ -1728,7 +1727,7 @@ int sqh_engine_finish(sqh_engine* e)
         bool left = false;
         int big = 1;
         for (const EngReq& q : e->step_new)
-            if (q.n > kBatchSetMax) left |= e->h_local[big++].left != 0;
+            if (q.n > kEngineSetMax) left |= e->h_local[big++].left != 0;
         left |= e->h_local[0].left != 0;
         if (!left) return eng_collect_local(e, big);
         // a request that the local kernels do not take: the whole step again

@@ -193,13 +193,13 @@ __global__ __launch_bounds__(1024) void k_batch_init(BatchArgs a)
                 if (a.bad) {
                     a.bad[s] = 0;
                     a.hpos[s] = a.hpos_src[s];
-                    if (m > kBatchSetMax) continue;
+                    if (m > kEngineSetMax) continue;
                 }
                 if (m > kBatchSetMax || (m > kLocalPoints && !a.sieve)) s_left = 1;
                 if (m > 0) atomicAdd(&n[set_class(m)], 1);
             } else {
                 const int m = (int)(w - v);
-                if (m > 0 && m <= kBatchSetMax) a.order[atomicAdd(&at[set_class(m)], 1)] = s;
+                if (m > 0 && (!a.bad || m <= kEngineSetMax)) a.order[atomicAdd(&at[set_class(m)], 1)] = s;
             }
         }
         __syncthreads();
@@ -235,7 +235,7 @@ __device__ __forceinline__ void put_hull(const BatchArgs& a, int s, int base, in
     }
     int* out = a.hbuf + (a.hpos ? a.hpos[s] : base);
     for (int r = (int)threadIdx.x; r < h; r += T) gst(out + r, id[ring[r]]);
-    if (threadIdx.x == 0) a.hcnt[s] = h;
+    if (threadIdx.x == 0) a.hcnt[s] = max(h, 0);  // (a ring's comes later)
 }
 
 // Sets of up to kSmallP points, a workgroup each.
@@ -266,9 +266,9 @@ template <int T, int P>
 __device__ __forceinline__ bool cut_pockets(const BatchArgs& a, SolveLds<P>& L, int h, int s, int base, int n,
                                             Counters& ctr)
 {
-    static_assert(sizeof(DenseLds) <= sizeof(L.bins), "the tables take the slabs' space");
+    static_assert(sizeof(DenseLds) <= offsetof(SolveLds<P>, kmin), "the tables take the solve's space");
     constexpr int U = 4;
-    DenseLds& D = *reinterpret_cast<DenseLds*>(&L.bins[0]);
+    DenseLds& D = *reinterpret_cast<DenseLds*>(&L);
     __shared__ int s_t0, s_d, s_q[kTasks];
     const int t = (int)threadIdx.x;
     const int K = min(min(max(4, n / kDenseTarget), h / 2), kDenseMaxK);
@@ -276,55 +276,71 @@ __device__ __forceinline__ bool cut_pockets(const BatchArgs& a, SolveLds<P>& L, 
     if (!dense_build<T, P>(L, h, K, D)) return false;
     const float2* xy = a.xy + base;
     bool bad = false;
-    // twice over the set: counts, then the points to their pockets
-    for (int ps = 0; ps < 2; ++ps) {
-        for (int q0 = 0; q0 < n; q0 += T * U) {
-            float2 v[U];
+    // each point's pocket (kept in the ring nodes' space), counted; a step's
+    // points are loaded a step ahead
+    uint16_t* pid = reinterpret_cast<uint16_t*>(a.slots2 + base);
+    float2 nv[U];
+    auto fetch = [&](int q0) {
 #pragma unroll
-            for (int j = 0; j < U; ++j) v[j] = gld(xy + min(q0 + t + T * j, n - 1));
+        for (int j = 0; j < U; ++j) nv[j] = gld(xy + min(q0 + t + T * j, n - 1));
+    };
+    fetch(0);
+    for (int q0 = 0; q0 < n; q0 += T * U) {
+        float2 v[U];
 #pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const int q = q0 + t + T * j;
-                const bool fin = (int)isfinite(v[j].x) & (int)isfinite(v[j].y);
-                bad |= !fin;
-                int k = -1;
-                if (q < n && fin) k = pocket_of(D, K, v[j].x, v[j].y, q, ctr);
-                if (k >= 0) {
-                    if (ps == 0) {
-                        atomicAdd(&D.cnt[k], 1);
-                    } else {
-                        float* d = a.slots + 3 * (size_t)(base + atomicAdd(&D.cur[k], 1));
-                        gst(d, v[j].x);
-                        gst(d + 1, v[j].y);
-                        gst(d + 2, __int_as_float(q));
-                    }
-                }
+        for (int j = 0; j < U; ++j) v[j] = nv[j];
+        fetch(q0 + T * U);
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int q = q0 + t + T * j;
+            const bool fin = (int)isfinite(v[j].x) & (int)isfinite(v[j].y);
+            bad |= !fin;
+            if (q < n && fin) {
+                const int k = pocket_of(D, K, v[j].x, v[j].y, q, ctr);
+                pid[q] = (uint16_t)k;
+                if (k >= 0) atomicAdd(&D.cnt[k], 1);
             }
         }
-        if (ps == 0) {
-            if (__ballot(bad) && lane_id() == 0) L.bad = 1;
-            lds_barrier();
-            if (L.bad) return true;
-            // slot ranges (one more than its points for v_k), by one wave
-            if (t < 64) {
-                int run = 0;
-                for (int k0 = 0; k0 < K; k0 += 64) {
-                    const int k = k0 + t, c = k < K ? D.cnt[k] + 1 : 0;
-                    if (c > P - 1) D.bad = 1;
-                    const int inc = wave_incl_sum(c);
-                    if (k < K) D.cur[k] = run + inc - c;
-                    run += __builtin_amdgcn_readlane(inc, 63);
-                }
-                if (t == 0) {
-                    const int d = atomicAdd(&a.ctl->n_dense, 1);
-                    s_t0 = atomicAdd(&a.ctl->n_pocket, K);
-                    if (d >= a.dense_cap || s_t0 + K > a.pocket_cap) D.bad = 1;
-                    else gst(a.dense + d, DenseSet{s, s_t0, K, 0, D.c.x, D.c.y, {0, 0}});
-                    s_d = d;
-                }
-            }
-            lds_barrier();
-            if (D.bad) return false;
+    }
+    if (__ballot(bad) && lane_id() == 0) L.bad = 1;
+    lds_barrier();
+    if (L.bad) return true;
+    // slot ranges (one more than its points for v_k), by one wave
+    if (t < 64) {
+        int run = 0;
+        for (int k0 = 0; k0 < K; k0 += 64) {
+            const int k = k0 + t, c = k < K ? D.cnt[k] + 1 : 0;
+            if (c > kTaskP[kTasks - 1] - 1) D.bad = 1;
+            const int inc = wave_incl_sum(c);
+            if (k < K) D.cur[k] = run + inc - c;
+            run += __builtin_amdgcn_readlane(inc, 63);
+        }
+        if (t == 0) {
+            const int d = atomicAdd(&a.ctl->n_dense, 1);
+            s_t0 = atomicAdd(&a.ctl->n_pocket, K);
+            if (d >= a.dense_cap || s_t0 + K > a.pocket_cap) D.bad = 1;
+            else gst(a.dense + d, DenseSet{s, s_t0, K, 0, D.c.x, D.c.y, {0, 0}});
+            s_d = d;
+        }
+    }
+    lds_barrier();
+    if (D.bad) return false;
+    // the points to their pockets
+    constexpr int V = 8;
+    for (int q0 = 0; q0 < n; q0 += T * V) {
+        float2 v[V];
+        int k[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const int q = min(q0 + t + T * j, n - 1);
+            v[j] = gld(xy + q);
+            k[j] = pid[q];
+        }
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const int q = q0 + t + T * j;
+            if (q < n && k[j] < K)
+                gst(a.slots + base + atomicAdd(&D.cur[k[j]], 1), make_float4(v[j].x, v[j].y, __int_as_float(q), 0.0f));
         }
     }
     if (t < kTasks) s_q[t] = 0;
@@ -345,10 +361,7 @@ __device__ __forceinline__ bool cut_pockets(const BatchArgs& a, SolveLds<P>& L, 
         p.aid = D.id[k]; p.off = off; p.len = len; p.ring = s_d;
         if (len == 0) {
             // the vertex alone
-            float* d = a.slots + 3 * (size_t)off;
-            gst(d, v.x);
-            gst(d + 1, v.y);
-            gst(d + 2, __int_as_float(p.aid));
+            gst(a.slots + off, make_float4(v.x, v.y, __int_as_float(p.aid), 0.0f));
             p.len = 1;
         } else {
             const int c = size_of(len);
@@ -359,10 +372,13 @@ __device__ __forceinline__ bool cut_pockets(const BatchArgs& a, SolveLds<P>& L, 
     return true;
 }
 
-// Larger sets, the largest first.
+// Larger sets, the largest first. (Two workgroups of 512 threads and 2048 points
+// to a compute unit, so that one fills the other's waits, took as long, and
+// their smaller samples cut less even pockets.)
 __global__ __launch_bounds__(kMidT) void k_batch_big(BatchArgs a)
 {
-    __shared__ SolveLds<kMidP> L;
+    constexpr int T = kMidT, P = kMidP;
+    __shared__ SolveLds<P> L;
     __shared__ BatchAcc A;
     __shared__ int s_i;
     BatchCtl* ctl = a.ctl;
@@ -380,26 +396,24 @@ __global__ __launch_bounds__(kMidT) void k_batch_big(BatchArgs a)
         if (i >= nb) break;
         const int s = a.order[i], base = a.start[s], n = a.start[s + 1] - base;
         int sample = 0;
-        int h = solve_set<kMidT, kMidP>(L, a.xy + base, n, a.fp64 != 0, ctr, &A.st, &sample);
+        int h = solve_set<T, P>(L, a.xy + base, n, a.fp64 != 0, ctr, &A.st, &sample);
         if (h == kSetDense) {
-            const bool ok = sample > 0 && cut_pockets<kMidT, kMidP>(a, L, sample, s, base, n, ctr);
+            const bool ok = sample > 0 && cut_pockets<T, P>(a, L, sample, s, base, n, ctr);
             if (!ok && threadIdx.x == 0) ctl->left = 1;
             if (L.bad) h = kSetBad;
         }
-        put_hull(a, s, base, h, L.id, L.ring, kMidT);
+        put_hull(a, s, base, h, L.id, L.ring, T);
         lds_barrier();
     }
     acc_flush(A, ctr, ctl);
 }
 
-__device__ __forceinline__ void put_nodes(float* slot, const float2* xy, const int* id, const uint16_t* ring, int nodes,
+__device__ __forceinline__ void put_nodes(float4* slot, const float2* xy, const int* id, const uint16_t* ring, int nodes,
                                           int T)
 {
     for (int r = (int)threadIdx.x; r < nodes; r += T) {
         const int q = ring[r];
-        gst(slot + 3 * r, xy[q].x);
-        gst(slot + 3 * r + 1, xy[q].y);
-        gst(slot + 3 * r + 2, __int_as_float(id[q]));
+        gst(slot + r, make_float4(xy[q].x, xy[q].y, __int_as_float(id[q]), 0.0f));
     }
 }
 
@@ -422,28 +436,23 @@ __global__ __launch_bounds__(64 * kPocketWaves) void k_batch_pocket(BatchArgs a)
         const int j = gld(a.todo[0] + i);
         const Pocket p = gld(a.pockets + j);
         const float2 c = make_float2(gld(&a.dense[p.ring].cx), gld(&a.dense[p.ring].cy));
-        float* slot = a.slots + 3 * (size_t)p.off;
+        float4* slot = a.slots + p.off;
 #pragma unroll
         for (int r = 0; r < kWavePts / 64; ++r) {
             const int q = lane + 64 * r;
             if (q < p.len) {
-                W.xy[0][q] = make_float2(gld(slot + 3 * q), gld(slot + 3 * q + 1));
-                W.id[q] = __float_as_int(gld(slot + 3 * q + 2));
+                const float4 v = gld(slot + q);
+                W.xy[0][q] = make_float2(v.x, v.y);
+                W.id[q] = __float_as_int(v.z);
             }
         }
         wave_sync();
         int f;
         const int m = wave_chain<false>(W, p.len, c, make_float2(p.ax, p.ay), make_float2(p.bx, p.by), f, ctr);
-        for (int q = lane; q < m; q += 64) {
-            float* d = slot + 3 * (q + 1);
-            gst(d, W.xy[f][q].x);
-            gst(d + 1, W.xy[f][q].y);
-            gst(d + 2, __int_as_float(W.id[W.at[f][q]]));
-        }
+        for (int q = lane; q < m; q += 64)
+            gst(slot + q + 1, make_float4(W.xy[f][q].x, W.xy[f][q].y, __int_as_float(W.id[W.at[f][q]]), 0.0f));
         if (lane == 0) {
-            gst(slot, p.ax);
-            gst(slot + 1, p.ay);
-            gst(slot + 2, __int_as_float(p.aid));
+            gst(slot, make_float4(p.ax, p.ay, __int_as_float(p.aid), 0.0f));
             gst(&a.pockets[j].len, m + 1);
         }
         wave_sync();
@@ -467,10 +476,11 @@ __global__ __launch_bounds__(kTaskT[C], 4) void k_batch_chain(BatchArgs a)
     for (int i = (int)blockIdx.x; i < nt; i += (int)gridDim.x) {
         const int j = a.todo[C][i];
         const Pocket p = gld(a.pockets + j);
-        float* slot = a.slots + 3 * (size_t)p.off;
+        float4* slot = a.slots + p.off;
         for (int r = t; r < p.len; r += T) {
-            L.xy[r] = make_float2(gld(slot + 3 * r), gld(slot + 3 * r + 1));
-            L.id[r] = __float_as_int(gld(slot + 3 * r + 2));
+            const float4 v = gld(slot + r);
+            L.xy[r] = make_float2(v.x, v.y);
+            L.id[r] = __float_as_int(v.z);
         }
         if (t == 0) {
             L.xy[p.len] = make_float2(p.ax, p.ay);
@@ -490,7 +500,7 @@ __global__ __launch_bounds__(kTaskT[C], 4) void k_batch_chain(BatchArgs a)
 // The rings: the pockets' nodes as one list, a workgroup per set, and the
 // removal rounds over it until every node is strictly convex; then the hull
 // from its lexicographic minimum.
-constexpr int kRingT = 512, kRingRows = 32;
+constexpr int kRingT = 512;
 __global__ __launch_bounds__(kRingT) void k_batch_ring(BatchArgs a)
 {
     constexpr int W = kRingT / 64;
@@ -526,87 +536,32 @@ __global__ __launch_bounds__(kRingT) void k_batch_ring(BatchArgs a)
         }
         __syncthreads();
         int m = s_at[K];
-        // two buffers of this set's slots: the list goes from one to the other
-        float* buf[2] = {a.slots2 + 3 * (size_t)base, a.slots + 3 * (size_t)base};
+        // two lists of this set's slots: the nodes go from one to the other
+        const NodesGlobal list = {{a.slots2 + base, a.slots + base}};
         for (int k = w; k < K; k += W) {
-            const float* src = a.slots + 3 * (size_t)s_off[k];
+            const float4* src = a.slots + s_off[k];
             const int q0 = s_at[k], len = s_at[k + 1] - q0;
-            for (int e = lane; e < 3 * len; e += 64) gst(buf[0] + 3 * q0 + e, gld(src + e));
+            for (int e = lane; e < len; e += 64) list.put(0, q0 + e, gld(src + e));
         }
         __syncthreads();
-        int f = 0;
-        for (;;) {
-            // each wave takes a contiguous run of whole rows, kRingRows at a time
-            const float* src = buf[f];
-            float* dst = buf[f ^ 1];
-            int out = 0;  // nodes kept before the block of rows
-            for (int q0 = 0; q0 < m; q0 += kRingT * kRingRows) {
-                const int mb = min(m - q0, kRingT * kRingRows);
-                const int per = (((mb + W - 1) / W) + 63) & ~63;
-                const int wb = q0 + min(w * per, mb), we = q0 + min(w * per + per, mb);
-                uint32_t keep = 0u;
-                int cnt = 0;
-                for (int r = 0; wb + 64 * r < we; ++r) {
-                    const int q = wb + 64 * r + lane;
-                    bool kp = false;
-                    if (q < we) {
-                        const float* p = src + 3 * (size_t)q;
-                        const float* o = src + 3 * (size_t)(q > 0 ? q - 1 : m - 1);
-                        const float* e = src + 3 * (size_t)(q + 1 < m ? q + 1 : 0);
-                        kp = orient_of(make_float2(gld(o), gld(o + 1)), make_float2(gld(p), gld(p + 1)),
-                                       make_float2(gld(e), gld(e + 1)), ctr) > 0;
-                    }
-                    keep |= (uint32_t)kp << r;
-                    cnt += (int)__popcll(__ballot(kp));
-                }
-                __syncthreads();
-                if (lane == 0) red[w] = cnt;
-                __syncthreads();
-                int at = out;
-#pragma unroll
-                for (int u = 0; u < W; ++u) {
-                    at += u < w ? red[u] : 0;
-                    out += red[u];
-                }
-                for (int r = 0; wb + 64 * r < we; ++r) {
-                    const int q = wb + 64 * r + lane;
-                    const bool kp = (keep >> r) & 1u;
-                    const uint64_t M = __ballot(kp);
-                    if (kp) {
-                        float* d = dst + 3 * (size_t)(at + bits_below(M));
-                        const float* p = src + 3 * (size_t)q;
-                        gst(d, gld(p));
-                        gst(d + 1, gld(p + 1));
-                        gst(d + 2, gld(p + 2));
-                    }
-                    at += (int)__popcll(M);
-                }
-            }
-            __syncthreads();
-            f ^= 1;
-            if (out == m) break;  // (uniform)
-            m = out;
-        }
-        const float* src = buf[f];
+        int f;
+        m = ring_rounds<kRingT, true>(list, m, f, red, ctr);
         uint64_t lo = ~0ull;
-        auto key = [&](int q) {
-            return ((uint64_t)order_key(gld(src + 3 * (size_t)q) + 0.0f) << 32) | order_key(gld(src + 3 * (size_t)q + 1) + 0.0f);
-        };
         for (int q = t; q < m; q += kRingT) {
-            const uint64_t v = key(q);
+            const uint64_t v = lex_key(list.get(f, q));
             lo = v < lo ? v : lo;
         }
         lo = wave_min_u64(lo);
         if (lane == 63) atomicMin(&s_min, (unsigned long long)lo);
         __syncthreads();
         for (int q = t; q < m; q += kRingT)
-            if (key(q) == s_min) s_start = q;  // (one node: the ring's positions differ)
+            if (lex_key(list.get(f, q)) == s_min) s_start = q;  // (one node: the ring's positions differ)
         __syncthreads();
         const int st = s_start;
         int* out = a.hbuf + (a.hpos ? gld(a.hpos + ds.set) : base);
         for (int q = t; q < m; q += kRingT) {
             const int r = q >= st ? q - st : q - st + m;
-            gst(out + r, __float_as_int(gld(src + 3 * (size_t)q + 2)));
+            gst(out + r, __float_as_int(list.get(f, q).z));
         }
         if (t == 0) a.hcnt[ds.set] = m;
         __syncthreads();
@@ -705,7 +660,7 @@ hipError_t launch_batch(const BatchArgs& a, int cus, hipStream_t st)
     k_batch_init<<<1, 1024, 0, st>>>(a);
     if (a.N > kSmallP) k_batch_big<<<std::min(a.G, cus), kMidT, 0, st>>>(a);
     k_batch_small<<<std::min(a.G, 4 * cus), kSmallT, 0, st>>>(a);
-    if (a.sieve && a.N > kLocalPoints) {
+    if (a.sieve && a.N > kLocalPoints) {  // (no smaller set is cut into pockets)
         k_batch_chain<2><<<cus, kTaskT[2], 0, st>>>(a);
         k_batch_chain<1><<<4 * cus, kTaskT[1], 0, st>>>(a);
         k_batch_pocket<<<6 * cus, 64 * kPocketWaves, 0, st>>>(a);

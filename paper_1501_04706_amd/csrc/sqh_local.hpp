@@ -107,6 +107,7 @@ hipError_t launch_ring(const RingArgs& a, int cus, hipStream_t st, LaunchMark ma
 // A batch of sets (at most kBatchSetMax points each; larger ones leave the
 // whole batch to the general path).
 constexpr int kBatchSetMax = 1 << 20;
+constexpr int kEngineSetMax = 1 << 18; // an engine's larger requests have launches of their own
 struct Pocket;
 struct DenseSet;
 struct BatchCtl;
@@ -124,8 +125,8 @@ struct BatchArgs {
     int* hcnt;         // G: hull sizes
     int* order;        // G: sets by size class
     int* hbuf;         // N: each set's hull from its first slot
-    float* slots;      // 3 N words: pocket points
-    float* slots2;     // 3 N words: ring nodes
+    float4* slots;     // N: pocket points
+    float4* slots2;    // N: ring nodes
     Pocket* pockets;   // pocket records ...
     int* todo[3];      // ... and their indices by solver size
     int pocket_cap;
@@ -135,7 +136,7 @@ struct BatchArgs {
     // an engine's requests (null for a batch): offsets in place of set_off,
     // where each hull goes in hbuf, a flag for each set with a non-finite
     // coordinate, and the host's copies of sizes and flags. Sets of more than
-    // kBatchSetMax points are left out.
+    // kEngineSetMax points are left out.
     const int *off32, *hpos_src;
     int *hpos, *bad, *h_host, *bad_host;
 };

@@ -30,9 +30,7 @@
 namespace sqh {
 
 constexpr int kRays = 512;
-constexpr int kRingBins = 4096;     // bins of the angle
 constexpr int kRingSample = 8192;
-constexpr float kRingNear = 0x1p-10f;  // (a share of a bin)
 constexpr int kSubRays = 512;       // pockets of a wedge, at most
 constexpr int kSubBins = 1024;
 constexpr int kPocketTarget = 100;
@@ -66,21 +64,6 @@ struct RingCtl {
 
 __device__ __forceinline__ bool gate_shut(const RingArgs& a) { return a.gate && *a.gate != 1; }
 
-// The bin of a direction: 1024 to a quadrant, by the share of |y| in |x| + |y|
-// (turning counter-clockwise). near: closer to a bin's border than the rounding
-// of x, y (scaled by the extents) and of this may have moved it, or the border:
-// together less than half of kRingNear where the centre is within 64 extents of 0.
-__device__ __forceinline__ int ring_bin(float x, float y, bool& near)
-{
-    constexpr int Q = kRingBins / 4;
-    const float a = fabsf(x), b = fabsf(y), s = a + b;
-    const bool l = x < 0.0f, d = y < 0.0f;
-    const float f = (l == d ? b : a) * __builtin_amdgcn_rcpf(s) * (float)Q;
-    const int j = min(max((int)f, 0), Q - 1);
-    const float r = f - (float)j;
-    near = !((int)(r >= kRingNear) & (int)(r <= 1.0f - kRingNear) & (int)(s > 0x1p-100f));
-    return (d ? (l ? 2 : 3) : (l ? 1 : 0)) * Q + j;
-}
 __device__ __forceinline__ float2 ring_dir(int b)  // a bin's start
 {
     constexpr int Q = kRingBins / 4;
