@@ -76,7 +76,13 @@ typedef struct sqh_ctx sqh_ctx;
  * ms_total and ms_kernel come from HIP events recorded on the call's stream;
  * the phase times are differences of the device's constant 100 MHz clock read
  * by workgroup 0 at the end of each phase of the persistent kernel (each
- * phase ends at a grid-wide barrier, so they partition ms_kernel). */
+ * phase ends at a grid-wide barrier, so they partition ms_kernel).
+ * A call that the workgroup-local kernels finish (small sets, sets past the
+ * sieve, rings, batches) has no such phases: ms_seed .. ms_emit and pass_ms
+ * are 0, ms_total and ms_kernel are from the first kernel's start to the last
+ * one's end by that clock, first_survivors counts the points the sieve left
+ * (those of a small set that entered its first pass, all points of a ring),
+ * and the passes are those of the last solve. */
 typedef struct sqh_stats {
     int64_t passes;           /* segmented passes after the first compaction */
     int64_t points;           /* input points */
@@ -99,9 +105,9 @@ typedef struct sqh_stats {
     double  ms_sort;          /* sorted-chain variant: the sort of the first segments */
     int64_t sorted_points;    /* sorted-chain variant: points sorted; -1: no sort ran */
     int64_t sort_violations;  /* sorted-chain variant: neighbours found out of order after the sort (0) */
-    int64_t stream_path;      /* 0: general path; 1: the streaming kernels finished the hull;
-                                 2: ... and the passes kernel took over (more than 256 segments) */
-    int64_t line_filter;      /* 1: the streaming path used the static line filter */
+    int64_t stream_path;      /* 0: no streaming path; 1: the sieve or the streaming kernels finished the hull;
+                                 2: a ring (the ring kernels, or the passes kernel took over) */
+    int64_t line_filter;      /* 1: the sieve or the streaming path used the static line filter */
 } sqh_stats;
 
 /*
@@ -131,10 +137,12 @@ int sqh_set_precision(sqh_ctx *ctx, int mode);
 /*
  * Streaming path on (on != 0, the default) or off. On, a call on one set of
  * at least 2^16 points (no pre-filter, partition variant, 16-byte aligned
- * input) runs its first phases and passes over few large segments as
- * ordinary launches that never wait for one another, and the cooperative
- * passes kernel only for what they leave. The output is identical either
- * way. Returns SQH_OK or SQH_EINVAL.
+ * input) reads its input once past a sieve, or, if it is a ring of points,
+ * cuts it into wedges; what neither takes runs its first phases and passes
+ * over few large segments as ordinary launches that never wait for one
+ * another, and the cooperative passes kernel for what they leave. Off, and
+ * in graphs, such a set runs on the general path. The output is identical
+ * either way. Returns SQH_OK or SQH_EINVAL.
  */
 int sqh_set_streaming(sqh_ctx *ctx, int on);
 
@@ -335,6 +343,10 @@ void sqh_graph_destroy(sqh_graph *graph);
  *   - emits the hulls of the requests left without segments (same result
  *     convention as sqh_hull, indices local to the request) and frees their
  *     slots.
+ * A step of 16 passes or more (default precision, nothing resident) finishes
+ * all of its requests on the workgroup-local kernels instead, large ones one
+ * after another; if they leave one, the whole step runs on the segment table
+ * before sqh_engine_finish returns.
  * An engine is used by one host thread. Admissions may use their own stream
  * (a copy stream) and overlap a launched step.
  */

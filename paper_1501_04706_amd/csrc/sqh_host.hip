@@ -719,7 +719,7 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
     }
     // several sets: each on a workgroup of its own (4096 sets of 64M points:
     // 15.9 ms on the persistent kernel, whose every pass streams all sets'
-    // points between two grid barriers, and 1.74 ms so). One large set in a
+    // points between two grid barriers, and 1.60 ms so). One large set in a
     // batch stays with the streaming path.
     if (plain && N > 0 && ((d_set_off && (nsets > 1 || N < kStreamMin)) || ring)) {
         BatchArgs b{};
@@ -1689,8 +1689,8 @@ int sqh_engine_launch(sqh_engine* e, int max_passes, void* stream)
     if (e->admitted) HIP_OK(hipStreamWaitEvent(st, e->ev_admit, 0));  // staged points have arrived
     e->admitted = false;
     // A step of many passes finishes its requests anyway: without residents it
-    // runs on the local kernels (a serving step of 16M points: 4 ms on the
-    // segment table and 1 ms so). Fewer passes ask for short steps in which
+    // runs on the local kernels (a serving step of 13M points: 4 ms on the
+    // segment table and 1.6 ms so). Fewer passes ask for short steps in which
     // old and new requests share the table.
     e->max_passes = max_passes;
     e->local = max_passes >= kLocalStepPasses && G > 0 && e->resident.empty() && c->line && !c->fp64;

@@ -12,6 +12,13 @@
 //              section 4); many points left: kLocalPoints to a workgroup first
 // Sets that leave few points take k_sieve_solve for the last two.
 // A set that keeps many points (a ring) is left to other paths.
+//
+// Bound by the read: k_sieve streams 20M points of a square in 34 us (4.7 TB/s;
+// a plain copy reaches 5.1), of a disk in 42 us (more points past the slabs).
+// The other kernels are latency: k_extreme 9 us, k_polygon 14, k_rest 37 (square)
+// to 64 us (disk), about a third of it the last workgroup's passes. Before, seed,
+// split, first compaction and passes took 375 and 560 us a call, now 110 and 149.
+// k_sieve_solve takes 32 us for 20K points, 45 for 1M.
 #pragma once
 #include "sqh_sieve.hpp"
 #include "sqh_dense.hpp"

@@ -6,14 +6,17 @@
 // their indices. Both are bound by the reads (8 bytes a point each; the second
 // writes 12 bytes a kept point). As one cooperative kernel with a workgroup to
 // a compute unit and two grid barriers this took 81 us for 5M points of a
-// disk, and the general kernel after it 584 us on the 498K kept.
+// disk, and the general kernel after it 584 us on the 498K kept; these take 14
+// and 32 us (42 with twice the workgroups of half the threads: the second waits
+// on its reservations, one for 16K points now), and the sieve 82 us for the
+// subset.
 #pragma once
 #include "sqh_prefilter.hpp"
 #include "sqh_solve.hpp"
 
 namespace sqh {
 
-constexpr int kPreT = 512, kPreGrid = 512;
+constexpr int kPreT = 1024, kPreGrid = 256;
 struct PreCtl {
     int keep, pad;
     unsigned int done, pad2;
