@@ -55,7 +55,13 @@ def call_bytes(st: dict, n: int) -> int:
     pass   reads each point entering the pass (12 B) and writes each point
            kept for the next pass (12 B)
     Segment tables, counters and the output are O(h + segments) and left out.
+
+    A call that the workgroup-local kernels finished (one_read) reads the
+    input once past the sieve and writes and reads the points left, whose
+    passes run in LDS: 8 B/pt and 24 B per point left.
     """
+    if one_read(st):
+        return sum(launch_bytes(launch_sequence(st, 0), st, n))
     pts = list(st["pass_points"])[: int(st["passes"])]
     pass_bytes = 0
     for k, v in enumerate(pts):
@@ -64,10 +70,33 @@ def call_bytes(st: dict, n: int) -> int:
     return 8 * n + 8 * n + 8 * n + 12 * int(st["first_survivors"]) + pass_bytes
 
 
+RING_KERNELS = ["k_ring_rays", "k_ring_count", "k_ring_scan", "k_ring_scatter", "k_ring_cut", "k_ring_pocket",
+                "k_ring_wedge", "k_ring_join", "k_ring_emit"]
+# bytes per point: the wedge numbers are 2 B, a slot 16 B (the kernels not
+# listed read and write the few nodes left)
+RING_BYTES = {"k_ring_count": 8 + 2, "k_ring_scatter": 8 + 2 + 16, "k_ring_cut": 16 + 2 + 16 + 2 + 16,
+              "k_ring_pocket": 16}
+
+
+def one_read(st: dict) -> bool:
+    """Whether the workgroup-local kernels finished the call (they time no
+    phase of the general path)."""
+    return "ms_first" in st and float(st["ms_first"]) == 0.0 and float(st.get("ms_total", 0.0)) > 0.0
+
+
 def launch_sequence(st: dict, n_spass: int) -> list:
-    """The launches of a plain sqh_hull call, as (name, 0.0) pairs: the
-    streaming path (with n_spass k_spass launches; the passes kernel when the
-    call needed it) or the general path's one hull kernel."""
+    """The launches of a plain sqh_hull call, as (name, 0.0) pairs: one
+    workgroup's kernel, the sieve's (and the ring kernels'), the streaming
+    path (with n_spass k_spass launches; the passes kernel when the call
+    needed it) or the general path's one hull kernel."""
+    n = int(st.get("points", 0))
+    if one_read(st):
+        if n <= 4096:
+            return [("k_local_one", 0.0)]
+        names = (["k_extreme"] if n > 100_000 else []) + ["k_polygon"] + \
+                (["k_sieve_solve"] if n <= 1_500_000 else ["k_sieve", "k_rest"]) + \
+                (RING_KERNELS if int(st["stream_path"]) == 2 else [])
+        return [(x, 0.0) for x in names]
     if int(st.get("stream_path", 0)) == 0:
         names = ["k_reset", "k_hull<plain>"]
     else:
@@ -94,7 +123,17 @@ def launch_bytes(launches: list, st: dict, n: int) -> list:
     out, k_spass, spass_ran = [], 0, 0
     for name, _ in launches:
         b = 0
-        if name == "k_hull<plain>":
+        if name == "k_local_one":
+            b = 8 * n
+        elif name in ("k_sieve", "k_sieve_solve"):
+            # (a ring is found by the sample: the sieve reads nothing)
+            ring = int(st["stream_path"]) == 2
+            b = 0 if ring else 8 * n + (12 if name == "k_sieve" else 24) * int(st["first_survivors"])
+        elif name == "k_rest":
+            b = 0 if int(st["stream_path"]) == 2 else 12 * int(st["first_survivors"])
+        elif name in RING_BYTES:
+            b = RING_BYTES[name] * n
+        elif name == "k_hull<plain>":
             b = call_bytes(st, n)
         elif name in ("k_sseed", "k_ssplit"):
             b = 8 * n
