@@ -45,7 +45,7 @@ constexpr float kRingNear = 0x1p-10f;  // (a share of a bin)
 // The bin of a direction: 1024 to a quadrant, by the share of |y| in |x| + |y|
 // (turning counter-clockwise). near: closer to a bin's border than the rounding
 // of x, y (scaled by the extents) and of this may have moved it, or the border:
-// together less than half of kRingNear where the centre is within 64 extents of 0.
+// together less than half of kRingNear where the centre is within 1024 extents of 0.
 __device__ __forceinline__ int ring_bin(float x, float y, bool& near)
 {
     constexpr int Q = kRingBins / 4;

@@ -667,7 +667,7 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
     if (whole && !a.prefilter && sieve && (N < kStreamMin || a.stream)) {
         ctx->nl = 0;
         HIP_OK(run_sieve(ctx, a, a.xy, nullptr, (int)N, d_out, out_cap, st));
-        const bool by_ring = ctx->lstat->left != 0;
+        const bool by_ring = ctx->lstat->left == 1;
         if (by_ring) {
             // (5M points of a circle: 1530 us on the streaming path, 440 us so;
             // 30000: 350 us with one workgroup cutting the ring, as a batch's)
@@ -704,7 +704,7 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
             HIP_OK(run_local(ctx, a, a.xy2, a.ids2, n2, d_out, out_cap, st));
         } else {
             HIP_OK(run_sieve(ctx, a, a.xy2, a.ids2, n2, d_out, out_cap, st));
-            if (ctx->lstat->left) HIP_OK(run_ring(ctx, a, a.xy2, a.ids2, n2, d_out, out_cap, st));
+            if (ctx->lstat->left == 1) HIP_OK(run_ring(ctx, a, a.xy2, a.ids2, n2, d_out, out_cap, st));
         }
         if (!ctx->lstat->left) {
             rc = collect_local(ctx, N, out_cap, h_total);

@@ -549,7 +549,7 @@ __global__ __launch_bounds__(kRingT) void k_batch_ring(BatchArgs a)
         }
         __syncthreads();
         int f;
-        m = ring_rounds<kRingT, true>(list, m, f, red, ctr);
+        m = ring_rounds<kRingT, true>(list, m, make_float2(ds.cx, ds.cy), f, red, ctr);
         uint64_t lo = ~0ull;
         for (int q = t; q < m; q += kRingT) {
             const uint64_t v = lex_key(list.get(f, q));

@@ -12,7 +12,8 @@ constexpr int kLocalStatPasses = 64;  // passes whose sizes are noted
 struct LocalStatus {
     int h;      // hull vertices (all sets)
     int err;    // kErr* flags
-    int left;   // 1: nothing was written, the general path has to run; 2: launch_rest has to
+    int left;   // nothing was written: 1: the ring kernels or the general path have to run; 2: launch_rest
+                // has to; 3: the general path has to
     int passes;
     int first_v;
     int line;   // the sieve's edges took the static line filter
@@ -59,7 +60,7 @@ struct SieveArgs {
     int* lcnt;         // n / 64 or more: their sizes
     SieveCtl* ctl;
     // one of an engine's requests (else null): its hull size and bad flag, and
-    // what follows (0: nothing, 1: the ring kernels, 2: k_rest)
+    // what follows (as LocalStatus::left)
     int *h_dev, *bad_dev, *gate;
 };
 size_t sieve_ctl_bytes();

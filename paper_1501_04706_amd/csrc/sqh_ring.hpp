@@ -31,6 +31,7 @@ namespace sqh {
 
 constexpr int kRays = 512;
 constexpr int kRingSample = 8192;
+constexpr float kRayFar = 1024.0f;  // a ray's point, in extents from the centre
 constexpr int kSubRays = 512;       // pockets of a wedge, at most
 constexpr int kSubBins = 1024;
 constexpr int kPocketTarget = 100;
@@ -103,6 +104,13 @@ __global__ __launch_bounds__(1024) void k_ring_rays(RingArgs a)
     if (gate_shut(a)) return;
     const int t = (int)threadIdx.x, lane = lane_id(), n = a.n;
     constexpr int U = kRingSample / 1024;
+    // the centre: of three vertices of the sieve's polygon (its control block
+    // is where this one goes), inside the hull also where the box's is not
+    const SieveCtl* sieve = reinterpret_cast<const SieveCtl*>(ctl);
+    const int ph = sieve->h;
+    const bool poly = ph >= 3;
+    const float2 pa = sieve->ring[0], pb = sieve->ring[poly ? ph / 3 : 0], pc = sieve->ring[poly ? 2 * ph / 3 : 0];
+    __syncthreads();
     if (t == 0) {
         ctl->t0 = wall_clock64();
         ctl->left = 0; ctl->err = 0; ctl->n_pocket = 0;
@@ -135,10 +143,12 @@ __global__ __launch_bounds__(1024) void k_ring_rays(RingArgs a)
     __syncthreads();
     auto back = [](uint32_t v) { return __uint_as_float((v & 0x80000000u) ? v ^ 0x80000000u : ~v); };
     const double xl = back(lo[0]), xh = back(hi[0]), yl = back(lo[1]), yh = back(hi[1]);
-    const float2 c = make_float2((float)(0.5 * (xl + xh)), (float)(0.5 * (yl + yh)));
+    const float2 c = poly ? make_float2((float)(((double)pa.x + (double)pb.x + (double)pc.x) / 3.0),
+                                        (float)(((double)pa.y + (double)pb.y + (double)pc.y) / 3.0))
+                          : make_float2((float)(0.5 * (xl + xh)), (float)(0.5 * (yl + yh)));
     const float ex = (float)(0.5 * (xh - xl)), ey = (float)(0.5 * (yh - yl));
     const bool ok = ex > 0x1p-50f && ex < 0x1p50f && ey > 0x1p-50f && ey < 0x1p50f &&
-                    fabsf(c.x) <= 64.0f * ex && fabsf(c.y) <= 64.0f * ey;
+                    fabsf(c.x) <= kRayFar * ex && fabsf(c.y) <= kRayFar * ey;
     const float ix = ok ? 1.0f / ex : 0.0f, iy = ok ? 1.0f / ey : 0.0f;
 #pragma unroll
     for (int j = 0; j < U; ++j) {
@@ -180,7 +190,7 @@ __global__ __launch_bounds__(1024) void k_ring_rays(RingArgs a)
     if (t < nr) {
         // far out, where the rounding of the point turns the ray least
         const float2 d = ring_dir(bin[t]);
-        ray[t] = make_float2(c.x + 64.0f * ex * d.x, c.y + 64.0f * ey * d.y);
+        ray[t] = make_float2(c.x + kRayFar * ex * d.x, c.y + kRayFar * ey * d.y);
     }
     __syncthreads();
     if (t < nr) {
@@ -522,13 +532,24 @@ struct NodesLds {
 // The removal rounds over the m nodes of buf's first list, by a workgroup of T threads: as a
 // ring (RING), or as a chain whose two ends stay. Returns how many are left, in
 // list f. red: T / 64 words.
+// Where two arcs meet at a reflex node, a round takes two nodes: after 8 rounds
+// every other one tests a node against those m / 4, m / 8, .. places away (any
+// two nodes around it will do as long as they are less than half a turn apart),
+// which takes such a stretch at once (two circles of 1M points side by side:
+// 20 ms of rounds without).
 template <int T, bool RING, typename Buf>
-__device__ __forceinline__ int ring_rounds(const Buf& buf, int m, int& f, int* red, Counters& ctr)
+__device__ __forceinline__ int ring_rounds(const Buf& buf, int m, float2 c, int& f, int* red, Counters& ctr)
 {
     constexpr int W = T / 64, kRows = 32;
     const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
     f = 0;
-    for (;;) {
+    int far = 0;
+    for (int round = 0;; ++round) {
+        int step = 1;
+        if (round >= 8 && (round & 1)) {
+            far = min(far < 2 ? m : far >> 1, m >> 2);
+            step = max(far, 1);
+        }
         // each wave takes a contiguous run of whole rows, kRows at a time
         int out = 0;  // nodes kept before the block of rows
         for (int q0 = 0; q0 < m; q0 += T * kRows) {
@@ -541,9 +562,12 @@ __device__ __forceinline__ int ring_rounds(const Buf& buf, int m, int& f, int* r
                 const int q = wb + 64 * r + lane;
                 bool kp = false;
                 if (q < we) {
-                    const float4 p = buf.get(f, q), o = buf.get(f, q > 0 ? q - 1 : m - 1), e = buf.get(f, q + 1 < m ? q + 1 : 0);
-                    kp = (!RING && (q == 0 || q == m - 1)) ||
-                         orient_of(make_float2(o.x, o.y), make_float2(p.x, p.y), make_float2(e.x, e.y), ctr) > 0;
+                    const int qo = q - step, qe = q + step;
+                    const float4 p = buf.get(f, q), o = buf.get(f, qo >= 0 ? qo : (RING ? qo + m : 0)),
+                                 e = buf.get(f, qe < m ? qe : (RING ? qe - m : m - 1));
+                    const float2 op = make_float2(o.x, o.y), ep = make_float2(e.x, e.y);
+                    kp = (!RING && (q == 0 || q == m - 1)) || orient_of(op, make_float2(p.x, p.y), ep, ctr) > 0 ||
+                         (RING && step > 1 && orient_of(c, op, ep, ctr) <= 0);
                 }
                 keep |= (uint32_t)kp << r;
                 cnt += (int)__popcll(__ballot(kp));
@@ -566,7 +590,7 @@ __device__ __forceinline__ int ring_rounds(const Buf& buf, int m, int& f, int* r
         }
         __syncthreads();
         f ^= 1;
-        if (out == m) return m;  // (uniform)
+        if (out == m && step == 1) return m;  // (uniform)
         m = out;
     }
 }
@@ -620,7 +644,7 @@ __global__ __launch_bounds__(kWedgeT) void k_ring_wedge(RingArgs a)
         }
         __syncthreads();
         int f;
-        m = ring_rounds<kWedgeT, false>(list, m, f, red, ctr);
+        m = ring_rounds<kWedgeT, false>(list, m, ctl->c, f, red, ctr);
         // back to `slots`; its lexicographic minimum
         for (int i = t; i < m; i += kWedgeT) {
             const float4 p = list.get(f, i);
@@ -764,7 +788,7 @@ __global__ __launch_bounds__(1024) void k_ring_join(RingArgs a)
         __syncthreads();
         const NodesGlobal list = {{a.slots2, a.slots}};
         int f;
-        h = ring_rounds<1024, true>(list, h, f, red, ctr);
+        h = ring_rounds<1024, true>(list, h, c, f, red, ctr);
         buf = f ^ 1;
         for (int j = t; j < h; j += 1024)
             if (lex_key(list.get(f, j)) == s_min) s_start = j;  // (one node: the ring's positions differ)

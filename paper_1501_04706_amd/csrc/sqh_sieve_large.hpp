@@ -343,7 +343,9 @@ __global__ __launch_bounds__(1024) void k_polygon(SieveArgs a, int ne)
         ctl->Mx = s_m[0];
         ctl->My = s_m[1];
         ctl->slabs = sl;
-        if (h >= 3 && s_keep > 256) ctl->left = 1;
+        // (three quarters of a ring or an arc are kept, and the ring kernels take
+        // it; between the two the general path is the better guess)
+        if (h >= 3 && s_keep > 256) ctl->left = s_keep > 768 ? 1 : 3;
     }
 }
 static_assert(kSlabs == 1024, "a thread of k_polygon per slab");
@@ -460,7 +462,8 @@ __device__ __forceinline__ void rest_finish(const SieveArgs& a, SolveLds<P>& L, 
     if (t == 0) {
         s->h = hh;
         s->err = err;
-        s->left = (!err && left) ? 1 : 0;
+        const int code = (!err && left) ? (ctl->left ? ctl->left : 1) : 0;
+        s->left = code;
         s->passes = st.passes;
         s->first_v = M;
         s->line = ctl->line;
@@ -473,7 +476,7 @@ __device__ __forceinline__ void rest_finish(const SieveArgs& a, SolveLds<P>& L, 
         if (a.gate) {
             *a.h_dev = hh;
             *a.bad_dev = err != 0;
-            *a.gate = (!err && left) ? 1 : 0;
+            *a.gate = code;
         }
     }
 }
@@ -678,9 +681,9 @@ __global__ __launch_bounds__(kMidT) void k_sieve_solve(SieveArgs a, int per)
     SieveCtl* ctl = a.ctl;
     if (ctl->left) {
         if (blockIdx.x == 0 && t == 0) {
-            a.status->left = 1;
+            a.status->left = ctl->left;
             a.status->err = 0;
-            if (a.gate) *a.gate = 1;
+            if (a.gate) *a.gate = ctl->left;
         }
         return;
     }

@@ -142,6 +142,9 @@ def rings(n):
     yield "uneven", np.stack([np.cos(t), np.sin(t)], 1).astype(np.float32)
     x = rng.permutation(n) - n // 2
     yield "parabola", np.stack([x, x.astype(np.float64) ** 2 / n], 1).astype(np.float32)
+    two = np.concatenate([c[: n // 2], c[n // 2:] + np.float32([5.0, 1.0])])  # arcs that meet at reflex nodes
+    yield "two circles", two[rng.permutation(n)]
+    yield "most of two circles", np.concatenate([c[: n - n // 8], (c[n - n // 8:] * np.float32(0.5) + np.float32([1.2, 0.0]))])
 
 
 @pytest.mark.parametrize("n", [4097, 6001, 40_000, 65535])
@@ -217,7 +220,7 @@ def test_batches(H, n):
     each size class, rings in pockets, sieved sets."""
     import torch
     print(f"[case] batch of sets of about {n}", file=sys.stderr, flush=True)
-    parts = [np.zeros((0, 2), np.float32)] + [xy for _, xy in rings(n)][:8 if n < 500_000 else 2]
+    parts = [np.zeros((0, 2), np.float32)] + [xy for _, xy in rings(n)][:10 if n < 500_000 else 2]
     parts += [workloads.make(k, m, 3) for k in ("square", "disk", "grid") for m in (n, max(1, n // 7))]
     parts += [workloads.circle(m, 4) for m in (1, 2, 3, 65)] + [np.zeros((0, 2), np.float32)]
     off = np.zeros(len(parts) + 1, np.int64)
