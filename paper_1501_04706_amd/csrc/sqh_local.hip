@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kSmallT, 4) void k_batch_small(BatchArgs a)
     __shared__ SolveLds<kSmallP> L;
     __shared__ BatchAcc A;
     const BatchCtl* ctl = a.ctl;
-    if (ctl->err | ctl->left) return;
+    if (call_ended(&ctl->err, &ctl->left)) return;
     Counters ctr = {0u, 0u, 0u};
     acc_init(A);
     const int ns = ctl->n_small, nb = ctl->n_big;
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(kMidT) void k_batch_big(BatchArgs a)
     __shared__ BatchAcc A;
     __shared__ int s_i;
     BatchCtl* ctl = a.ctl;
-    if (ctl->err | ctl->left) return;
+    if (call_ended(&ctl->err, &ctl->left)) return;
     Counters ctr = {0u, 0u, 0u};
     acc_init(A);
     const int nb = ctl->n_big;

@@ -385,7 +385,7 @@ __global__ __launch_bounds__(1024) void k_ring_cut(RingArgs a)
     RingCtl* ctl = a.ctl;
     if (gate_shut(a)) return;
     const int t = (int)threadIdx.x, w = (int)blockIdx.x;
-    if ((ctl->left | ctl->err) || w >= ctl->nr) return;
+    if (call_ended(&ctl->err, &ctl->left) || w >= ctl->nr) return;
     const int off = ctl->wedge[w].off, len = ctl->wedge[w].len;
     const float2 c = ctl->c, A = gld(ctl->ray + w), B = gld(ctl->ray + w + 1);
     const int want = min(max(len / kPocketTarget, 1), kSubRays);
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(64 * kRingWaves) void k_ring_pocket(RingArgs a)
     __shared__ uint32_t csum[3];
     RingCtl* ctl = a.ctl;
     if (gate_shut(a)) return;
-    if (ctl->left | ctl->err) return;
+    if (call_ended(&ctl->err, &ctl->left)) return;
     const int lane = lane_id(), w = (int)(threadIdx.x >> 6), np = ctl->n_pocket;
     const float2 c = ctl->c;
     WaveLds& W = Ws[w];

@@ -95,6 +95,21 @@ __device__ __forceinline__ int bits_below(uint64_t M)
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(M >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)M, 0u));
 }
 
+// Whether an earlier kernel of the call ended it (err | left), alike on every
+// wave of the workgroup: one thread reads the words, because a kernel whose
+// workgroups also set them may have set them between two waves' own reads, and
+// a workgroup that goes on without some of its waves works on LDS they never
+// wrote. Every thread calls it; it holds a barrier.
+__device__ __forceinline__ bool call_ended(const int* err, const int* left)
+{
+    __shared__ int s_ended;
+    if (threadIdx.x == 0)
+        s_ended = __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) |
+                  __hip_atomic_load(left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return s_ended != 0;
+}
+
 // Exact order of two distinct candidates for the edge o -> e (section 4.4.1;
 // ties: the point earliest along the edge, then the lower index).
 __device__ __forceinline__ bool farther_exact(float2 o, float2 e, float2 p, int pid, float2 q, int qid)

@@ -1,0 +1,59 @@
+"""GPU tests of calls that the fast paths take only in part: batches with a set
+that ends the call, sets that no polygon thins, sets that are refused. Hull
+index lists are integer results: the bar is equality."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1501_04706_amd import sqh, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import torch
+    assert torch.cuda.is_available(), "gpu tests need a HIP device"
+    h = sqh.Hull(0)
+    yield h
+    h.close()
+
+
+def say(msg):
+    print(f"[case] {msg}", file=sys.stderr, flush=True)
+
+
+def hull(xy):
+    return [int(v) for v in oracle.c_hull(xy)]
+
+
+def batch(H, parts):
+    import torch
+    off = np.zeros(len(parts) + 1, np.int64)
+    off[1:] = np.cumsum([len(p) for p in parts])
+    xy = np.concatenate(parts, 0).astype(np.float32)
+    out, out_off = H.hull_batched(torch.from_numpy(xy).cuda(), torch.from_numpy(off).cuda())
+    out, out_off = out.cpu().numpy(), out_off.cpu().numpy()
+    return [[int(v) for v in out[out_off[s]:out_off[s + 1]]] for s in range(len(parts))]
+
+
+@pytest.mark.parametrize("where", ["small", "big", "both"])
+def test_bad_sets_among_many(H, where):
+    # sets flagged while other workgroups of the same launch start or wait
+    say(f"bad sets among many: {where}")
+    rng = np.random.default_rng(3)
+    sizes = [int(v) for v in np.exp(rng.uniform(np.log(8), np.log(20_000), 1500))]
+    parts = [workloads.make(("square", "disk", "circle")[i % 3], n, i) for i, n in enumerate(sizes)]
+    good = [hull(p) for p in parts]
+    pick = [i for i, n in enumerate(sizes) if (n <= 1024 if where == "small" else n > 1024 if where == "big" else True)]
+    bad = list(parts)
+    for i in pick[::7]:
+        bad[i] = bad[i].copy()
+        bad[i][len(bad[i]) // 2, i % 2] = np.nan if i % 3 else np.inf
+    for _ in range(3):
+        with pytest.raises(sqh.SqhError) as e:
+            batch(H, bad)
+        assert e.value.code == sqh.SQH_EINVAL
+        assert batch(H, parts) == good
