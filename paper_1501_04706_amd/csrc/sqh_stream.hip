@@ -1770,6 +1770,14 @@ __device__ __forceinline__ unsigned okey(float f)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// Bounds of a point's area a +- w for the election of a leader. The area is
+// positive. Where the products overflow, a - w or both bounds are NaN, whose
+// sign no expression fixes (two evaluations of one difference came out with
+// different bits, so that no point held the largest lower bound): such a point
+// has the whole range.
+__device__ __forceinline__ float area_lo(float a, float w) { return fmaxf(a - w, 0.0f); }
+__device__ __forceinline__ float area_hi(float a, float w) { return fminf(a + w, INFINITY); }
+
 __device__ __forceinline__ int lseg_of(const LTail& L, int S, int i)
 {
     int lo = 0, hi = S - 1;
@@ -1876,7 +1884,7 @@ __device__ __forceinline__ bool lds_passes(const HullArgs& a, int cur, int pass,
                     pw[r] = 2.0f * (k == 0 ? o1.es : o2.es);
                     const int u = 2 * sg + k;
                     const int rank = atomicAdd(&L.cnt[u], 1);
-                    atomicMax(&L.key[u], okey(pa[r] - pw[r]));
+                    atomicMax(&L.key[u], okey(area_lo(pa[r], pw[r])));
                     pk[r] = (sg << 14) | (k << 13) | rank;
                 }
             }
@@ -1893,8 +1901,8 @@ __device__ __forceinline__ bool lds_passes(const HullArgs& a, int cur, int pass,
             if (pk[r] >= 0) {
                 const int u = pk[r] >> 13;
                 const unsigned kmax = L.key[u];
-                const unsigned lo = okey(pa[r] - pw[r]);
-                cand[r] = f64 || okey(pa[r] + pw[r]) >= kmax;
+                const unsigned lo = okey(area_lo(pa[r], pw[r]));
+                cand[r] = f64 || okey(area_hi(pa[r], pw[r])) >= kmax;
                 if (lo == kmax) atomicMin(&L.lead[u], t + kBlock * r);
             }
         }

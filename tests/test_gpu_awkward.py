@@ -57,3 +57,20 @@ def test_bad_sets_among_many(H, where):
             batch(H, bad)
         assert e.value.code == sqh.SQH_EINVAL
         assert batch(H, parts) == good
+
+
+@pytest.mark.parametrize("mode", [sqh.SQH_FP32_FILTER, sqh.SQH_FP32_SEMISTATIC, sqh.SQH_FP64_ONLY])
+@pytest.mark.parametrize("n,scale", [(70_001, 3e38), (300_000, 1e25), (1_500_000, 1e28)])
+def test_products_overflow(H, n, scale, mode):
+    # the area of nearly every point is no float32 number: bounds that are NaN
+    import torch
+    say(f"products overflow: n={n} scale={scale} mode={mode}")
+    H.set_precision(mode)
+    try:
+        for kind in ("square", "disk"):
+            xy = (workloads.make(kind, n, 5).astype(np.float64) * scale).astype(np.float32)
+            t = torch.from_numpy(xy).cuda()
+            for _ in range(2):  # (the second call enqueues as many passes as the first one took)
+                assert [int(v) for v in H.hull(t).cpu().numpy()] == hull(xy), kind
+    finally:
+        H.set_precision(sqh.SQH_FP32_FILTER)
