@@ -187,7 +187,7 @@ struct sqh_ctx {
     int spass_used[64];   // per size class: streaming passes the last call ran (-1: none yet)
     // per-launch timing (sqh_set_launch_timing): events before and after
     // each kernel of the last call, and the kernels' names
-    static constexpr int kMaxTimed = 24;
+    static constexpr int kMaxTimed = 32;  // (the sieve, the ring kernels and the streaming path in one call: 27)
     int ltiming = 0;
     char lonly[32] = {};  // time only the launches of this kernel ("": all)
     int nl = 0;
@@ -426,7 +426,6 @@ inline int time_close(sqh_ctx* ctx, const char* name, hipStream_t st)
 // Enqueue the workspace reset and the launches, bracketed by events.
 int enqueue(sqh_ctx* ctx, HullArgs& a, int reset_grid, int grid, int sgrid, hipStream_t st, bool fallback = true)
 {
-    ctx->nl = 0;
     HIP_OK(hipEventRecord(ctx->ev0, st));
     if (time_open(ctx, "k_reset", st) != SQH_OK) return SQH_EDEVICE;
     k_reset<<<reset_grid, 256, 0, st>>>(a);
@@ -640,6 +639,29 @@ hipError_t run_ring(sqh_ctx* ctx, const HullArgs& a, const float2* xy, const int
     return e != hipSuccess ? e : hipStreamSynchronize(st);
 }
 
+// Device time and counters of a call's local kernels that left the set to
+// another path; they belong to the call.
+struct Spent {
+    double ms = 0.0, ms_prefilter = 0.0;
+    uint64_t orient = 0, orient_exact = 0, cmp_exact = 0;
+    void add(const LocalStatus& L, uint64_t t0)
+    {
+        ms += (double)(L.t1 - t0) * 1e-5;
+        orient += L.orient;
+        orient_exact += L.orient_exact;
+        cmp_exact += L.cmp_exact;
+    }
+    void report(sqh_stats& S) const
+    {
+        S.ms_total += ms;
+        S.ms_kernel += ms;
+        S.ms_prefilter += ms_prefilter;
+        S.orient_evals += orient;
+        S.orient_exact += orient_exact;
+        S.cmp_exact += cmp_exact;
+    }
+};
+
 int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const int64_t* d_set_off, int32_t* d_out,
               int64_t* d_out_off, int64_t out_cap, int64_t* h_total, void* d_ws, size_t ws_bytes, hipStream_t st,
               const TuneEntry& tu)
@@ -648,6 +670,8 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
     int reset_grid = 1;
     int rc = setup(ctx, d_xy, N, nsets, d_set_off, d_out, d_out_off, out_cap, d_ws, ws_bytes, tu, a, reset_grid);
     if (rc != SQH_OK) return rc;
+    ctx->nl = 0;
+    Spent spent;
     const bool plain = !a.prefilter && !a.sorted && !ctx->trace;
     const bool sieve = a.line_ok && !a.fp64;  // static float32 certificates may be used
     // one set in plain mode. Up to kLocalPoints points: one workgroup, the
@@ -660,12 +684,10 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
     bool ring = false;
     const bool whole = nsets == 1 && !d_set_off && !a.sorted && !ctx->trace;
     if (whole && !a.prefilter && N <= kLocalPoints) {
-        ctx->nl = 0;
         HIP_OK(run_local(ctx, a, a.xy, nullptr, (int)N, d_out, out_cap, st));
         return collect_local(ctx, N, out_cap, h_total);
     }
     if (whole && !a.prefilter && sieve && (N < kStreamMin || a.stream)) {
-        ctx->nl = 0;
         HIP_OK(run_sieve(ctx, a, a.xy, nullptr, (int)N, d_out, out_cap, st));
         const bool by_ring = ctx->lstat->left == 1;
         if (by_ring) {
@@ -682,6 +704,7 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
             }
             return rc;
         }
+        spent.add(*ctx->lstat, ctx->lstat->t0);
     }
     // the pre-filter, then the same on its subset, of which the host has to
     // know the size (10 us; 5M points of a disk: 700 us by the cooperative
@@ -695,7 +718,6 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
         p.out_id = a.ids2;
         p.status = ctx->lstat;
         p.ctl = reinterpret_cast<PreCtl*>(a.slots);
-        ctx->nl = 0;
         HIP_OK(launch_pre(p, ctx->cus, st, launch_mark, ctx));
         HIP_OK(hipStreamSynchronize(st));
         const int n2 = ctx->lstat->pre_n;
@@ -716,6 +738,9 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
             S.ms_total = S.ms_kernel = (double)(L.t1 - L.pre_t0) * 1e-5;
             return rc;
         }
+        spent.add(*ctx->lstat, ctx->lstat->pre_t0);
+        spent.orient += ctx->lstat->pre_orient;
+        spent.ms_prefilter = (double)(ctx->lstat->pre_t1 - ctx->lstat->pre_t0) * 1e-5;
     }
     // several sets: each on a workgroup of its own (4096 sets of 64M points:
     // 15.9 ms on the persistent kernel, whose every pass streams all sets'
@@ -741,18 +766,24 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
         b.dense = reinterpret_cast<DenseSet*>(a.seg_cid[0]);
         b.dense_cap = (int)(N / 4096 + 1);
         b.ctl = reinterpret_cast<BatchCtl*>(a.slots);
-        ctx->nl = 0;
         if (time_open(ctx, "k_batch", st) != SQH_OK) return SQH_EDEVICE;
         HIP_OK(launch_batch(b, ctx->cus, st));
         HIP_OK(launch_batch_emit(b, ctx->cus, st));
         if (time_close(ctx, "k_batch", st) != SQH_OK) return SQH_EDEVICE;
         HIP_OK(hipStreamSynchronize(st));
-        if (!ctx->lstat->left) return collect_local(ctx, N, out_cap, h_total);
+        if (!ctx->lstat->left) {
+            rc = collect_local(ctx, N, out_cap, h_total);
+            spent.report(ctx->stats);
+            return rc;
+        }
+        spent.add(*ctx->lstat, ctx->lstat->t0);
     }
     if (!a.stream) {
         rc = enqueue(ctx, a, reset_grid, tu.grid, tu.sgrid, st);
         if (rc != SQH_OK) return rc;
-        return collect(ctx, a, N, out_cap, h_total, st, true);
+        rc = collect(ctx, a, N, out_cap, h_total, st, true);
+        spent.report(ctx->stats);
+        return rc;
     }
     // streaming path: the passes kernel only if the streaming kernels left work
     const int cls = std::min(log2_class(N), 63);
@@ -763,14 +794,19 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
     const HullInfo& hi = *ctx->hinfo;
     const bool done = hi.stream_done != 0 || *ctx->herr != 0;
     ctx->spass_used[cls] = hi.stream_done != 0 ? std::min(hi.spass_n, kStreamPassLaunches) : kStreamPassLaunches;
-    if (done) return rc;
+    if (done) {
+        spent.report(ctx->stats);
+        return rc;
+    }
     void* argv[] = {static_cast<void*>(&a)};
     if (time_open(ctx, "k_hull<passes>", st) != SQH_OK) return SQH_EDEVICE;
     HIP_OK(hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_hull<kHullPasses>), dim3(tu.grid),
                                       dim3(kBlock), argv, 0, st));
     if (time_close(ctx, "k_hull<passes>", st) != SQH_OK) return SQH_EDEVICE;
     HIP_OK(hipEventRecord(ctx->ev1, st));
-    return collect(ctx, a, N, out_cap, h_total, st, true);
+    rc = collect(ctx, a, N, out_cap, h_total, st, true);
+    spent.report(ctx->stats);
+    return rc;
 }
 
 int run(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const int64_t* d_set_off, int32_t* d_out,

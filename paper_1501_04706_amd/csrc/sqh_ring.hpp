@@ -110,14 +110,16 @@ __global__ __launch_bounds__(1024) void k_ring_rays(RingArgs a)
     const int ph = sieve->h;
     const bool poly = ph >= 3;
     const float2 pa = sieve->ring[0], pb = sieve->ring[poly ? ph / 3 : 0], pc = sieve->ring[poly ? 2 * ph / 3 : 0];
+    // (the call's clock and counters go on from the sieve's)
+    const unsigned long long t0 = sieve->t0, before = t < 3 ? ctr_total(sieve->ctr, t) : 0ull;
     __syncthreads();
     if (t == 0) {
-        ctl->t0 = wall_clock64();
+        ctl->t0 = t0;
         ctl->left = 0; ctl->err = 0; ctl->n_pocket = 0;
         ctl->turns = 0; ctl->bad = 0; ctl->ticket = 0;
         s_bad = 0;
     }
-    if (t < 3 * kCtrSlots) ctl->ctr[t / 3].c[t % 3] = 0ull;
+    if (t < 3 * kCtrSlots) ctl->ctr[t / 3].c[t % 3] = before;
     if (t < 2) { lo[t] = ~0u; hi[t] = 0u; }
     for (int b = t; b < kRingBins; b += 1024) hist[b] = 0;
     float2 p[U];
@@ -839,6 +841,11 @@ __global__ __launch_bounds__(kRingEmitT) void k_ring_emit(RingArgs a)
             st->h = 0;
             st->err = ctl->err;
             st->left = ctl->err ? 0 : 1;
+            st->orient = ctr_total(ctl->ctr, 0);
+            st->orient_exact = ctr_total(ctl->ctr, 1);
+            st->cmp_exact = ctr_total(ctl->ctr, 2);
+            st->t0 = ctl->t0;
+            st->t1 = wall_clock64();
             if (a.gate) {
                 *a.h_dev = 0;
                 *a.bad_dev = ctl->err != 0;
@@ -902,7 +909,7 @@ __global__ __launch_bounds__(kRingEmitT) void k_ring_emit(RingArgs a)
         st->line = a.line;
         st->orient = ctr_total(ctl->ctr, 0);
         st->orient_exact = ctr_total(ctl->ctr, 1);
-        st->cmp_exact = 0;
+        st->cmp_exact = ctr_total(ctl->ctr, 2);
         st->t0 = ctl->t0;
         st->t1 = wall_clock64();
     }

@@ -467,10 +467,13 @@ __device__ __forceinline__ void rest_finish(const SieveArgs& a, SolveLds<P>& L, 
         s->passes = st.passes;
         s->first_v = M;
         s->line = ctl->line;
-        // one side test per point of the sieve
-        s->orient = ctr_total(ctl->ctr, 0) + csum[0] + (unsigned long long)a.n;
-        s->orient_exact = ctr_total(ctl->ctr, 1) + csum[1];
-        s->cmp_exact = ctr_total(ctl->ctr, 2) + csum[2];
+        // one side test per point of the sieve (which did not run if k_polygon left the set)
+        const unsigned long long sum[3] = {csum[0] + (ctl->left ? 0ull : (unsigned long long)a.n), csum[1], csum[2]};
+        s->orient = ctr_total(ctl->ctr, 0) + sum[0];
+        s->orient_exact = ctr_total(ctl->ctr, 1) + sum[1];
+        s->cmp_exact = ctr_total(ctl->ctr, 2) + sum[2];
+        if (code)  // (the ring kernels go on from these)
+            for (int i = 0; i < 3; ++i) atomicAdd(&ctl->ctr[0].c[i], sum[i]);
         s->t0 = ctl->t0;
         s->t1 = wall_clock64();
         if (a.gate) {
@@ -681,8 +684,13 @@ __global__ __launch_bounds__(kMidT) void k_sieve_solve(SieveArgs a, int per)
     SieveCtl* ctl = a.ctl;
     if (ctl->left) {
         if (blockIdx.x == 0 && t == 0) {
-            a.status->left = ctl->left;
-            a.status->err = 0;
+            LocalStatus* s = a.status;
+            s->left = ctl->left;
+            s->err = 0;
+            s->line = ctl->line;
+            s->orient = s->orient_exact = s->cmp_exact = 0ull;
+            s->t0 = ctl->t0;
+            s->t1 = wall_clock64();
             if (a.gate) *a.gate = ctl->left;
         }
         return;
@@ -696,15 +704,16 @@ __global__ __launch_bounds__(kMidT) void k_sieve_solve(SieveArgs a, int per)
     static_assert(sizeof(L.seg) >= sizeof(int) * (kSieveGrid + 1), "the places fit");
     const int err = __hip_atomic_load(&ctl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int M = rest_places<kMidT>(ctl, nb, err != 0, pre);
-    int h = 0;
-    if (M > kMidP) h = -1;
-    else if (M > 0) h = rest_solve<kMidT, kMidP>(a, L, pre, nb, per, M, ctr, &st);
-    rest_finish<kMidT, kMidP>(a, L, h, M, st, ctr, csum);
-    if (t == 0 && M > kMidP) {
-        ctl->done = 0u;
-        a.status->left = 2;  // k_rest takes them
-        if (a.gate) *a.gate = 2;
+    if (M > kMidP) {  // (uniform) k_rest takes them
+        if (t == 0) {
+            ctl->done = 0u;
+            a.status->left = 2;
+            if (a.gate) *a.gate = 2;
+        }
+        return;
     }
+    const int h = M > 0 ? rest_solve<kMidT, kMidP>(a, L, pre, nb, per, M, ctr, &st) : 0;
+    rest_finish<kMidT, kMidP>(a, L, h, M, st, ctr, csum);
 }
 
 // The points left by ns sieve workgroups: at most kMidP of them solved by one

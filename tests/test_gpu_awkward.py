@@ -74,3 +74,34 @@ def test_products_overflow(H, n, scale, mode):
                 assert [int(v) for v in H.hull(t).cpu().numpy()] == hull(xy), kind
     finally:
         H.set_precision(sqh.SQH_FP32_FILTER)
+
+
+def timed_hull(H, xy):
+    """(hull, launches, stats) with per-launch timing on."""
+    import torch
+    t = torch.from_numpy(np.ascontiguousarray(xy, dtype=np.float32)).cuda()
+    H.set_launch_timing(True)
+    try:
+        H.hull(t)
+        got = [int(v) for v in H.hull(t).cpu().numpy()]
+        return got, H.launch_times(), H.stats()
+    finally:
+        H.set_launch_timing(False)
+
+
+@pytest.mark.parametrize("n", [6000, 70_000, 400_000])
+@pytest.mark.parametrize("kind", ["circle", "two thirds"])
+def test_times_cover_the_whole_call(H, kind, n):
+    # rings (the sieve's kernels, then the ring kernels), and a set that the
+    # sieve leaves to the general or the streaming path
+    say(f"times: {kind} n={n}")
+    xy = workloads.circle(n, 4)
+    if kind != "circle":
+        xy[::2] = workloads.disk(len(xy[::2]), 5) * np.float32(0.9)
+    got, launches, st = timed_hull(H, xy)
+    assert got == hull(xy)
+    names = [k for k, _ in launches]
+    assert "k_polygon" in names and len(set(names)) > 3, names
+    assert ("k_ring_emit" in names) == (kind == "circle"), names
+    # the events also see the gaps around a kernel: a tenth of room
+    assert st["ms_total"] >= 0.9 * sum(ms for _, ms in launches), (st["ms_total"], launches)
