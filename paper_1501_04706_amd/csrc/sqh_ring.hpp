@@ -13,10 +13,11 @@
 //                   neighbours are elsewhere)
 //   k_ring_wedge    a workgroup per wedge: the rounds over its pockets' nodes
 //   k_ring_join     the wedges joined at their seams into the hull
+//   k_ring_emit     its indices and the status
 // Every removed point lies in the triangle of c and two points of the set, so
 // it is no hull vertex as long as c is inside the hull, and what is left is a
-// polygon around c with only strictly convex nodes: both are checked at the
-// end, and a set that fails is left to the streaming path.
+// polygon around c with only strictly convex nodes: both are checked before
+// anything is written, and a set that fails is left to the streaming path.
 //
 // The passes of the streaming path kept nearly every point of a circle for 9
 // of its 16 passes: 1530 us for 5M points. Here each point is read four times
@@ -60,7 +61,7 @@ struct RingCtl {
     // off, piece k's first vertex is the hull's at[k]th
     int pieces, h, start, buf;
     int off[kRays], at[kRays + 1];
-    int turns, bad, ticket, pad;
+    int bad, pad;  // bad: the nodes are no star around c
 };
 
 __device__ __forceinline__ bool gate_shut(const RingArgs& a) { return a.gate && *a.gate != 1; }
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(1024) void k_ring_rays(RingArgs a)
     if (t == 0) {
         ctl->t0 = t0;
         ctl->left = 0; ctl->err = 0; ctl->n_pocket = 0;
-        ctl->turns = 0; ctl->bad = 0; ctl->ticket = 0;
+        ctl->bad = 0;
         s_bad = 0;
     }
     if (t < 3 * kCtrSlots) ctl->ctr[t / 3].c[t % 3] = before;
@@ -634,6 +635,7 @@ __global__ __launch_bounds__(kWedgeT) void k_ring_wedge(RingArgs a)
     // the pockets' nodes as one list (m <= the wedge's points), in LDS if it fits
     uint64_t lo = ~0ull;
     int lo_at = 0;
+    bool bad = false;
     auto solve = [&](const auto& list) {
         for (int i = t; i < m; i += kWedgeT) {
             int l = 0, u = K;
@@ -647,9 +649,15 @@ __global__ __launch_bounds__(kWedgeT) void k_ring_wedge(RingArgs a)
         __syncthreads();
         int f;
         m = ring_rounds<kWedgeT, false>(list, m, ctl->c, f, red, ctr);
-        // back to `slots`; its lexicographic minimum
+        // back to `slots`; its lexicographic minimum; every edge has to turn
+        // about c (the first one may lie on a ray: the join sees to it)
         for (int i = t; i < m; i += kWedgeT) {
             const float4 p = list.get(f, i);
+            if (i + 1 < m) {
+                const float4 q = list.get(f, i + 1);
+                const int o = orient_of(ctl->c, make_float2(p.x, p.y), make_float2(q.x, q.y), ctr);
+                bad |= o < 0 || (o == 0 && i > 0);
+            }
             gst(a.slots + off + i, p);
             const uint64_t v = lex_key(p);
             lo_at = v < lo ? i : lo_at;
@@ -659,6 +667,7 @@ __global__ __launch_bounds__(kWedgeT) void k_ring_wedge(RingArgs a)
     if (m <= kWedgeLds) solve(NodesLds<kWedgeLds>{s_list});
     else solve(NodesGlobal{{a.slots + off, a.slots2 + off}});
     if (t == 0) s_min = ~0ull;
+    if (__ballot(bad) && lane_id() == 0) atomicOr(&ctl->bad, 1);
     __syncthreads();
     const uint64_t wl = wave_min_u64(lo);
     if (lane_id() == 63) atomicMin(&s_min, (unsigned long long)wl);
@@ -675,7 +684,13 @@ __global__ __launch_bounds__(kWedgeT) void k_ring_wedge(RingArgs a)
 // nodes and piece k's first ones: nodes that are not strictly convex between
 // their neighbours go, from both sides of the seam, until those left are.
 // Neighbouring seams share a piece and take turns; a piece that would empty is
-// one thread's work afterwards (rare).
+// left to the removal rounds over the whole ring (rare).
+// The nodes are the hull if the ring of them turns about c: each is strictly
+// convex, they are in order by angle, wedge by wedge, and every edge takes less
+// than half a turn, so all of them together take one. The edges inside a wedge
+// were checked there (removing nodes at its ends adds none); left are each
+// piece's first edge and the ones across the seams. Nothing is written for a
+// set that fails.
 constexpr int kEnds = 4;
 __global__ __launch_bounds__(1024) void k_ring_join(RingArgs a)
 {
@@ -780,6 +795,7 @@ __global__ __launch_bounds__(1024) void k_ring_join(RingArgs a)
     }
     __syncthreads();
     int h, start, buf = 0;
+    bool bad = false;
     if (s_seq) {
         const int n = t < K ? suf[t] - pre[t] : 0;
         const int p = block_prefix<1024>(n, red, &h);
@@ -792,6 +808,10 @@ __global__ __launch_bounds__(1024) void k_ring_join(RingArgs a)
         int f;
         h = ring_rounds<1024, true>(list, h, c, f, red, ctr);
         buf = f ^ 1;
+        for (int j = t; j < h; j += 1024) {
+            const float4 p = list.get(f, j), q = list.get(f, j + 1 < h ? j + 1 : 0);
+            bad |= orient_of(c, make_float2(p.x, p.y), make_float2(q.x, q.y), ctr) <= 0;
+        }
         for (int j = t; j < h; j += 1024)
             if (lex_key(list.get(f, j)) == s_min) s_start = j;  // (one node: the ring's positions differ)
         __syncthreads();
@@ -809,10 +829,16 @@ __global__ __launch_bounds__(1024) void k_ring_join(RingArgs a)
             ctl->off[t] = off[t] + pre[t];
             ctl->at[t] = p;
             at[t] = p;
+            const int k = inc(t);
+            const float2 A = node(t, pre[t]), Z = node(t, suf[t] - 1);
+            bad |= orient_of(c, Z, node(k, pre[k]), ctr) <= 0;
+            if (n > 1) bad |= orient_of(c, A, node(t, pre[t] + 1), ctr) <= 0;
         }
         __syncthreads();
         start = at[s_start] + low_at[s_start] - pre[s_start];
     }
+    bad |= h < 3;
+    if (__ballot(bad) && lane == 0) atomicOr(&ctl->bad, 1);
     if (t == 0) {
         ctl->at[K] = h;
         ctl->pieces = K;
@@ -823,96 +849,56 @@ __global__ __launch_bounds__(1024) void k_ring_join(RingArgs a)
     ctr_flush(ctl->ctr, ctr, csum);
 }
 
-// The hull from its lexicographic minimum, and the proof that it is one: every
-// edge turns about the centre the same way, once around. The last workgroup
-// writes the status.
+// The hull from its lexicographic minimum, if the nodes are one, and the status.
 constexpr int kRingEmitT = 256;
 __global__ __launch_bounds__(kRingEmitT) void k_ring_emit(RingArgs a)
 {
     __shared__ int at[kRays + 1], off[kRays];
-    __shared__ int s_last;
-    __shared__ uint32_t csum[3];
-    RingCtl* ctl = a.ctl;
+    const RingCtl* ctl = a.ctl;
     if (gate_shut(a)) return;
     LocalStatus* st = a.status;
     const int t = (int)threadIdx.x, b = (int)blockIdx.x, nb = (int)gridDim.x;
-    if (ctl->left | ctl->err) {
-        if (b == 0 && t == 0) {
-            st->h = 0;
-            st->err = ctl->err;
-            st->left = ctl->err ? 0 : 1;
+    const int err = ctl->err;
+    const bool good = !(ctl->left | err) && ctl->bad == 0;
+    const int h = good ? ctl->h : 0;
+    if (b == 0) {
+        if (t < kLocalStatPasses) { st->pass_v[t] = 0; st->pass_s[t] = 0; }
+        if (t == 0) {
+            st->h = h;
+            st->err = err;
+            st->left = (good || err) ? 0 : 1;
+            if (a.gate) {
+                *a.h_dev = h;
+                *a.bad_dev = err != 0;
+            }
+            st->passes = 0;
+            st->first_v = a.n;
+            st->line = a.line;
             st->orient = ctr_total(ctl->ctr, 0);
             st->orient_exact = ctr_total(ctl->ctr, 1);
             st->cmp_exact = ctr_total(ctl->ctr, 2);
             st->t0 = ctl->t0;
-            st->t1 = wall_clock64();
-            if (a.gate) {
-                *a.h_dev = 0;
-                *a.bad_dev = ctl->err != 0;
+        }
+    }
+    if (good) {
+        const int K = ctl->pieces, start = ctl->start;
+        const float4* nodes = ctl->buf ? a.slots2 : a.slots;
+        for (int k = t; k <= K; k += kRingEmitT) at[k] = ctl->at[k];
+        for (int k = t; k < K; k += kRingEmitT) off[k] = ctl->off[k];
+        __syncthreads();
+        for (int e = b * kRingEmitT + t; e < h; e += nb * kRingEmitT) {
+            int l = 0, u = K;
+            while (u - l > 1) {
+                const int m = (l + u) >> 1;
+                if (at[m] <= e) l = m;
+                else u = m;
             }
+            const float4 p = gld(nodes + off[l] + (e - at[l]));
+            const int r = e >= start ? e - start : e - start + h;
+            if (r < a.cap) gst(a.out + r, __float_as_int(p.z));
         }
-        return;
     }
-    const int K = ctl->pieces, h = ctl->h, start = ctl->start;
-    const float4* nodes = ctl->buf ? a.slots2 : a.slots;
-    const float2 c = ctl->c;
-    for (int k = t; k <= K; k += kRingEmitT) at[k] = ctl->at[k];
-    for (int k = t; k < K; k += kRingEmitT) off[k] = ctl->off[k];
-    if (t < 3) csum[t] = 0u;
-    __syncthreads();
-    Counters ctr = {0u, 0u, 0u};
-    bool bad = h < 3;
-    int up = 0;
-    for (int e = b * kRingEmitT + t; e < h && h >= 3; e += nb * kRingEmitT) {
-        int l = 0, u = K;
-        while (u - l > 1) {
-            const int m = (l + u) >> 1;
-            if (at[m] <= e) l = m;
-            else u = m;
-        }
-        const float4 p = gld(nodes + off[l] + (e - at[l]));
-        if (e + 1 >= at[l + 1]) l = l + 1 < K ? l + 1 : 0;
-        const float4 q = gld(nodes + off[l] + (e + 1 < h ? e + 1 - at[l] : 0));
-        bad |= orient_of(c, make_float2(p.x, p.y), make_float2(q.x, q.y), ctr) <= 0;
-        up += p.y < c.y && q.y >= c.y;
-        const int r = e >= start ? e - start : e - start + h;
-        if (r < a.cap) gst(a.out + r, __float_as_int(p.z));
-    }
-    up = wave_total(up);
-    const bool any = __ballot(bad) != 0;
-    if (lane_id() == 0) {
-        if (up) atomicAdd(&ctl->turns, up);
-        if (any) atomicOr(&ctl->bad, 1);
-    }
-    ctr_flush(ctl->ctr, ctr, csum);
-    __syncthreads();
-    if (t == 0) {
-        __threadfence();
-        s_last = atomicAdd(&ctl->ticket, 1) == nb - 1;
-    }
-    __syncthreads();
-    if (!s_last) return;
-    if (t < kLocalStatPasses) { st->pass_v[t] = 0; st->pass_s[t] = 0; }
-    if (t == 0) {
-        __threadfence();
-        auto now = [](auto* v) { return __hip_atomic_load(v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-        const bool good = now(&ctl->turns) == 1 && now(&ctl->bad) == 0;
-        st->h = good ? h : 0;
-        st->err = 0;
-        st->left = good ? 0 : 1;
-        if (a.gate) {
-            *a.h_dev = good ? h : 0;
-            *a.bad_dev = 0;
-        }
-        st->passes = 0;
-        st->first_v = a.n;
-        st->line = a.line;
-        st->orient = ctr_total(ctl->ctr, 0);
-        st->orient_exact = ctr_total(ctl->ctr, 1);
-        st->cmp_exact = ctr_total(ctl->ctr, 2);
-        st->t0 = ctl->t0;
-        st->t1 = wall_clock64();
-    }
+    if (b == 0 && t == 0) st->t1 = wall_clock64();
 }
 
 }  // namespace sqh

@@ -105,3 +105,41 @@ def test_times_cover_the_whole_call(H, kind, n):
     assert ("k_ring_emit" in names) == (kind == "circle"), names
     # the events also see the gaps around a kernel: a tenth of room
     assert st["ms_total"] >= 0.9 * sum(ms for _, ms in launches), (st["ms_total"], launches)
+def around_its_box(n):
+    """A quarter of a circle whose sampled places all hold one inner point, so
+    that no polygon is found and the ring kernels take the box's centre, which
+    lies on the chord: they cut, sort and join, and then have to refuse."""
+    t = np.linspace(0.0, np.pi / 2, n)
+    xy = np.stack([np.cos(t), np.sin(t)], 1)
+    xy[0], xy[-1] = [1, 0], [0, 1]
+    xy = xy[np.random.default_rng(n).permutation(n)]
+    ends = [np.array([1.0, 0.0]), np.array([0.0, 1.0])]
+    for r in range(128):  # the sample of one workgroup: 128 runs of 8 points
+        q = min(r * n // 128, n - 8)
+        xy[q:q + 8] = [0.6, 0.6]
+    # the box's sample is every n / 8192th point: the two ends among them
+    q = [int(i * n // 8192) for i in (11, 4099)]
+    assert all(not np.array_equal(xy[i], [0.6, 0.6]) for i in q)
+    xy[q] = ends
+    return xy.astype(np.float32)
+
+
+@pytest.mark.parametrize("n", [40_000, 90_001])
+def test_refused_ring_writes_nothing(H, n):
+    import torch
+    say(f"refused ring n={n}")
+    xy = around_its_box(n)
+    want = hull(xy)
+    assert len(want) > 1024
+    t = torch.from_numpy(xy).cuda()
+    out = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    H.set_launch_timing(True)
+    try:
+        got = H.hull(t, out=out)
+        names = [k for k, _ in H.launch_times()]
+    finally:
+        H.set_launch_timing(False)
+    assert [int(v) for v in got.cpu().numpy()] == want
+    assert bool((out[len(want):] == -7).all())
+    # the ring kernels ran to their end, and another path followed
+    assert names.index("k_ring_emit") < len(names) - 1, names
