@@ -637,6 +637,7 @@ struct HullArgs {
     float2* xy2;             // the kept subset: points ...
     int* ids2;               // ... and their input indices
     int* gs2;                // {0, subset size}
+    int sub_n = -1;          // the subset is there already: its size (k_prefilter does not run)
     // sorted-chain variant (single hulls; the host launches k_sort between
     // the first phases and the passes)
     int sorted;
@@ -1908,7 +1909,11 @@ __global__ void k_reset(HullArgs a)
         a.info->vcount = 0;
         a.info->vcap = a.vcap;
         a.info->pass_traced = 0;
-        a.info->prefilter_n = -1;
+        a.info->prefilter_n = a.sub_n;
+        if (a.sub_n >= 0) {
+            a.gs2[0] = 0;
+            a.gs2[1] = a.sub_n;
+        }
         a.info->keep_n = 0;
         a.info->sort_n = -1;
         a.info->sort_bad = 0;

@@ -143,3 +143,29 @@ def test_refused_ring_writes_nothing(H, n):
     assert bool((out[len(want):] == -7).all())
     # the ring kernels ran to their end, and another path followed
     assert names.index("k_ring_emit") < len(names) - 1, names
+
+
+@pytest.mark.parametrize("case", ["square", "rim", "refused"])
+def test_prefiltered_subset_is_not_made_twice(H, case):
+    # a subset of which the sieve's polygon keeps between a quarter and three
+    # quarters, and one whose ring is refused: both go on from the subset
+    say(f"pre-filtered subset: {case}")
+    if case == "square":
+        xy = workloads.square(20_000_000, 0)  # 4176 points are left
+    elif case == "rim":
+        xy = np.concatenate([workloads.circle(50_000, 3), workloads.disk(950_000, 4) * np.float32(0.95)])
+        xy = xy.astype(np.float32)[np.random.default_rng(1).permutation(1_000_000)]
+    else:
+        # (extents below the ring kernels' range)
+        xy = workloads.circle(300_000, 5) * np.float32(1e-20)
+    H.set_prefilter(sqh.SQH_PREFILTER_OCTAGON)
+    try:
+        got, launches, st = timed_hull(H, xy)
+    finally:
+        H.set_prefilter(sqh.SQH_PREFILTER_NONE)
+    names = [k for k, _ in launches]
+    assert got == hull(xy)
+    assert st["prefilter_points"] > 4096 and st["ms_prefilter"] > 0
+    assert names.count("k_pre_keep") == 1 and "k_prefilter" not in names, names
+    assert ("k_hull<prefiltered>" in names) == (case == "refused"), names
+    assert st["ms_total"] >= 0.9 * sum(ms for _, ms in launches), (st["ms_total"], launches)
