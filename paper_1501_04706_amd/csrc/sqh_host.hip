@@ -730,7 +730,7 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
             // the sieve's keeps less than three quarters of it: the 4176 points of
             // 20M in a square 0.25 ms a call, 70635 of 1M in a disk and on its
             // rim 0.20; on the persistent kernel 0.36 and 1.01)
-            if (ctx->lstat->left) HIP_OK(run_ring(ctx, a, a.xy2, a.ids2, n2, d_out, out_cap, st));
+            if (ctx->lstat->left && ctx->lstat->left != 4) HIP_OK(run_ring(ctx, a, a.xy2, a.ids2, n2, d_out, out_cap, st));
         }
         if (!ctx->lstat->left) {
             rc = collect_local(ctx, N, out_cap, h_total);

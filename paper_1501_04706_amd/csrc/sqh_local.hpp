@@ -13,7 +13,7 @@ struct LocalStatus {
     int h;      // hull vertices (all sets)
     int err;    // kErr* flags
     int left;   // nothing was written: 1: the ring kernels or the general path have to run; 2: launch_rest
-                // has to; 3: the general path has to
+                // has to; 3: the general path has to; 4: the same, and the set is no ring
     int passes;
     int first_v;
     int line;   // the sieve's edges took the static line filter

@@ -33,6 +33,7 @@ constexpr int kSieveT = 512;
 constexpr int kSieveGrid = 1024;   // workgroups of the sieve, at most
 constexpr int kRestOne = 1 << 16;  // up to this many points left one workgroup takes them
 constexpr int kRestHull = 1024;    // hulls of more vertices are left to other paths
+constexpr int kFlatMost = 1 << 18; // sets of copies or on a line: up to this many points stay
 
 struct SieveCtl {
     int left, err, h, kB, line;
@@ -270,7 +271,7 @@ __global__ __launch_bounds__(1024) void k_polygon(SieveArgs a, int ne)
     __shared__ unsigned int lo[2], hi[2];
     __shared__ float2 v[3][kDirs];
     __shared__ float2 bins[kSlabs];
-    __shared__ int s_h, s_kb, s_line, s_keep;
+    __shared__ int s_h, s_kb, s_line, s_keep, s_new;
     __shared__ float s_m[2];
     SieveCtl* ctl = a.ctl;
     const int t = (int)threadIdx.x, lane = lane_id();
@@ -279,7 +280,7 @@ __global__ __launch_bounds__(1024) void k_polygon(SieveArgs a, int ne)
     const float2 probe = gld(a.xy + (int)((long long)t * a.n / 1024));
     if (t < kDirs) best[t] = 0ull;
     if (t < 2) { lo[t] = ~0u; hi[t] = 0u; }
-    if (t == 0) s_keep = 0;
+    if (t == 0) { s_keep = 0; s_new = 0; }
     if (ne > 0) {
         __syncthreads();
         unsigned long long k = 0ull;
@@ -333,8 +334,15 @@ __global__ __launch_bounds__(1024) void k_polygon(SieveArgs a, int ne)
     const bool kp = !slab_inside(sl, bins, probe.x, probe.y) &&
                     !(h >= 3 && chain_inside(v[2], h, s_kb, s_line != 0, s_m[0], s_m[1], probe.x, probe.y,
                                              ctr.orient_exact));
-    const uint64_t M = __ballot(kp);
-    if (lane == 0) atomicAdd(&s_keep, (int)__popcll(M));
+    // ... and how many of those are no copies of its vertices
+    bool copy = false;
+    if (kp && h >= 3)
+        for (int i = 0; i < h; ++i) copy |= v[2][i].x == probe.x && v[2][i].y == probe.y;
+    const uint64_t M = __ballot(kp), N = __ballot(kp && !copy);
+    if (lane == 0) {
+        atomicAdd(&s_keep, (int)__popcll(M));
+        atomicAdd(&s_new, (int)__popcll(N));
+    }
     __syncthreads();
     if (t == 0) {
         ctl->h = h;
@@ -345,7 +353,11 @@ __global__ __launch_bounds__(1024) void k_polygon(SieveArgs a, int ne)
         ctl->slabs = sl;
         // (three quarters of a ring or an arc are kept, and the ring kernels take
         // it; between the two the general path is the better guess)
-        if (h >= 3 && s_keep > 256) ctl->left = s_keep > 768 ? 1 : 3;
+        if (h >= 3 && s_new > 256) ctl->left = s_new > 768 ? 1 : 3;
+        // what stays are copies, or there is no polygon (points on a line): kMidP
+        // at a time that takes 150 us for 1M points of one position and 4 ms for
+        // 20M, the general path 70 and 90
+        else if (s_keep > 256 && a.n > kFlatMost) ctl->left = 4;
     }
 }
 static_assert(kSlabs == 1024, "a thread of k_polygon per slab");

@@ -169,3 +169,41 @@ def test_prefiltered_subset_is_not_made_twice(H, case):
     assert names.count("k_pre_keep") == 1 and "k_prefilter" not in names, names
     assert ("k_hull<prefiltered>" in names) == (case == "refused"), names
     assert st["ms_total"] >= 0.9 * sum(ms for _, ms in launches), (st["ms_total"], launches)
+
+
+def copies(n, k, seed=1):
+    t = np.random.default_rng(seed).integers(0, k, n) * (2 * np.pi / k)
+    return np.stack([np.cos(t), np.sin(t)], 1).astype(np.float32)
+
+
+def thin_sets(n):
+    rng = np.random.default_rng(n)
+    a = rng.permutation(n).astype(np.float32)
+    heap = workloads.circle(n, 9)
+    heap[rng.random(n) < 0.6] = heap[17]
+    yield "one position", np.full((n, 2), 0.5, np.float32)
+    yield "two positions", np.float32([[1, 2], [-3, 0.5]])[rng.integers(0, 2, n)]
+    yield "line", np.stack([a, 2 * a], 1)
+    yield "copies of three", copies(n, 3)
+    yield "copies of 150", copies(n, 150)
+    yield "copies of 600", copies(n, 600)
+    yield "heap", heap
+    # most points in one direction from the centre, in 4000 places
+    far = np.concatenate([workloads.circle(n - n // 2, 3), (workloads.circle(n // 2, 4) * 1e-3 + [0.9, 0.0])])
+    yield "cluster", far[rng.permutation(n)].astype(np.float32)
+
+
+@pytest.mark.parametrize("n", [4097, 30_000, 65_536, 262_144, 262_145, 600_001])
+def test_sets_that_no_polygon_thins(H, n):
+    # copies of a few points, and points on a line: no wave and no workgroup
+    # may be left with a share of the set (200K copies of three points took the
+    # ring kernels 85 ms, 2M 0.9 s)
+    for name, xy in thin_sets(n):
+        say(f"no polygon: {name} n={n}")
+        got, launches, st = timed_hull(H, xy)
+        assert got == hull(xy), name
+        names = [k for k, _ in launches]
+        if name.startswith("copies of") or "position" in name or name == "line":
+            assert "k_ring_pocket" not in names or name == "copies of 600", (name, names)
+        # (a wave that sorts a thousand copies takes a millisecond)
+        assert dict(launches).get("k_ring_pocket", 0.0) < 1.5, (name, launches)
