@@ -240,8 +240,10 @@ int sqh_hull_noalloc(sqh_ctx *ctx, const float *d_xy, int64_t n, int32_t *d_out,
  *              set) is written at d_out[d_out_off[s] .. d_out_off[s+1]).
  *   d_out_off  device, n_sets + 1 int64, written by the call.
  *   h_total    host; receives d_out_off[n_sets] (total vertices).
- * All sets are processed together: the per-set first split and every pass
- * run over the segments of all sets in one launch sequence. Returns as
+ * All sets are processed together: by a workgroup each, and those that this
+ * does not suit (more than 2^20 points, a ring that cannot be cut, copies) by
+ * the general path, whose first split and passes run over the segments of all
+ * of them; where they hold most of the points, it takes every set. Returns as
  * sqh_hull (SQH_ECAPACITY if the total exceeds out_cap; then no hull is
  * written past out_cap). Synchronises the stream before returning.
  */
@@ -344,9 +346,9 @@ void sqh_graph_destroy(sqh_graph *graph);
  *     convention as sqh_hull, indices local to the request) and frees their
  *     slots.
  * A step of 16 passes or more (default precision, nothing resident) finishes
- * all of its requests on the workgroup-local kernels instead, large ones one
- * after another; if they leave one, the whole step runs on the segment table
- * before sqh_engine_finish returns.
+ * its requests on the workgroup-local kernels instead, large ones one after
+ * another; those that they leave run on the segment table before
+ * sqh_engine_finish returns.
  * An engine is used by one host thread. Admissions may use their own stream
  * (a copy stream) and overlap a launched step.
  */

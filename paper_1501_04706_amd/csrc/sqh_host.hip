@@ -662,6 +662,59 @@ struct Spent {
     }
 };
 
+// The sets that the batch kernels refused, as a batch of their own on the
+// persistent kernel, then all hulls to the caller. Their points go to xy2 (the
+// hulls behind them), offsets and set starts to the sort's counts; what the
+// batch kernels left for the emission is where that kernel does not work. If
+// they hold more than that takes, lstat->left sends the whole batch there. (One
+// such set among 500 made the call 1.2 to 2 times as long as it had been.)
+int run_refused(sqh_ctx* ctx, const HullArgs& a, const BatchArgs& b, const TuneEntry& tu, hipStream_t st, Spent& spent)
+{
+    const int64_t n = ctx->lstat->refused_points, g = ctx->lstat->refused;
+    const size_t off_bytes = sizeof(int64_t) * (size_t)(g + 1);
+    if (3 * n > 2 * (int64_t)a.N || 8 * g > 7 * (int64_t)a.G ||
+        2 * off_bytes + sizeof(int) * (size_t)(2 * g + 1) > sizeof(int) * (size_t)kSortBuckets * (size_t)kMaxGrid) {
+        ctx->lstat->left = 3;
+        return SQH_OK;
+    }
+    char* at = reinterpret_cast<char*>(a.shist);
+    RefusedArgs r{};
+    r.n = (int)n;
+    r.g = (int)g;
+    r.xy = a.xy2;
+    r.off = reinterpret_cast<int64_t*>(at);
+    r.rset = reinterpret_cast<int*>(at + 2 * off_bytes);
+    HullArgs q = a;
+    q.xy = r.xy;
+    q.N = r.n;
+    q.G = r.g;
+    q.set_off = r.off;
+    q.out = reinterpret_cast<int32_t*>(a.xy2 + n);
+    q.cap = n;
+    q.out_off = reinterpret_cast<int64_t*>(at + off_bytes);
+    q.gstart = r.rset + g;
+    q.W = (r.n + 63) / 64;
+    r.out = q.out;
+    r.out_off = q.out_off;
+    if (time_open(ctx, "k_refused", st) != SQH_OK) return SQH_EDEVICE;
+    HIP_OK(launch_refused_gather(b, r, ctx->cus, st));
+    if (time_close(ctx, "k_refused", st) != SQH_OK) return SQH_EDEVICE;
+    const int64_t work = std::max<int64_t>(q.W, 4 * g);
+    int rc = enqueue(ctx, q, (int)std::min<int64_t>(2048, (work + 255) / 256), tu.grid, tu.sgrid, st);
+    if (rc != SQH_OK) return rc;
+    rc = collect(ctx, q, n, n, nullptr, st, false);
+    if (rc != SQH_OK) return rc;
+    spent.orient += ctx->stats.orient_evals;
+    spent.orient_exact += ctx->stats.orient_exact;
+    spent.cmp_exact += ctx->stats.cmp_exact;
+    if (time_open(ctx, "k_batch", st) != SQH_OK) return SQH_EDEVICE;
+    HIP_OK(launch_refused_put(b, r, ctx->cus, st));
+    HIP_OK(launch_batch_emit(b, ctx->cus, st, 1));
+    if (time_close(ctx, "k_batch", st) != SQH_OK) return SQH_EDEVICE;
+    HIP_OK(hipStreamSynchronize(st));
+    return SQH_OK;
+}
+
 int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const int64_t* d_set_off, int32_t* d_out,
               int64_t* d_out_off, int64_t out_cap, int64_t* h_total, void* d_ws, size_t ws_bytes, hipStream_t st,
               const TuneEntry& tu)
@@ -764,18 +817,25 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
         b.sieve = sieve;
         b.status = ctx->lstat;
         b.start = a.gstart;
-        b.hcnt = reinterpret_cast<int*>(a.sets);
+        // (what has to last while the general path solves refused sets lies
+        // where it does not work: hcnt behind seven eighths of the sets' records,
+        // hbuf and ctl in the pre-filter's buffers)
+        b.hcnt = reinterpret_cast<int*>(a.sets) + 14 * nsets;
         b.order = b.hcnt + nsets;
-        b.hbuf = a.vidx;
+        b.hbuf = a.ids2;
         batch_space(b, a.recs, a.segs[0], a.segs[1]);
         b.dense = reinterpret_cast<DenseSet*>(a.seg_cid[0]);
         b.dense_cap = (int)(N / 4096 + 1);
-        b.ctl = reinterpret_cast<BatchCtl*>(a.slots);
+        b.ctl = reinterpret_cast<BatchCtl*>(a.ext);
         if (time_open(ctx, "k_batch", st) != SQH_OK) return SQH_EDEVICE;
         HIP_OK(launch_batch(b, ctx->cus, st));
         HIP_OK(launch_batch_emit(b, ctx->cus, st));
         if (time_close(ctx, "k_batch", st) != SQH_OK) return SQH_EDEVICE;
         HIP_OK(hipStreamSynchronize(st));
+        if (!ctx->lstat->left && ctx->lstat->refused) {
+            rc = run_refused(ctx, a, b, tu, st, spent);
+            if (rc < 0) return rc;
+        }
         if (!ctx->lstat->left) {
             rc = collect_local(ctx, N, out_cap, h_total);
             spent.report(ctx->stats);
@@ -994,9 +1054,32 @@ void eng_free(sqh_engine* e, int64_t base, int64_t alloc)
 
 namespace {
 
+static_assert(sizeof(SetInfo) == 64, "a batch's hull sizes lie behind seven eighths of the records");
+
 constexpr int kLocalStepPasses = 16;  // (a circle of 5M points takes 16)
 
 int no_mark(void*, const char*, int, hipStream_t) { return SQH_OK; }
+
+// The launched step's requests as the kernels read them: places in the staging
+// half (N points) and slots of the new ones, slots and sizes of all.
+void eng_fill_up(sqh_engine* e, int64_t N)
+{
+    const int64_t R = e->L.R;
+    int* up_gstart = e->h_up;
+    int* up_sbase = e->h_up + (R + 1);
+    int* up_rbase = e->h_up + (2 * R + 1);
+    int* up_rn = e->h_up + (3 * R + 1);
+    const int G = (int)e->step_new.size(), nres = (int)e->step_all.size();
+    for (int g = 0; g < G; ++g) {
+        up_gstart[g] = (int)e->step_new[g].stage_at;
+        up_sbase[g] = (int)e->step_new[g].base;
+    }
+    up_gstart[G] = (int)N;
+    for (int r = 0; r < nres; ++r) {
+        up_rbase[r] = (int)e->step_all[r].base;
+        up_rn[r] = (int)e->step_all[r].n;
+    }
+}
 
 // The launched step (step_new, step_all) on the resident segment table: N
 // points in staging half `side`.
@@ -1175,15 +1258,16 @@ int eng_local(sqh_engine* e, int side, int64_t N, hipStream_t st)
 
 namespace {
 
-// Collects a step that the local kernels finished: `count` status blocks.
-int eng_collect_local(sqh_engine* e, int count)
+// Collects what the local kernels finished of a step (`count` status blocks).
+// The requests they left stay in step_new and step_all, their points moved to
+// the front of staging half `side`. Returns how many were finished.
+int eng_collect_local(sqh_engine* e, int count, int side, hipStream_t st)
 {
     sqh_ctx* c = e->ctx;
     const EngLayout& L = e->L;
     const int G = (int)e->step_new.size();
     const int* dn_h = e->h_down + L.R;
     const int* dn_bad = e->h_down + 2 * L.R;
-    ++e->steps;
     sqh_stats& S = c->stats;
     S = sqh_stats{};
     S.points = up_points(e);
@@ -1198,8 +1282,16 @@ int eng_collect_local(sqh_engine* e, int count)
     }
     S.ms_total = S.ms_kernel = (double)(e->h_local[0].t1 - e->h_local[0].t0) * 1e-5;
     int64_t off = 0;
+    int big = 1;
+    const bool none = (e->h_local[0].left | e->h_local[0].err) != 0;  // (nothing was emitted)
+    std::vector<EngReq> left;
     for (int g = 0; g < G; ++g) {
         const EngReq& q = e->step_new[g];
+        const bool own = q.n > kEngineSetMax;  // (a launch, and a status, of its own)
+        if (none || (own ? e->h_local[big++].left != 0 : dn_h[g] < 0)) {
+            left.push_back(q);
+            continue;
+        }
         const int64_t h = dn_h[g];
         EngDone d{q.tag, SQH_OK, {}};
         if (dn_bad[g]) {
@@ -1216,9 +1308,23 @@ int eng_collect_local(sqh_engine* e, int count)
         e->done.push_back(std::move(d));
         eng_free(e, q.base, q.alloc);
     }
-    e->step_new.clear();
-    e->step_all.clear();
-    return G;
+    const int finished = G - (int)left.size();
+    if (!left.empty() && finished > 0) {
+        // (through the first survivor buffer, x and y of which are 8 bytes a slot)
+        float2* stage = reinterpret_cast<float2*>(e->arena + L.stage) + (size_t)side * L.SC;
+        float2* tmp = reinterpret_cast<float2*>(e->arena + L.x[0]);
+        int64_t n = 0;
+        for (EngReq& q : left) {
+            HIP_OK(hipMemcpyAsync(tmp + n, stage + q.stage_at, sizeof(float2) * (size_t)q.n, hipMemcpyDeviceToDevice, st));
+            q.stage_at = n;
+            n += q.n;
+        }
+        HIP_OK(hipMemcpyAsync(stage, tmp, sizeof(float2) * (size_t)n, hipMemcpyDeviceToDevice, st));
+    }
+    e->step_all = left;
+    std::sort(e->step_all.begin(), e->step_all.end(), [](const EngReq& p, const EngReq& q) { return p.base < q.base; });
+    e->step_new.swap(left);
+    return finished;
 }
 
 }  // namespace
@@ -1713,20 +1819,7 @@ int sqh_engine_launch(sqh_engine* e, int max_passes, void* stream)
               [](const EngReq& p, const EngReq& q) { return p.base < q.base; });
     e->step_new.swap(e->staged);
     e->staged.clear();
-    const int nres = (int)e->step_all.size();
-    int* up_gstart = e->h_up;
-    int* up_sbase = e->h_up + (R + 1);
-    int* up_rbase = e->h_up + (2 * R + 1);
-    int* up_rn = e->h_up + (3 * R + 1);
-    for (int g = 0; g < G; ++g) {
-        up_gstart[g] = (int)e->step_new[g].stage_at;
-        up_sbase[g] = (int)e->step_new[g].base;
-    }
-    up_gstart[G] = (int)e->stage_used;
-    for (int r = 0; r < nres; ++r) {
-        up_rbase[r] = (int)e->step_all[r].base;
-        up_rn[r] = (int)e->step_all[r].n;
-    }
+    eng_fill_up(e, e->stage_used);
     if (e->admitted) HIP_OK(hipStreamWaitEvent(st, e->ev_admit, 0));  // staged points have arrived
     e->admitted = false;
     // A step of many passes finishes its requests anyway: without residents it
@@ -1758,28 +1851,32 @@ int sqh_engine_finish(sqh_engine* e)
     const EngLayout& L = e->L;
     const int64_t R = L.R;
     char* A = e->arena;
-    const int G = (int)e->step_new.size();
-    const int nres = (int)e->step_all.size();
     int* dn_alive = e->h_down;
     int* dn_h = e->h_down + R;
     int* dn_bad = e->h_down + 2 * R;
     int* dn_err = e->h_down + 3 * R;
+    int finished = 0;
+    sqh_stats before{};
     if (e->local) {
-        bool left = false;
-        int big = 1;
-        for (const EngReq& q : e->step_new)
-            if (q.n > kEngineSetMax) left |= e->h_local[big++].left != 0;
-        left |= e->h_local[0].left != 0;
-        if (!left) return eng_collect_local(e, big);
-        // a request that the local kernels do not take: the whole step again
-        // on the segment table
+        // what the local kernels leave runs on the segment table
         e->local = false;
-        int64_t N = 0;
-        for (const EngReq& q : e->step_new) N += q.n;
+        int count = 1;
+        for (const EngReq& q : e->step_new) count += q.n > kEngineSetMax;
+        finished = eng_collect_local(e, count, e->side ^ 1, st);
+        if (finished < 0) return finished;
+        if (e->step_new.empty()) {
+            ++e->steps;
+            return finished;
+        }
+        before = c->stats;
+        const int64_t N = up_points(e);
+        eng_fill_up(e, N);
         const int rc = eng_general(e, e->side ^ 1, N, st);
         if (rc != SQH_OK) return rc;
         HIP_OK(hipEventSynchronize(e->ev_done));
     }
+    const int G = (int)e->step_new.size();
+    const int nres = (int)e->step_all.size();
     if (*dn_err & (kErrSpin | kErrBounds)) {
         e->broken = true;
         return SQH_EDEVICE;
@@ -1789,8 +1886,8 @@ int sqh_engine_finish(sqh_engine* e)
     {
         sqh_stats& S = c->stats;
         S = sqh_stats{};
-        S.points = up_points(e);
-        S.passes = e->h_info->passes;
+        S.points = std::max(up_points(e), before.points);
+        S.passes = std::max<int64_t>(e->h_info->passes, before.passes);
         phase_times(*e->h_info, S);
         for (int i = 0; i < kStatSlots; ++i) {
             S.orient_evals += c->hstats[4 * i + 0];
@@ -1800,13 +1897,17 @@ int sqh_engine_finish(sqh_engine* e)
         float ms = 0.0f;
         if (hipEventElapsedTime(&ms, c->ev0, c->ev1) == hipSuccess) S.ms_total = ms;
         if (hipEventElapsedTime(&ms, c->evk, c->ev1) == hipSuccess) S.ms_kernel = ms;
+        S.orient_evals += before.orient_evals;
+        S.orient_exact += before.orient_exact;
+        S.cmp_exact += before.cmp_exact;
+        S.ms_total += before.ms_total;
+        S.ms_kernel += before.ms_kernel;
     }
     // bad inputs among the new requests (their sets were skipped)
     std::map<int64_t, int> bad_base;
     for (int g = 0; g < G; ++g)
         if (dn_bad[g]) bad_base[e->step_new[g].base] = 1;
     // collect finished requests: copy their hulls through the pinned bounce buffer
-    int finished = 0;
     std::vector<EngReq> keep;
     std::vector<std::pair<EngReq, int>> fin;
     for (int r = 0; r < nres; ++r) {

@@ -130,6 +130,8 @@ struct alignas(128) BatchStats {
 };
 struct BatchCtl {
     int err, left;
+    int n_refused;
+    unsigned long long refused_points;
     int n_small, n_big;         // queue lengths: class 0; classes 5 .. 1
     int head_big, n_task[kTasks];
     int n_pocket, n_dense;
@@ -173,12 +175,13 @@ __device__ __forceinline__ int set_class(int n)
 // first (one workgroup: a few loads per set).
 __global__ __launch_bounds__(1024) void k_batch_init(BatchArgs a)
 {
-    __shared__ int n[kClasses], at[kClasses], s_err, s_left;
+    __shared__ int n[kClasses], at[kClasses], s_err, s_left, s_over;
+    __shared__ unsigned long long s_over_points;
     const int t = (int)threadIdx.x;
     BatchCtl* ctl = a.ctl;
     for (int i = t; i < (int)(sizeof(BatchCtl) / sizeof(int)); i += 1024) reinterpret_cast<int*>(ctl)[i] = 0;
     if (t < kClasses) n[t] = 0;
-    if (t == 0) { s_err = 0; s_left = 0; }
+    if (t == 0) { s_err = 0; s_left = 0; s_over = 0; s_over_points = 0ull; }
     __syncthreads();
     for (int pass = 0; pass < 2; ++pass) {
         for (int s = t; s < a.G; s += 1024) {
@@ -196,11 +199,17 @@ __global__ __launch_bounds__(1024) void k_batch_init(BatchArgs a)
                     a.hpos[s] = a.hpos_src[s];
                     if (m > kEngineSetMax) continue;
                 }
-                if (m > kBatchSetMax || (m > kLocalPoints && !a.sieve)) s_left = 1;
+                if (m > kLocalPoints && !a.sieve) s_left = 1;
+                if (m > kBatchSetMax) {
+                    a.hcnt[s] = -1;
+                    atomicAdd(&s_over, 1);
+                    atomicAdd(&s_over_points, (unsigned long long)m);
+                    continue;
+                }
                 if (m > 0) atomicAdd(&n[set_class(m)], 1);
             } else {
                 const int m = (int)(w - v);
-                if (m > 0 && (!a.bad || m <= kEngineSetMax)) a.order[atomicAdd(&at[set_class(m)], 1)] = s;
+                if (m > 0 && m <= (a.bad ? kEngineSetMax : kBatchSetMax)) a.order[atomicAdd(&at[set_class(m)], 1)] = s;
             }
         }
         __syncthreads();
@@ -219,7 +228,9 @@ __global__ __launch_bounds__(1024) void k_batch_init(BatchArgs a)
     }
     if (t == 0) {
         ctl->err = s_err ? kErrBounds : 0;
-        ctl->left = (s_left && !s_err) ? 1 : 0;
+        ctl->left = ((s_left || 3 * s_over_points > 2ull * (unsigned long long)a.N) && !s_err) ? 1 : 0;
+        ctl->n_refused = s_over;
+        ctl->refused_points = s_over_points;
         ctl->t0 = wall_clock64();
     }
 }
@@ -236,7 +247,7 @@ __device__ __forceinline__ void put_hull(const BatchArgs& a, int s, int base, in
     }
     int* out = a.hbuf + (a.hpos ? a.hpos[s] : base);
     for (int r = (int)threadIdx.x; r < h; r += T) gst(out + r, id[ring[r]]);
-    if (threadIdx.x == 0) a.hcnt[s] = max(h, 0);  // (a ring's comes later)
+    if (threadIdx.x == 0) a.hcnt[s] = h;  // (a ring's comes later)
 }
 
 // Sets of up to kSmallP points, a workgroup each.
@@ -262,7 +273,7 @@ __global__ __launch_bounds__(kSmallT, 4) void k_batch_small(BatchArgs a)
 }
 
 // A ring of points: cut into pockets for the chain solves that follow.
-// False if it cannot be (the general path has to run).
+// False if it cannot be (the set is refused).
 template <int T, int P>
 __device__ __forceinline__ bool cut_pockets(const BatchArgs& a, SolveLds<P>& L, int h, int s, int base, int n,
                                             Counters& ctr)
@@ -309,18 +320,22 @@ __device__ __forceinline__ bool cut_pockets(const BatchArgs& a, SolveLds<P>& L, 
     // slot ranges (one more than its points for v_k), by one wave
     if (t < 64) {
         int run = 0;
+        bool over = false;
         for (int k0 = 0; k0 < K; k0 += 64) {
             const int k = k0 + t, c = k < K ? D.cnt[k] + 1 : 0;
-            if (c > kTaskP[kTasks - 1] - 1) D.bad = 1;
+            over |= c > kTaskP[kTasks - 1] - 1;
             const int inc = wave_incl_sum(c);
             if (k < K) D.cur[k] = run + inc - c;
             run += __builtin_amdgcn_readlane(inc, 63);
         }
-        if (t == 0) {
+        over = __ballot(over) != 0ull;
+        if (t == 0 && over) D.bad = 1;
+        if (t == 0 && !over) {
             const int d = atomicAdd(&a.ctl->n_dense, 1);
             s_t0 = atomicAdd(&a.ctl->n_pocket, K);
-            if (d >= a.dense_cap || s_t0 + K > a.pocket_cap) D.bad = 1;
-            else gst(a.dense + d, DenseSet{s, s_t0, K, 0, D.c.x, D.c.y, {0, 0}});
+            const bool fits = s_t0 + K <= a.pocket_cap;
+            if (d < a.dense_cap) gst(a.dense + d, DenseSet{s, s_t0, fits ? K : 0, 0, D.c.x, D.c.y, {0, 0}});
+            if (d >= a.dense_cap || !fits) D.bad = 1;
             s_d = d;
         }
     }
@@ -400,8 +415,12 @@ __global__ __launch_bounds__(kMidT) void k_batch_big(BatchArgs a)
         int h = solve_set<T, P>(L, a.xy + base, n, a.fp64 != 0, ctr, &A.st, &sample);
         if (h == kSetDense) {
             const bool ok = sample > 0 && cut_pockets<T, P>(a, L, sample, s, base, n, ctr);
-            if (!ok && threadIdx.x == 0) ctl->left = 1;
             if (L.bad) h = kSetBad;
+            else if (ok) h = 0;
+            else if (threadIdx.x == 0) {  // (h: -1)
+                atomicAdd(&ctl->n_refused, 1);
+                atomicAdd(&ctl->refused_points, (unsigned long long)n);
+            }
         }
         put_hull(a, s, base, h, L.id, L.ring, T);
         lds_barrier();
@@ -521,7 +540,8 @@ __global__ __launch_bounds__(kRingT) void k_batch_ring(BatchArgs a)
     const int t = (int)threadIdx.x, lane = lane_id(), w = t >> 6, nd = ctl->n_dense;
     for (int i = (int)blockIdx.x; i < nd; i += (int)gridDim.x) {
         const DenseSet ds = gld(a.dense + i);
-        const int K = ds.k, base = gld(a.start + ds.set), n = gld(a.start + ds.set + 1) - base;
+        const int K = ds.k, base = gld(a.start + ds.set);
+        if (K == 0) continue;  // (uniform: a refused set)
         for (int k = t; k < K; k += kRingT) {
             s_at[k] = gld(&a.pockets[ds.t0 + k].len);
             s_off[k] = gld(&a.pockets[ds.t0 + k].off);
@@ -578,27 +598,29 @@ __global__ __launch_bounds__(kRingT) void k_batch_ring(BatchArgs a)
 // run of the output (each thread finds its element's set by bisection, so
 // that one large hull does not hold a wave up).
 constexpr int kEmitT = 256;
-__global__ __launch_bounds__(kEmitT) void k_batch_emit(BatchArgs a)
+__global__ __launch_bounds__(kEmitT) void k_batch_emit(BatchArgs a, int all_sets)
 {
     constexpr int W = kEmitT / 64;
     __shared__ int red[W];
     __shared__ int s_at[kEmitT], s_src[kEmitT];
     const BatchCtl* ctl = a.ctl;
     const int t = (int)threadIdx.x, lane = lane_id(), w = t >> 6, b = (int)blockIdx.x, nb = (int)gridDim.x;
-    const int bad = ctl->err | ctl->left;
+    // (refused sets of an engine are left out, those of a batch are waited for)
+    const int refused = all_sets ? 0 : ctl->n_refused;
+    const int bad = ctl->err | ctl->left | (refused && !a.h_host);
     const int per = (a.G + nb - 1) / nb;
     const int s0 = min(b * per, a.G), s1 = min(s0 + per, a.G);
     int run = 0;
     if (!bad) {
         int v = 0;
-        for (int s = t; s < s0; s += kEmitT) v += gld(a.hcnt + s);
+        for (int s = t; s < s0; s += kEmitT) v += max(gld(a.hcnt + s), 0);
         v = wave_total(v);
         if (lane == 0) red[w] = v;
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < W; ++u) run += red[u];
         for (int c0 = s0; c0 < s1; c0 += kEmitT) {
-            const int s = c0 + t, h = s < s1 ? gld(a.hcnt + s) : 0;
+            const int s = c0 + t, hs = s < s1 ? gld(a.hcnt + s) : 0, h = max(hs, 0);
             const int inc = wave_incl_sum(h);
             __syncthreads();
             if (lane == 63) red[w] = inc;
@@ -612,7 +634,7 @@ __global__ __launch_bounds__(kEmitT) void k_batch_emit(BatchArgs a)
             s_at[t] = before + inc - h;
             s_src[t] = s < s1 ? gld((a.hpos ? a.hpos : a.start) + s) : 0;
             if (s < s1 && a.h_host) {
-                a.h_host[s] = h;
+                a.h_host[s] = hs;
                 a.bad_host[s] = gld(a.bad + s);
             }
             if (s < s1 && a.out_off) a.out_off[s] = (int64_t)(run + before + inc - h);
@@ -649,6 +671,8 @@ __global__ __launch_bounds__(kEmitT) void k_batch_emit(BatchArgs a)
             s->h = bad ? 0 : run;
             s->err = ctl->err;
             s->left = ctl->err ? 0 : ctl->left;
+            s->refused = (ctl->err | ctl->left) ? 0 : refused;
+            s->refused_points = (int64_t)ctl->refused_points;
             s->line = 0;
             s->orient = ctr_total(ctl->ctr, 0);
             s->orient_exact = ctr_total(ctl->ctr, 1);
@@ -672,9 +696,67 @@ hipError_t launch_batch(const BatchArgs& a, int cus, hipStream_t st)
     }
     return hipGetLastError();
 }
-hipError_t launch_batch_emit(const BatchArgs& a, int cus, hipStream_t st)
+hipError_t launch_batch_emit(const BatchArgs& a, int cus, hipStream_t st, int all)
 {
-    k_batch_emit<<<std::min((a.G + 3) / 4, 4 * cus), kEmitT, 0, st>>>(a);
+    k_batch_emit<<<std::min((a.G + 3) / 4, 4 * cus), kEmitT, 0, st>>>(a, all);
+    return hipGetLastError();
+}
+
+// The refused sets' numbers and places, in order (one workgroup).
+__global__ __launch_bounds__(1024) void k_refused_plan(BatchArgs a, RefusedArgs r)
+{
+    __shared__ int red[16];
+    const int t = (int)threadIdx.x;
+    int g = 0;
+    int64_t n = 0;
+    for (int s0 = 0; s0 < a.G; s0 += 1024) {
+        const int s = s0 + t;
+        const bool mine = s < a.G && gld(a.hcnt + s) < 0;
+        const int m = mine ? gld(a.start + s + 1) - gld(a.start + s) : 0;
+        int sets, points;  // (of 1024 sets: less than 2^31)
+        const int k = block_prefix<1024>(mine ? 1 : 0, red, &sets), p = block_prefix<1024>(m, red, &points);
+        if (mine) {
+            r.rset[g + k] = s;
+            r.off[g + k] = n + p;
+        }
+        g += sets;
+        n += points;
+    }
+    if (t == 0) r.off[g] = n;
+}
+// Their points back to back.
+__global__ __launch_bounds__(256) void k_refused_gather(BatchArgs a, RefusedArgs r)
+{
+    for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < r.n; i += (int)(gridDim.x * 256)) {
+        int l = 0, u = r.g;
+        while (u - l > 1) {
+            const int m = (l + u) >> 1;
+            if (gld(r.off + m) <= i) l = m;
+            else u = m;
+        }
+        gst(r.xy + i, gld(a.xy + gld(a.start + gld(r.rset + l)) + (i - (int)gld(r.off + l))));
+    }
+}
+// Their hulls to where the batch's are, a workgroup per set.
+__global__ __launch_bounds__(256) void k_refused_put(BatchArgs a, RefusedArgs r)
+{
+    for (int k = (int)blockIdx.x; k < r.g; k += (int)gridDim.x) {
+        const int s = gld(r.rset + k), h = (int)(gld(r.out_off + k + 1) - gld(r.out_off + k));
+        const int32_t* src = r.out + gld(r.out_off + k);
+        int* dst = a.hbuf + gld(a.start + s);
+        for (int i = (int)threadIdx.x; i < h; i += 256) gst(dst + i, gld(src + i));
+        if (threadIdx.x == 0) a.hcnt[s] = h;
+    }
+}
+hipError_t launch_refused_gather(const BatchArgs& a, const RefusedArgs& r, int cus, hipStream_t st)
+{
+    k_refused_plan<<<1, 1024, 0, st>>>(a, r);
+    k_refused_gather<<<std::min((r.n + 255) / 256, 8 * cus), 256, 0, st>>>(a, r);
+    return hipGetLastError();
+}
+hipError_t launch_refused_put(const BatchArgs& a, const RefusedArgs& r, int cus, hipStream_t st)
+{
+    k_refused_put<<<std::min(r.g, 4 * cus), 256, 0, st>>>(a, r);
     return hipGetLastError();
 }
 

@@ -20,6 +20,9 @@ struct LocalStatus {
     unsigned long long orient, orient_exact, cmp_exact;
     unsigned long long t0, t1;  // device clock (100 MHz) at the call's start and end
     int pass_v[kLocalStatPasses], pass_s[kLocalStatPasses];
+    // launch_batch: sets that the batch kernels do not take (hcnt -1)
+    int refused;
+    int64_t refused_points;
     // launch_pre
     int pre_n;  // points kept (-1: a coordinate is not finite)
     unsigned long long pre_orient, pre_t0, pre_t1;
@@ -105,8 +108,11 @@ struct RingArgs {
 size_t ring_ctl_bytes();
 hipError_t launch_ring(const RingArgs& a, int cus, hipStream_t st, LaunchMark mark, void* ctx);
 
-// A batch of sets (at most kBatchSetMax points each; larger ones leave the
-// whole batch to the general path).
+// A batch of sets. Those of more than kBatchSetMax points, and those whose ring
+// cannot be cut, are refused: the general path takes them as a batch of their
+// own (launch_refused_gather, launch_refused_put). If they hold most of the
+// points, or the mode has no certificates for sets past one workgroup's LDS, it
+// takes the whole batch.
 constexpr int kBatchSetMax = 1 << 20;
 constexpr int kEngineSetMax = 1 << 18; // an engine's larger requests have launches of their own
 struct Pocket;
@@ -123,7 +129,7 @@ struct BatchArgs {
     LocalStatus* status;
     // workspace
     int* start;        // G + 1: set offsets
-    int* hcnt;         // G: hull sizes
+    int* hcnt;         // G: hull sizes (-1: refused)
     int* order;        // G: sets by size class
     int* hbuf;         // N: each set's hull from its first slot
     float4* slots;     // N: pocket points
@@ -143,6 +149,19 @@ struct BatchArgs {
 };
 size_t batch_ctl_bytes();
 hipError_t launch_batch(const BatchArgs& a, int cus, hipStream_t st);
-hipError_t launch_batch_emit(const BatchArgs& a, int cus, hipStream_t st);
+// (all: the refused sets have their hulls)
+hipError_t launch_batch_emit(const BatchArgs& a, int cus, hipStream_t st, int all = 0);
+// The refused sets, in order, as a batch: set r is rset[r], its points from
+// off[r] on of xy (n of them in g sets, as the status says).
+struct RefusedArgs {
+    int n, g;
+    int* rset;         // g
+    int64_t* off;      // g + 1
+    float2* xy;        // n
+    const int32_t* out;      // the batch's hulls ...
+    const int64_t* out_off;  // ... and their places (g + 1)
+};
+hipError_t launch_refused_gather(const BatchArgs& a, const RefusedArgs& r, int cus, hipStream_t st);
+hipError_t launch_refused_put(const BatchArgs& a, const RefusedArgs& r, int cus, hipStream_t st);
 
 }  // namespace sqh

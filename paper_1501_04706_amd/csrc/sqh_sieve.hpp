@@ -204,8 +204,9 @@ __device__ __forceinline__ int load_points(SolveLds<P>& L, const float2* xy, int
 
 // The hull of a set of n points: its ring in L.ring[0 .. h) (positions; L.id
 // gives the indices). Returns h, kSetDense (more than a quarter of the sample,
-// or more than P / 2 collected points, are vertices of their hull: nothing is
-// written) or kSetBad.
+// or more than P / 2 collected points, are vertices of their hull, or the sieve
+// thins the set so little that it would be solved P points at a time: nothing
+// is written) or kSetBad.
 //
 // Up to P points are solved as they are. A larger set is streamed past the
 // slabs of its sample's hull; the points left are collected in LDS. Should
@@ -276,6 +277,7 @@ __device__ __forceinline__ int solve_set(SolveLds<P>& L, const float2* xy, int n
                 for (int j = 0; j < U; ++j) nv[j] = gld(xy + min(at + t + T * j, n - 1));
             }
         };
+        const int from = pos;
         fetch(pos);
         while (pos < n) {
             // one step: U rows of T points, or one row where U might not fit
@@ -335,6 +337,12 @@ __device__ __forceinline__ int solve_set(SolveLds<P>& L, const float2* xy, int n
         if (__ballot(bad) && lane_id() == 0) L.bad = 1;
         fin = pos >= n;
         lds_barrier();
+        // (copies, or points on a line: 16 solves of 4096 of them take 0.25 ms,
+        // and a million 4 ms; other paths drop them at the first split)
+        if (n - pos > 16ll * (pos - from)) {
+            *sample = 0;
+            return L.bad ? kSetBad : kSetDense;
+        }
     }
 }
 

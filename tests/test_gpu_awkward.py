@@ -207,3 +207,94 @@ def test_sets_that_no_polygon_thins(H, n):
             assert "k_ring_pocket" not in names or name == "copies of 600", (name, names)
         # (a wave that sorts a thousand copies takes a millisecond)
         assert dict(launches).get("k_ring_pocket", 0.0) < 1.5, (name, launches)
+
+
+def awkward_sets():
+    """Sets that the batch kernels refuse, one by one."""
+    rng = np.random.default_rng(8)
+    rim = np.concatenate([workloads.circle(54_000, 3), workloads.disk(246_000, 4) * np.float32(0.95)])
+    heap = workloads.circle(90_000, 5)
+    heap[rng.random(len(heap)) < 0.6] = heap[11]
+    a = rng.permutation(200_000).astype(np.float32)
+    return {"rim": rim[rng.permutation(len(rim))].astype(np.float32), "heap": heap,
+            "line": np.stack([a, 2 * a], 1), "copies": copies(200_000, 3), "large": workloads.disk((1 << 20) + 1, 6)}
+
+
+AWKWARD = list(awkward_sets()) + ["all", "most"]
+
+
+def around_awkward(which):
+    sets = awkward_sets()
+    some = list(sets.values()) if which in ("all", "most") else [sets[which]]
+    few = [workloads.make(("square", "disk", "circle", "grid")[i % 4], n, i)
+           for i, n in enumerate([1, 7, 64, 900, 1024, 1025, 4097, 20_000, 30_000, 60_000] * (1 if which == "most" else 12))]
+    few += [np.zeros((0, 2), np.float32)]
+    at = len(few) // 2
+    return few[:at] + some[:1] + few[at:] + some[1:] + few[:3], [id(s) for s in some]
+
+
+@pytest.mark.parametrize("which", AWKWARD)
+def test_batch_with_awkward_sets(H, which):
+    # only the refused sets take the general path, unless they are most of it
+    import torch
+    say(f"batch with awkward sets: {which}")
+    parts, odd = around_awkward(which)
+    want = [hull(p) for p in parts]
+    H.set_launch_timing(True)
+    try:
+        got = batch(H, parts)
+        names = [k for k, _ in H.launch_times()]
+    finally:
+        H.set_launch_timing(False)
+    for s, w in enumerate(want):
+        assert got[s] == w, (s, len(parts[s]))
+    assert names[0] == "k_batch" and "k_hull<plain>" in names, names
+    assert ("k_refused" in names) == (which != "most"), names
+    # a short output: the offsets and the total are whole, nothing is written past it
+    off = np.zeros(len(parts) + 1, np.int64)
+    off[1:] = np.cumsum([len(p) for p in parts])
+    xy = torch.from_numpy(np.concatenate(parts, 0).astype(np.float32)).cuda()
+    flat = [v for w in want for v in w]
+    out = torch.full((len(flat),), -7, dtype=torch.int32, device="cuda")
+    out_off = torch.empty(len(parts) + 1, dtype=torch.int64, device="cuda")
+    ws = H.workspace(len(xy), len(parts))
+    rc, h = sqh.sqh_hull_batched(H.ctx, xy, torch.from_numpy(off).cuda(), len(parts), len(xy), out, out_off,
+                                 len(flat) - 9, ws, ws.numel())
+    assert rc == sqh.SQH_ECAPACITY and h == len(flat) and int(out_off[-1]) == h
+    assert [int(v) for v in out.cpu().numpy()] == flat[:-9] + [-7] * 9
+    # a bad point in a refused set, and in one that is not
+    for s in (next(i for i, p in enumerate(parts) if id(p) in odd), 3):
+        z = [p.copy() for p in parts]
+        z[s][len(z[s]) // 2, 1] = np.nan
+        with pytest.raises(sqh.SqhError) as e:
+            batch(H, z)
+        assert e.value.code == sqh.SQH_EINVAL
+
+
+@pytest.mark.parametrize("which", AWKWARD)
+def test_engine_step_with_awkward_requests(H, which):
+    say(f"engine step with awkward requests: {which}")
+    parts, odd = around_awkward(which)
+    bad = workloads.disk(30_000, 3)
+    bad[7, 0] = np.inf
+    parts = parts + [bad]
+    want = [None if p is bad else hull(p) for p in parts]
+    E = H.engine(1 << 23, 256, 1 << 22)
+    try:
+        for passes in (32, 16, 32):
+            for i, p in enumerate(parts):
+                assert E.admit(p, i)
+            E.launch(passes)
+            assert E.admit(parts[2], 999)  # (into the other half while the step runs)
+            E.finish()
+            for _ in range(64):  # (a step of 16 passes may leave residents)
+                if E.status()["resident"] + E.status()["staged"] == 0:
+                    break
+                E.step(passes)
+            got = dict(iter(E.poll, None))
+            for i, w in enumerate(want):
+                assert (got[i] is None) if w is None else ([int(v) for v in got[i]] == w), (passes, i, len(parts[i]))
+            assert [int(v) for v in got[999]] == want[2]
+            assert E.status()["free_slots"] == E.slots
+    finally:
+        E.close()
