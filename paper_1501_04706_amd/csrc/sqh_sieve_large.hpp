@@ -334,16 +334,18 @@ __global__ __launch_bounds__(1024) void k_polygon(SieveArgs a, int ne)
     const bool kp = !slab_inside(sl, bins, probe.x, probe.y) &&
                     !(h >= 3 && chain_inside(v[2], h, s_kb, s_line != 0, s_m[0], s_m[1], probe.x, probe.y,
                                              ctr.orient_exact));
-    // ... and how many of those are no copies of its vertices
-    bool copy = false;
-    if (kp && h >= 3)
-        for (int i = 0; i < h; ++i) copy |= v[2][i].x == probe.x && v[2][i].y == probe.y;
-    const uint64_t M = __ballot(kp), N = __ballot(kp && !copy);
-    if (lane == 0) {
-        atomicAdd(&s_keep, (int)__popcll(M));
-        atomicAdd(&s_new, (int)__popcll(N));
-    }
+    const uint64_t M = __ballot(kp);
+    if (lane == 0) atomicAdd(&s_keep, (int)__popcll(M));
     __syncthreads();
+    // ... and, where it matters, how many of those are no copies of its vertices
+    if (s_keep > 256) {  // (uniform)
+        bool copy = false;
+        if (kp && h >= 3)
+            for (int i = 0; i < h; ++i) copy |= v[2][i].x == probe.x && v[2][i].y == probe.y;
+        const uint64_t N = __ballot(kp && !copy);
+        if (lane == 0) atomicAdd(&s_new, (int)__popcll(N));
+        __syncthreads();
+    }
     if (t == 0) {
         ctl->h = h;
         ctl->kB = s_kb;
