@@ -147,6 +147,16 @@ int sqh_set_precision(sqh_ctx *ctx, int mode);
 int sqh_set_streaming(sqh_ctx *ctx, int on);
 
 /*
+ * Workgroup-local kernels (small sets in LDS, the sieve, rings, batches, the
+ * two-launch pre-filter, engine steps of many passes) on (on != 0, the
+ * default) or off. Off, a call runs on the streaming path where it qualifies
+ * (sqh_set_streaming) and else on the general path, whose phases the stats
+ * time one by one. The output is identical either way. Returns SQH_OK or
+ * SQH_EINVAL.
+ */
+int sqh_set_local(sqh_ctx *ctx, int on);
+
+/*
  * Pre-filter for calls on one set (sqh_hull, or a batch of one set; the
  * engine ignores it): the paper's first mode (section 4.2, Table 2's
  * Mode 1) takes extreme points in x and y and discards the points inside

@@ -184,6 +184,7 @@ struct sqh_ctx {
     int prefilter = 0;    // SQH_PREFILTER_*
     int variant = 0;      // SQH_VARIANT_*
     int stream = 1;       // large single hulls take the streaming path (SQH_STREAM=0 turns it off)
+    int local = 1;        // the workgroup-local kernels may be used (sqh_set_local)
     int spass_used[64];   // per size class: streaming passes the last call ran (-1: none yet)
     // per-launch timing (sqh_set_launch_timing): events before and after
     // each kernel of the last call, and the kernels' names
@@ -725,7 +726,7 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
     if (rc != SQH_OK) return rc;
     ctx->nl = 0;
     Spent spent;
-    const bool plain = !a.prefilter && !a.sorted && !ctx->trace;
+    const bool plain = ctx->local && !a.prefilter && !a.sorted && !ctx->trace;
     const bool sieve = a.line_ok && !a.fp64;  // static float32 certificates may be used
     // one set in plain mode. Up to kLocalPoints points: one workgroup, the
     // points in LDS, in every precision mode. More: past the sieve, unless
@@ -735,7 +736,7 @@ int run_tuned(sqh_ctx* ctx, const float* d_xy, int64_t N, int64_t nsets, const i
     // and to the streaming path above. (From 2^16 points the streaming switch
     // and a tuned path still choose.)
     bool ring = false;
-    const bool whole = nsets == 1 && !d_set_off && !a.sorted && !ctx->trace;
+    const bool whole = ctx->local && nsets == 1 && !d_set_off && !a.sorted && !ctx->trace;
     if (whole && !a.prefilter && N <= kLocalPoints) {
         HIP_OK(run_local(ctx, a, a.xy, nullptr, (int)N, d_out, out_cap, st));
         return collect_local(ctx, N, out_cap, h_total);
@@ -1439,6 +1440,13 @@ int sqh_set_streaming(sqh_ctx* c, int on)
     return SQH_OK;
 }
 
+int sqh_set_local(sqh_ctx* c, int on)
+{
+    if (!c) return SQH_EINVAL;
+    c->local = on != 0;
+    return SQH_OK;
+}
+
 size_t sqh_workspace_bytes(int64_t n_total, int64_t n_sets)
 {
     Layout L;
@@ -1827,7 +1835,8 @@ int sqh_engine_launch(sqh_engine* e, int max_passes, void* stream)
     // segment table and 1.6 ms so). Fewer passes ask for short steps in which
     // old and new requests share the table.
     e->max_passes = max_passes;
-    e->local = max_passes >= kLocalStepPasses && G > 0 && e->resident.empty() && c->line && !c->fp64;
+    e->local = max_passes >= kLocalStepPasses && G > 0 && e->resident.empty() && c->local && c->line &&
+               !c->fp64;
     const int rc = e->local ? eng_local(e, e->side, e->stage_used, st) : eng_general(e, e->side, e->stage_used, st);
     if (rc != SQH_OK) return rc;
     // later admissions fill the other staging half

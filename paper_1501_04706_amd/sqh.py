@@ -112,6 +112,8 @@ def load() -> ctypes.CDLL:
     lib.sqh_set_variant.restype = c_int
     lib.sqh_set_streaming.argtypes = [vp, c_int]
     lib.sqh_set_streaming.restype = c_int
+    lib.sqh_set_local.argtypes = [vp, c_int]
+    lib.sqh_set_local.restype = c_int
     lib.sqh_workspace_bytes_soa.argtypes = [i64]
     lib.sqh_workspace_bytes_soa.restype = ctypes.c_size_t
     lib.sqh_hull_soa.argtypes = [vp, vp, vp, i64, vp, i64, ctypes.POINTER(i64), vp, ctypes.c_size_t, vp]
@@ -218,6 +220,10 @@ def sqh_set_variant(ctx: int, variant: int) -> int:
 
 def sqh_set_streaming(ctx: int, on: int) -> int:
     return load().sqh_set_streaming(ctx, on)
+
+
+def sqh_set_local(ctx: int, on: int) -> int:
+    return load().sqh_set_local(ctx, on)
 
 
 def sqh_workspace_bytes_soa(n: int) -> int:
@@ -451,6 +457,11 @@ class Hull:
         rc = sqh_set_streaming(self.ctx, 1 if on else 0)
         if rc != SQH_OK:
             raise SqhError(rc, "sqh_set_streaming")
+
+    def set_local(self, on: bool):
+        rc = sqh_set_local(self.ctx, 1 if on else 0)
+        if rc != SQH_OK:
+            raise SqhError(rc, "sqh_set_local")
 
     def set_variant(self, variant: int):
         rc = sqh_set_variant(self.ctx, variant)
