@@ -271,9 +271,12 @@ int sqh_hull_batched(sqh_ctx *ctx, const float *d_xy, const int64_t *d_set_off, 
  * workgroups of the persistent kernel (all co-resident ones, 3/4, 1/2, 1/4)
  * times the tail threshold (0, 2^13, 2^16 points; at most 256 segments) below which one
  * workgroup finishes the remaining passes; for one set of at least 2^16
- * points (streaming on) also the streaming path with 1024, 512 or 256
- * workgroups per kernel. Later calls of any size use the
- * entry of the nearest class. The output of every shape is identical; only
+ * points that may take the streaming path also that path with 1024, 512 or 256
+ * workgroups per kernel. The shapes are timed with the workgroup-local kernels
+ * off: they serve the calls that those leave, graphs and engine steps. Whether
+ * such a set stays off the streaming path and the sieve ("stream": 0) is
+ * decided by its whole calls as they run; other problems store "stream": 1.
+ * Later calls of any size use the entry of the nearest class. The output of every shape is identical; only
  * time differs. Leaves the last candidate's result in d_out. Returns as
  * sqh_hull_batched, or SQH_ENOMEM when the context's table (40 classes) is
  * full. Synchronises the stream.

@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -1537,34 +1538,62 @@ int sqh_autotune(sqh_ctx* c, const float* d_xy, const int64_t* d_set_off, int64_
             cand[nc++].stream = 0;
         }
     }
-    if (n_sets == 1 && n_total >= kStreamMin && c->stream) {
+    if (n_sets == 1 && n_total >= kStreamMin && c->stream && !c->prefilter && c->variant == SQH_VARIANT_PARTITION &&
+        (reinterpret_cast<uintptr_t>(d_xy) & 15u) == 0) {
         for (const int sg : {kMaxSGrid, kMaxSGrid / 2, kMaxSGrid / 4}) {
             cand[nc] = TuneEntry{cls, m, kTailPoints};
             cand[nc].stream = 1;
             cand[nc++].sgrid = sg;
         }
     }
-    TuneEntry best{cls, m, kTailPoints};
-    double best_ms = 1e300;
     int64_t h = 0;
-    for (int ci = 0; ci < nc; ++ci) {
-        const TuneEntry& tu = cand[ci];
-        int rc = run_tuned(c, d_xy, n_total, n_sets, d_set_off, d_out, d_out_off, out_cap, &h, d_ws, ws_bytes, st,
-                           tu);  // warm-up
-        if (rc != SQH_OK) return rc;
+    auto call = [&](const TuneEntry& tu) {
+        return run_tuned(c, d_xy, n_total, n_sets, d_set_off, d_out, d_out_off, out_cap, &h, d_ws, ws_bytes, st, tu);
+    };
+    // median time of a call: on the device, or (wall) until it returns
+    auto median = [&](const TuneEntry& tu, bool wall, double& ms) {
+        int rc = call(tu);  // warm-up
         double t[100];
-        for (int r = 0; r < reps; ++r) {
-            rc = run_tuned(c, d_xy, n_total, n_sets, d_set_off, d_out, d_out_off, out_cap, &h, d_ws, ws_bytes, st,
-                           tu);
-            if (rc != SQH_OK) return rc;
-            t[r] = c->stats.ms_total;
+        for (int r = 0; r < reps && rc == SQH_OK; ++r) {
+            const auto t0 = std::chrono::steady_clock::now();
+            rc = call(tu);
+            t[r] = wall ? std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count()
+                        : c->stats.ms_total;
         }
+        if (rc != SQH_OK) return rc;
         std::sort(t, t + reps);
-        const double med = t[reps / 2];
-        if (med < best_ms) {
-            best_ms = med;
-            best = tu;
+        ms = t[reps / 2];
+        return rc;
+    };
+    // the shapes are those of the persistent and the streaming kernels, so the
+    // local kernels, which finish most calls without them, stay out of their times
+    const int local = c->local;
+    TuneEntry best[2] = {TuneEntry{cls, m, kTailPoints}, TuneEntry{cls, m, kTailPoints}};  // stream 0, 1
+    double best_ms[2] = {1e300, 1e300};
+    int rc = SQH_OK;
+    c->local = 0;
+    for (int ci = 0; ci < nc && rc == SQH_OK; ++ci) {
+        double ms = 0.0;
+        rc = median(cand[ci], false, ms);
+        const int k = cand[ci].stream;
+        if (rc == SQH_OK && ms < best_ms[k]) {
+            best_ms[k] = ms;
+            best[k] = cand[ci];
         }
+    }
+    c->local = local;
+    if (rc != SQH_OK) return rc;
+    // the path: of a set that has a choice, the faster one as its calls run;
+    // else none is tuned (an entry serves the sizes around it too)
+    TuneEntry pick = best[0];
+    pick.stream = 1;
+    if (best_ms[1] < 1e300) {
+        double ms[2];
+        for (int k = 0; k < 2; ++k) {
+            rc = median(best[k], true, ms[k]);
+            if (rc != SQH_OK) return rc;
+        }
+        pick = best[ms[1] <= ms[0] ? 1 : 0];
     }
     int slot = -1;
     for (int i = 0; i < c->ntune; ++i)
@@ -1573,7 +1602,7 @@ int sqh_autotune(sqh_ctx* c, const float* d_xy, const int64_t* d_set_off, int64_
         if (c->ntune >= sqh_ctx::kMaxTune) return SQH_ENOMEM;
         slot = c->ntune++;
     }
-    c->tune[slot] = best;
+    c->tune[slot] = pick;
     return SQH_OK;
 }
 

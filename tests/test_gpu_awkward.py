@@ -298,3 +298,37 @@ def test_engine_step_with_awkward_requests(H, which):
             assert E.status()["free_slots"] == E.slots
     finally:
         E.close()
+
+
+def test_autotune_times_the_shapes_it_stores(H):
+    # the shapes are those of the persistent kernel, which the local kernels
+    # spare most calls: it has to be the one that is timed, and an entry from a
+    # batch must not take a large single set off its path
+    import torch
+    say("autotune on a batch, a small set and a large one")
+    rng = np.random.default_rng(4)
+    parts = [workloads.make(("square", "disk", "circle")[i % 3], int(n), i)
+             for i, n in enumerate(rng.integers(500, 30_000, 70))]
+    off = np.zeros(len(parts) + 1, np.int64)
+    off[1:] = np.cumsum([len(p) for p in parts])
+    bxy, boff = torch.from_numpy(np.concatenate(parts, 0)).cuda(), torch.from_numpy(off).cuda()
+    xy = workloads.square(1_000_000, 3)
+    t = torch.from_numpy(xy).cuda()
+    assert H.tuning() == '{"entries": []}'
+    H.set_launch_timing(True)
+    try:
+        for args in ((bxy, boff), (t[:20_000],)):
+            text = H.autotune(*args, reps=1)
+            names = [k for k, _ in H.launch_times()]  # of the last candidate
+            assert names == ["k_reset", "k_hull<plain>"], names
+            assert '"stream": 0' not in text, text
+            assert [int(v) for v in H.hull(t).cpu().numpy()] == hull(xy)
+            assert "k_sieve_solve" in [k for k, _ in H.launch_times()]
+        text = H.autotune(t, reps=3)
+        assert text.count("log2n") == 3
+        # 0.09 ms past the sieve, at least 0.25 on the persistent kernel
+        assert '"log2n": 19' in text and '"stream": 0' not in text, text
+    finally:
+        H.set_launch_timing(False)
+        H.set_tuning('{"entries": []}')
+    assert batch(H, parts) == [hull(p) for p in parts]
