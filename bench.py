@@ -354,8 +354,11 @@ def bench_batched(H, sqh, torch, workloads, total, steps: int, warmup: int, seed
 def bench_breakdown(H, sqh, torch, workloads, steps: int = 5, warmup: int = 2) -> list:
     """Per-phase device time of single hulls at the paper's sizes (1M .. 20M
     points, square and disk), plain, with each pre-filter and in the sorted-
-    chain layout: the phase times come from the kernels' own clock stamps,
-    the total from HIP events. sort_bytes: the radix sort's algorithmic
+    chain layout. kernel (and Mpoints_per_s, subset, prefilter) are of the call
+    as it runs by default; the paper's sub-procedures (seed .. emit, passes,
+    survivors_total) and phased_kernel of the same call with the workgroup-local
+    kernels off, which have no such phases: the phase times come from the
+    kernels' own clock stamps, the total from HIP events. sort_bytes: the radix sort's algorithmic
     traffic (4 passes x (4 B key read + 12 B read + 12 B write) per point)."""
     modes = (("plain", sqh.SQH_PREFILTER_NONE, sqh.SQH_VARIANT_PARTITION),
              ("quad", sqh.SQH_PREFILTER_QUAD, sqh.SQH_VARIANT_PARTITION),
@@ -377,9 +380,18 @@ def bench_breakdown(H, sqh, torch, workloads, steps: int = 5, warmup: int = 2) -
                 for _ in range(steps):
                     H.hull(xy_d, out=out)
                     st = H.stats()
-                    for k in ("ms_kernel", "ms_prefilter", "ms_seed", "ms_split", "ms_first", "ms_sort", "ms_pass",
-                              "ms_emit"):
+                    for k in ("ms_kernel", "ms_prefilter"):
                         acc[k] = acc.get(k, 0.0) + st[k] / steps
+                H.set_local(False)
+                for _ in range(warmup):
+                    H.hull(xy_d, out=out)
+                for _ in range(steps):
+                    H.hull(xy_d, out=out)
+                    st = H.stats()
+                    acc["ms_phased_kernel"] = acc.get("ms_phased_kernel", 0.0) + st["ms_kernel"] / steps
+                    for k in ("ms_seed", "ms_split", "ms_first", "ms_sort", "ms_pass", "ms_emit"):
+                        acc[k] = acc.get(k, 0.0) + st[k] / steps
+                H.set_local(True)
                 row = {"kind": kind, "n": n, "mode": name,
                        "Mpoints_per_s": round(n / (acc["ms_kernel"] / 1000.0) / 1e6, 1),
                        "subset": int(st["prefilter_points"]), "passes": int(st["passes"]),
