@@ -129,19 +129,13 @@ __device__ __forceinline__ Slabs build_slabs(const float2* v, int h, float2* bin
     return s;
 }
 
-// The same polygon as two x-sorted chains, exactly: true if p is in the closed
-// polygon and at none of its vertices (so that it is no hull vertex; a copy of
-// a vertex stays). The lower and the upper edge over its x are certified by
-// the static line filter where it applies (line), else by the semi-static one;
-// the points neither certifies, long collinear runs on the border among them,
-// are settled exactly.
-__device__ __forceinline__ bool chain_inside(const float2* v, int h, int kB, bool line, float Mx, float My, float x,
-                                             float y, uint32_t& n_exact)
+// A polygon as two x-sorted chains: the last node of 0 .. kB - 1 at or left of x
+// (l0), and of kB .. h - 1 at or right of it (l1).
+__device__ __forceinline__ void chain_edges(const float2* v, int h, int kB, float x, int& l0, int& l1)
 {
-    const float2 A = v[0], B = v[kB];
-    if (!(x >= A.x && x <= B.x)) return false;
-    // the last node of 0 .. kB - 1 at or left of x, of kB .. h - 1 at or right of it
-    int l0 = 0, u0 = kB, l1 = kB, u1 = h;
+    int u0 = kB, u1 = h;
+    l0 = 0;
+    l1 = kB;
     for (int k = max(kB, h - kB); k > 1; k = (k + 1) >> 1) {
         const int m0 = (l0 + u0) >> 1, m1 = (l1 + u1) >> 1;
         const float x0 = v[m0].x, x1 = v[m1].x;
@@ -151,6 +145,33 @@ __device__ __forceinline__ bool chain_inside(const float2* v, int h, int kB, boo
         l1 = (o1 & g1) ? m1 : l1;
         u1 = (o1 & !g1) ? m1 : u1;
     }
+}
+
+// Whether p is at a vertex of the polygon: at an end of its edges over p's x.
+__device__ __forceinline__ bool chain_copy(const float2* v, int h, int kB, float x, float y)
+{
+    if (!(x >= v[0].x && x <= v[kB].x)) return false;
+    int l0, l1;
+    chain_edges(v, h, kB, x, l0, l1);
+    const float2 q[4] = {v[l0], v[l0 + 1], v[l1], v[l1 + 1 < h ? l1 + 1 : 0]};
+    bool at = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) at |= q[i].x == x && q[i].y == y;
+    return at;
+}
+
+// The same, exactly: true if p is in the closed polygon and at none of its
+// vertices (so that it is no hull vertex; a copy of a vertex stays). The lower and the upper edge over its x are certified by
+// the static line filter where it applies (line), else by the semi-static one;
+// the points neither certifies, long collinear runs on the border among them,
+// are settled exactly.
+__device__ __forceinline__ bool chain_inside(const float2* v, int h, int kB, bool line, float Mx, float My, float x,
+                                             float y, uint32_t& n_exact)
+{
+    const float2 A = v[0], B = v[kB];
+    if (!(x >= A.x && x <= B.x)) return false;
+    int l0, l1;
+    chain_edges(v, h, kB, x, l0, l1);
     const float2 o[2] = {v[l0], v[l1]}, e[2] = {v[l0 + 1], v[l1 + 1 < h ? l1 + 1 : 0]};
     bool sure = x > A.x && x < B.x, out = false;
 #pragma unroll

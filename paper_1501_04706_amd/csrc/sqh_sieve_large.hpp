@@ -339,9 +339,7 @@ __global__ __launch_bounds__(1024) void k_polygon(SieveArgs a, int ne)
     __syncthreads();
     // ... and, where it matters, how many of those are no copies of its vertices
     if (s_keep > 256) {  // (uniform)
-        bool copy = false;
-        if (kp && h >= 3)
-            for (int i = 0; i < h; ++i) copy |= v[2][i].x == probe.x && v[2][i].y == probe.y;
+        const bool copy = kp && h >= 3 && chain_copy(v[2], h, s_kb, probe.x, probe.y);
         const uint64_t N = __ballot(kp && !copy);
         if (lane == 0) atomicAdd(&s_new, (int)__popcll(N));
         __syncthreads();
