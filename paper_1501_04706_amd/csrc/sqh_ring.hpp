@@ -554,8 +554,11 @@ struct NodesLds {
 // every other one tests a node against those m / 4, m / 8, .. places away (any
 // two nodes around it will do as long as they are less than half a turn apart),
 // which takes such a stretch at once (two circles of 1M points side by side:
-// 20 ms of rounds without).
-template <int T, bool RING, typename Buf>
+// 20 ms of rounds without). SWEEP: no round before needs to take a node, as in
+// a list whose pieces went through their own rounds; the places apart go from
+// m / 4 to 1 and round again, until neighbours agree (five lobes of a star, 3M
+// points: 1.5 ms of the join without).
+template <int T, bool RING, bool SWEEP = false, typename Buf>
 __device__ __forceinline__ int ring_rounds(const Buf& buf, int m, float2 c, int& f, int* red, Counters& ctr)
 {
     constexpr int W = T / 64, kRows = 32;
@@ -564,7 +567,10 @@ __device__ __forceinline__ int ring_rounds(const Buf& buf, int m, float2 c, int&
     int far = 0;
     for (int round = 0;; ++round) {
         int step = 1;
-        if (round >= 8 && (round & 1)) {
+        if (SWEEP) {
+            far = far < 2 ? m >> 2 : min(far >> 1, m >> 2);
+            step = max(far, 1);
+        } else if (round >= 8 && (round & 1)) {
             far = min(far < 2 ? m : far >> 1, m >> 2);
             step = max(far, 1);
         }
@@ -821,7 +827,7 @@ __global__ __launch_bounds__(1024) void k_ring_join(RingArgs a)
         __syncthreads();
         const NodesGlobal list = {{a.slots2, a.slots}};
         int f;
-        h = ring_rounds<1024, true>(list, h, c, f, red, ctr);
+        h = ring_rounds<1024, true, true>(list, h, c, f, red, ctr);
         buf = f ^ 1;
         for (int j = t; j < h; j += 1024) {
             const float4 p = list.get(f, j), q = list.get(f, j + 1 < h ? j + 1 : 0);

@@ -332,3 +332,16 @@ def test_autotune_times_the_shapes_it_stores(H):
         H.set_launch_timing(False)
         H.set_tuning('{"entries": []}')
     assert batch(H, parts) == [hull(p) for p in parts]
+
+
+@pytest.mark.parametrize("lobes", [2, 5, 40])
+@pytest.mark.parametrize("n", [30_000, 300_000])
+def test_stars(H, n, lobes):
+    # lobes around the centre: whole wedges between them empty, so that the join
+    # has to go over the ring at once (0.81 ms at five lobes of 300K points)
+    say(f"star of {lobes} lobes n={n}")
+    t = np.random.default_rng(lobes).random(n) * 2 * np.pi
+    r = 1 + 0.3 * np.cos(lobes * t)
+    got, launches, _ = timed_hull(H, np.stack([r * np.cos(t), r * np.sin(t)], 1).astype(np.float32))
+    assert got == hull(np.stack([r * np.cos(t), r * np.sin(t)], 1).astype(np.float32))
+    assert dict(launches).get("k_ring_join", 0.0) < 0.7, launches
