@@ -388,6 +388,13 @@ __device__ __forceinline__ bool cut_pockets(const BatchArgs& a, SolveLds<P>& L, 
     return true;
 }
 
+// A set left to the general path.
+__device__ __noinline__ void refuse(BatchCtl* ctl, int n)
+{
+    atomicAdd(&ctl->n_refused, 1);
+    atomicAdd(&ctl->refused_points, (unsigned long long)n);
+}
+
 // Larger sets, the largest first. (Two workgroups of 512 threads and 2048 points
 // to a compute unit, so that one fills the other's waits, took as long, and
 // their smaller samples cut less even pockets.)
@@ -417,10 +424,7 @@ __global__ __launch_bounds__(kMidT) void k_batch_big(BatchArgs a)
             const bool ok = sample > 0 && cut_pockets<T, P>(a, L, sample, s, base, n, ctr);
             if (L.bad) h = kSetBad;
             else if (ok) h = 0;
-            else if (threadIdx.x == 0) {  // (h: -1)
-                atomicAdd(&ctl->n_refused, 1);
-                atomicAdd(&ctl->refused_points, (unsigned long long)n);
-            }
+            else if (threadIdx.x == 0) refuse(ctl, n);  // (h: -1)
         }
         put_hull(a, s, base, h, L.id, L.ring, T);
         lds_barrier();

@@ -76,7 +76,7 @@ __device__ __forceinline__ Slabs build_slabs(const float2* v, int h, float2* bin
     Slabs s;
     s.last = (uint32_t)(NB - 1);
     s.scale = ((float)(NB - 2) + 0x1p-5f) / ext;
-    const bool ok = ext > 0x1p-100f && ext < 0x1p100f;
+    const bool ok = ext > 0x1p-100f && ext < 0x1p126f;
     if (!ok) {
         s.scale = 0.0f;
         s.x0 = 0.0f;
@@ -360,7 +360,7 @@ __device__ __forceinline__ int solve_set(SolveLds<P>& L, const float2* xy, int n
         lds_barrier();
         // (copies, or points on a line: 16 solves of 4096 of them take 0.25 ms,
         // and a million 4 ms; other paths drop them at the first split)
-        if (n - pos > 16ll * (pos - from)) {
+        if ((n - pos) / 16 > pos - from) {  // (uniform)
             *sample = 0;
             return L.bad ? kSetBad : kSetDense;
         }

@@ -125,6 +125,19 @@ __device__ __forceinline__ bool farther_exact(float2 o, float2 e, float2 p, int 
 // ---- the solver ----
 
 constexpr int kSolvePasses = 64;  // passes whose sizes are noted
+// Coordinates beyond this make a set's areas be bounded by the high words of
+// float64 intervals (a point's products may overflow in float32, and with no
+// bounds every point challenges its child's leader exactly: 35K points scaled
+// by 1e34 took a batch 25 ms).
+constexpr float kWideFrom = 0x1p62f;
+// The bounds: the smaller one in the low word. Out of line, so that the float32
+// form keeps its registers (inlined it cost k_batch_big 4 %).
+__device__ __noinline__ uint64_t area_bounds64(float ox, float oy, float ex, float ey, float px, float py)
+{
+    double m;
+    const double d = -orient64(ox, oy, ex, ey, px, py, m);
+    return ((uint64_t)((uint32_t)__double2hiint(d + m) + 1u) << 32) | (uint32_t)__double2hiint(fmax(d - m, 0.0));
+}
 constexpr uint16_t kNoNext = 0xffffu;
 
 struct LSegIdx {
@@ -157,6 +170,7 @@ struct SolveLds {
     int ns[2], any[2], beat[2];
     int live[2];           // lengths of the lists
     int bad;
+    int wide;              // a coordinate is so large that float32 products may overflow
 };
 
 // What a call adds up over the sets one workgroup solves.
@@ -197,8 +211,10 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bo
         L.beat[0] = 0; L.beat[1] = 0;
         L.live[0] = cnt; L.live[1] = 0;
         L.map[0] = 0;
+        L.wide = 0;
     }
     lds_barrier();
+    bool big = false;
     // the first segment's "farthest point" is B itself: its children are the
     // sides of A -> B and, for a set, of B -> A
     int ic = ib;
@@ -209,6 +225,7 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bo
         for (int r = 0; r < R; ++r) {
             const int i = t + T * r;
             const float2 p = i < cnt ? L.xy[i] : make_float2(0.0f, 0.0f);
+            big |= fmaxf(fabsf(p.x), fabsf(p.y)) > kWideFrom;
             // (+ 0.0f: -0 counts as +0)
             k[r] = ((uint64_t)order_key(p.x + 0.0f) << 32) | order_key(p.y + 0.0f);
             if (i < cnt) {
@@ -216,6 +233,7 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bo
                 hi = k[r] > hi ? k[r] : hi;
             }
         }
+        if (__ballot(big) && lane == 0) L.wide = 1;
         lo = wave_min_u64(lo);
         hi = wave_max_u64(hi);
         if (lane == 63) {
@@ -242,6 +260,13 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bo
         }
         ic = ib;
         ib = ia;
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = t + T * r;
+            if (i < cnt) big |= fmaxf(fabsf(L.xy[i].x), fabsf(L.xy[i].y)) > kWideFrom;
+        }
+        if (__ballot(big) && lane == 0) L.wide = 1;
     }
     if (t == 0) {
         LSegIdx g;
@@ -249,6 +274,8 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bo
         L.seg[0][0] = g;
     }
     lds_barrier();
+    // the bounds of areas in float64, where float32 has none (or may not be asked)
+    const bool wide = f64 || L.wide != 0;
     int nodes = WHOLE ? 1 : 0;  // (pass 0 adds B to a ring, or counts A)
     int pass = 0;
     for (;; ++pass) {
@@ -321,6 +348,12 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bo
                 // a NaN (overflow) leaves the whole range
                 lok[r] = __float_as_uint(fmaxf(a - w, 0.0f));
                 hik[r] = __float_as_uint(fminf(a + w, INFINITY));
+                if (wide) {  // (uniform)
+                    const float2 o = in0 ? A[k] : C[k], e = in0 ? C[k] : B[k];
+                    const uint64_t b = area_bounds64(o.x, o.y, e.x, e.y, p[r].x, p[r].y);
+                    lok[r] = (uint32_t)b;
+                    hik[r] = (uint32_t)(b >> 32);
+                }
                 ch[r] = in ? 2 * lab[k] + (in0 ? 0 : 1) : -1;
                 key[k] = ((uint64_t)lok[r] << 32) | (uint32_t)~pos[r];
                 top[k] = L.key[max(ch[r], 0)];
@@ -354,7 +387,7 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bo
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const bool m = (ch[r] >= 0) & ((int)~(uint32_t)top[r] != pos[r]) &
-                               (f64 | (hik[r] >= (uint32_t)(top[r] >> 32)));
+                               (hik[r] >= (uint32_t)(top[r] >> 32));
                 cand |= (uint32_t)m << r;
             }
         }

@@ -345,3 +345,29 @@ def test_stars(H, n, lobes):
     got, launches, _ = timed_hull(H, np.stack([r * np.cos(t), r * np.sin(t)], 1).astype(np.float32))
     assert got == hull(np.stack([r * np.cos(t), r * np.sin(t)], 1).astype(np.float32))
     assert dict(launches).get("k_ring_join", 0.0) < 0.7, launches
+
+
+@pytest.mark.parametrize("mode", [sqh.SQH_FP32_FILTER, sqh.SQH_FP64_ONLY])
+@pytest.mark.parametrize("n", [500, 4000, 35_000])
+def test_overflowing_areas_are_elected_by_bounds(H, n, mode):
+    # where float32 has no bounds for an area, float64 has: few points challenge
+    # their child's leader exactly (all of them did: 25 ms a batch at 35K points)
+    rng = np.random.default_rng(n)
+    t = rng.random(n) * 2 * np.pi
+    two = np.stack([np.cos(t), np.sin(t)], 1) * np.where(rng.random(n) < 0.5, 1.0, 1e-2)[:, None]
+    two[rng.random(n) < 0.5] += [3.0, 1.0]
+    H.set_precision(mode)
+    try:
+        for name, unit in (("circles", two), ("disk", workloads.disk(n, 3)), ("square", workloads.square(n, 4))):
+            for scale in (1.0, 2.0 ** 62, 2.0 ** 90, 2.0 ** 125):
+                say(f"areas by float64 bounds: {name} n={n} scale={scale:.3g} mode={mode}")
+                xy = (unit.astype(np.float64) * scale).astype(np.float32)
+                want = hull(xy)
+                assert batch(H, [xy, workloads.square(2000, 1), xy[:7]])[0] == want
+                if n <= 4096:
+                    import torch
+                    assert [int(v) for v in H.hull(torch.from_numpy(xy).cuda()).cpu().numpy()] == want
+                    # (copies and near ties aside; every point of every pass before)
+                    assert H.stats()["cmp_exact"] <= 50 + n // 4, H.stats()["cmp_exact"]
+    finally:
+        H.set_precision(sqh.SQH_FP32_FILTER)
