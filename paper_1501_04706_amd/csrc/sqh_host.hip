@@ -673,9 +673,12 @@ struct Spent {
 int run_refused(sqh_ctx* ctx, const HullArgs& a, const BatchArgs& b, const TuneEntry& tu, hipStream_t st, Spent& spent)
 {
     const int64_t n = ctx->lstat->refused_points, g = ctx->lstat->refused;
-    const size_t off_bytes = sizeof(int64_t) * (size_t)(g + 1);
-    if (3 * n > 2 * (int64_t)a.N || 8 * g > 7 * (int64_t)a.G ||
-        2 * off_bytes + sizeof(int) * (size_t)(2 * g + 1) > sizeof(int) * (size_t)kSortBuckets * (size_t)kMaxGrid) {
+    // (one set alone gets an empty one beside it: single sets of up to 2^15
+    // points are one workgroup's there, 25000 points of a ring 3 ms instead of 1)
+    const int64_t g2 = std::max<int64_t>(g, 2);
+    const size_t off_bytes = sizeof(int64_t) * (size_t)(g2 + 1);
+    if (3 * n > 2 * (int64_t)a.N || 8 * g2 > 7 * (int64_t)a.G ||
+        2 * off_bytes + sizeof(int) * (size_t)(g + g2 + 1) > sizeof(int) * (size_t)kSortBuckets * (size_t)kMaxGrid) {
         ctx->lstat->left = 3;
         return SQH_OK;
     }
@@ -689,7 +692,7 @@ int run_refused(sqh_ctx* ctx, const HullArgs& a, const BatchArgs& b, const TuneE
     HullArgs q = a;
     q.xy = r.xy;
     q.N = r.n;
-    q.G = r.g;
+    q.G = (int)g2;
     q.set_off = r.off;
     q.out = reinterpret_cast<int32_t*>(a.xy2 + n);
     q.cap = n;
@@ -701,7 +704,7 @@ int run_refused(sqh_ctx* ctx, const HullArgs& a, const BatchArgs& b, const TuneE
     if (time_open(ctx, "k_refused", st) != SQH_OK) return SQH_EDEVICE;
     HIP_OK(launch_refused_gather(b, r, ctx->cus, st));
     if (time_close(ctx, "k_refused", st) != SQH_OK) return SQH_EDEVICE;
-    const int64_t work = std::max<int64_t>(q.W, 4 * g);
+    const int64_t work = std::max<int64_t>(q.W, 4 * g2);
     int rc = enqueue(ctx, q, (int)std::min<int64_t>(2048, (work + 255) / 256), tu.grid, tu.sgrid, st);
     if (rc != SQH_OK) return rc;
     rc = collect(ctx, q, n, n, nullptr, st, false);

@@ -726,7 +726,10 @@ __global__ __launch_bounds__(1024) void k_refused_plan(BatchArgs a, RefusedArgs 
         g += sets;
         n += points;
     }
-    if (t == 0) r.off[g] = n;
+    if (t == 0) {
+        r.off[g] = n;
+        if (g == 1) r.off[2] = n;
+    }
 }
 // Their points back to back.
 __global__ __launch_bounds__(256) void k_refused_gather(BatchArgs a, RefusedArgs r)

@@ -156,7 +156,7 @@ hipError_t launch_batch_emit(const BatchArgs& a, int cus, hipStream_t st, int al
 struct RefusedArgs {
     int n, g;
     int* rset;         // g
-    int64_t* off;      // g + 1
+    int64_t* off;      // g + 1 (3 if g is 1)
     float2* xy;        // n
     const int32_t* out;      // the batch's hulls ...
     const int64_t* out_off;  // ... and their places (g + 1)
