@@ -130,6 +130,7 @@ struct alignas(128) BatchStats {
 };
 struct BatchCtl {
     int err, left;
+    int stop;  // err | left as k_batch_init found them: for kernels that set err themselves
     int n_refused;
     unsigned long long refused_points;
     int n_small, n_big;         // queue lengths: class 0; classes 5 .. 1
@@ -227,8 +228,11 @@ __global__ __launch_bounds__(1024) void k_batch_init(BatchArgs a)
         __syncthreads();
     }
     if (t == 0) {
-        ctl->err = s_err ? kErrBounds : 0;
-        ctl->left = ((s_left || 3 * s_over_points > 2ull * (unsigned long long)a.N) && !s_err) ? 1 : 0;
+        const int err = s_err ? kErrBounds : 0;
+        const int left = ((s_left || 3 * s_over_points > 2ull * (unsigned long long)a.N) && !s_err) ? 1 : 0;
+        ctl->err = err;
+        ctl->left = left;
+        ctl->stop = err | left;
         ctl->n_refused = s_over;
         ctl->refused_points = s_over_points;
         ctl->t0 = wall_clock64();
@@ -256,7 +260,7 @@ __global__ __launch_bounds__(kSmallT, 4) void k_batch_small(BatchArgs a)
     __shared__ SolveLds<kSmallP> L;
     __shared__ BatchAcc A;
     const BatchCtl* ctl = a.ctl;
-    if (call_ended(&ctl->err, &ctl->left)) return;
+    if (ctl->stop) return;
     Counters ctr = {0u, 0u, 0u};
     acc_init(A);
     const int ns = ctl->n_small, nb = ctl->n_big;
@@ -405,7 +409,7 @@ __global__ __launch_bounds__(kMidT) void k_batch_big(BatchArgs a)
     __shared__ BatchAcc A;
     __shared__ int s_i;
     BatchCtl* ctl = a.ctl;
-    if (call_ended(&ctl->err, &ctl->left)) return;
+    if (ctl->stop) return;
     Counters ctr = {0u, 0u, 0u};
     acc_init(A);
     const int nb = ctl->n_big;

@@ -99,7 +99,8 @@ __device__ __forceinline__ int bits_below(uint64_t M)
 // wave of the workgroup: one thread reads the words, because a kernel whose
 // workgroups also set them may have set them between two waves' own reads, and
 // a workgroup that goes on without some of its waves works on LDS they never
-// wrote. Every thread calls it; it holds a barrier.
+// wrote. Every thread calls it; it holds a barrier. (A word that the kernel does
+// not set can be read by each wave: BatchCtl::stop.)
 __device__ __forceinline__ bool call_ended(const int* err, const int* left)
 {
     __shared__ int s_ended;

@@ -9,7 +9,7 @@ import re
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1501_04706_amd", "csrc")
-WORDS = ("err", "left")
+WORDS = ("err", "left", "stop")
 FILES = [os.path.join(CSRC, f) for f in ("sqh_local.hip", "sqh_ring.hpp", "sqh_sieve_large.hpp", "sqh_subset.hpp",
                                          "sqh_sieve.hpp", "sqh_dense.hpp", "sqh_solve.hpp")]
 
