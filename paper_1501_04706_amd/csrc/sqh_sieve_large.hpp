@@ -32,6 +32,7 @@ constexpr int kExtremeGrid = 256;  // workgroups of k_extreme, at most
 constexpr int kSieveT = 512;
 constexpr int kSieveGrid = 1024;   // workgroups of the sieve, at most
 constexpr int kRestOne = 1 << 16;  // up to this many points left one workgroup takes them
+constexpr int kRestRaw = 256;      // points of a workgroup's share that are few
 constexpr int kRestHull = 1024;    // hulls of more vertices are left to other paths
 constexpr int kFlatMost = 1 << 18; // sets of copies or on a line: up to this many points stay
 
@@ -752,74 +753,88 @@ __global__ __launch_bounds__(kMidT) void k_rest(SieveArgs a, int ns, int per, in
         rest_finish<kMidT, kMidP>(a, L, h, M, st, ctr, csum);
         return;
     }
-    int nc;
-    if (second && M <= kRestOne) {
-        // workgroup b's share against the second polygon
-        nc = nb;
-        float2* v = L.bins;  // (free between solves)
-        const float2* all = a.ids ? a.all : a.xy;
-        if (t < 64) {
+    const bool thin = second && M <= kRestOne;
+    const int nc = thin ? nb : (M + kMidP - 1) / kMidP;
+    for (int c = b; c < nc; c += nb) {
+        int cnt;
+        lds_barrier();
+        if (thin) {
+            // workgroup b's share against the second polygon (one list each)
+            float2* v = L.bins;  // (free between solves)
+            const float2* all = a.ids ? a.all : a.xy;
+            if (t < 64) {
 #pragma unroll
-            for (int k = 0; k < kDirs2 / 64; ++k) v[lane + 64 * k] = gld(all + (uint32_t)ctl->best2[lane + 64 * k]);
-            wave_sync();
-            const int p = wave_polygon(v, v + kDirs2, kDirs2, v + 2 * kDirs2, ctr);
-            float mx, my, ext;
-            wave_extent(v + 2 * kDirs2, p, mx, my, ext);
-            uint64_t hi = 0ull;
-            int at = 0;
-            for (int i = lane; i < p; i += 64) {
-                const float2 q = v[2 * kDirs2 + i];
-                const uint64_t k = ((uint64_t)order_key(q.x + 0.0f) << 32) | order_key(q.y + 0.0f);
-                if (k > hi) { hi = k; at = i; }
+                for (int k = 0; k < kDirs2 / 64; ++k) v[lane + 64 * k] = gld(all + (uint32_t)ctl->best2[lane + 64 * k]);
+                wave_sync();
+                const int p = wave_polygon(v, v + kDirs2, kDirs2, v + 2 * kDirs2, ctr);
+                float mx, my, ext;
+                wave_extent(v + 2 * kDirs2, p, mx, my, ext);
+                uint64_t hi = 0ull;
+                int at = 0;
+                for (int i = lane; i < p; i += 64) {
+                    const float2 q = v[2 * kDirs2 + i];
+                    const uint64_t k = ((uint64_t)order_key(q.x + 0.0f) << 32) | order_key(q.y + 0.0f);
+                    if (k > hi) { hi = k; at = i; }
+                }
+                const uint64_t top = wave_max_u64(hi);
+                if (lane == 63) { s_m[0] = mx; s_m[1] = my; s_at[0] = 0; s_at[1] = p >= 3 && line_domain(mx, my, ext); s_next[0] = p; }
+                const uint64_t who = __ballot(hi == (((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(top >> 32), 63) << 32) |
+                                                     (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)top, 63)));
+                if (lane == (int)__builtin_ctzll(who)) s_next[1] = at;  // the lexicographic maximum
             }
-            const uint64_t top = wave_max_u64(hi);
-            if (lane == 63) { s_m[0] = mx; s_m[1] = my; s_at[0] = 0; s_at[1] = p >= 3 && line_domain(mx, my, ext); s_next[0] = p; }
-            const uint64_t who = __ballot(hi == (((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(top >> 32), 63) << 32) |
-                                                 (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)top, 63)));
-            if (lane == (int)__builtin_ctzll(who)) s_next[1] = at;  // the lexicographic maximum
-        }
-        __syncthreads();
-        const int p = s_next[0], kB = s_next[1];
-        const bool line = s_at[1] != 0;
-        const float mx = s_m[0], my = s_m[1];
-        for (int i0 = b * kMidT; i0 < M; i0 += nb * kMidT) {
-            const int i = i0 + t;
-            const size_t d = rest_place(s_pre, ns, per, a.n, min(i, M - 1));
-            const float2 q = make_float2(gld(a.X[1] + d), gld(a.Y[1] + d));
-            const int id = gld(a.I[1] + d);
-            const bool kp = i < M && !(p >= 3 && chain_inside(v + 2 * kDirs2, p, kB, line, mx, my, q.x, q.y,
-                                                              ctr.orient_exact));
-            const uint64_t K = __ballot(kp);
-            if (!K) continue;
-            int at = 0;
-            if (lane == 0) at = atomicAdd(&s_at[0], (int)__popcll(K));
-            at = __builtin_amdgcn_readfirstlane(at) + bits_below(K);
-            if (kp && at < kMidP) {
-                gst(a.lxy + (size_t)b * kMidP + at, q);
-                gst(a.lid + (size_t)b * kMidP + at, id);
+            __syncthreads();
+            const int p = s_next[0], kB = s_next[1];
+            const bool line = s_at[1] != 0;
+            const float mx = s_m[0], my = s_m[1];
+            for (int i0 = b * kMidT; i0 < M; i0 += nb * kMidT) {
+                const int i = i0 + t;
+                const size_t d = rest_place(s_pre, ns, per, a.n, min(i, M - 1));
+                const float2 q = make_float2(gld(a.X[1] + d), gld(a.Y[1] + d));
+                const int id = gld(a.I[1] + d);
+                const bool kp = i < M && !(p >= 3 && chain_inside(v + 2 * kDirs2, p, kB, line, mx, my, q.x, q.y,
+                                                                  ctr.orient_exact));
+                const uint64_t K = __ballot(kp);
+                if (!K) continue;
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&s_at[0], (int)__popcll(K));
+                at = __builtin_amdgcn_readfirstlane(at) + bits_below(K);
+                if (kp && at < kMidP) {
+                    L.xy[at] = q;
+                    L.id[at] = id;
+                    if (at < kRestRaw) {
+                        gst(a.lxy + (size_t)c * kMidP + at, q);
+                        gst(a.lid + (size_t)c * kMidP + at, id);
+                    }
+                }
             }
-        }
-        __syncthreads();
-        if (t == 0) gst(a.lcnt + b, s_at[0] <= kMidP ? s_at[0] : kMidP + 1);
-    } else {
-        nc = (M + kMidP - 1) / kMidP;
-        for (int c = b; c < nc; c += nb) {
-            const int c0 = c * kMidP, cnt = min(kMidP, M - c0);
-            lds_barrier();
+            __syncthreads();
+            cnt = s_at[0];
+            if (cnt > kMidP) {  // (uniform)
+                if (t == 0) gst(a.lcnt + c, kMidP + 1);
+                continue;
+            }
+        } else {
+            const int c0 = c * kMidP;
+            cnt = min(kMidP, M - c0);
             for (int i = t; i < cnt; i += kMidT) {
                 const size_t q = rest_place(s_pre, ns, per, a.n, c0 + i);
                 L.xy[i] = make_float2(gld(a.X[1] + q), gld(a.Y[1] + q));
                 L.id[i] = gld(a.I[1] + q);
             }
             lds_barrier();
-            const int h = solve<kMidT, kMidP, true>(L, cnt, 0, 0, false, ctr, nullptr);
+        }
+        // what the second polygon thins goes on as it is; what it does not (copies
+        // of its vertices: 57K points made the last workgroup solve 14 times, 1.5 ms)
+        int h = cnt;
+        if (!thin || cnt > kRestRaw) {
+            h = solve<kMidT, kMidP, true>(L, cnt, 0, 0, false, ctr, nullptr);
             for (int r = t; r < h; r += kMidT) {
                 const int q = L.ring[r];
-                gst(a.lxy + (size_t)c0 + r, L.xy[q]);
-                gst(a.lid + (size_t)c0 + r, L.id[q]);
+                gst(a.lxy + (size_t)c * kMidP + r, L.xy[q]);
+                gst(a.lid + (size_t)c * kMidP + r, L.id[q]);
             }
-            if (t == 0) gst(a.lcnt + c, h);
         }
+        if (t == 0) gst(a.lcnt + c, h);
     }
     ctr_flush(ctl->ctr, ctr, csum);
     ctr = Counters{0u, 0u, 0u};

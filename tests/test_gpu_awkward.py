@@ -374,3 +374,19 @@ def test_overflowing_areas_are_elected_by_bounds(H, n, mode):
                     assert H.stats()["cmp_exact"] <= 50 + n // 4, H.stats()["cmp_exact"]
     finally:
         H.set_precision(sqh.SQH_FP32_FILTER)
+
+
+def test_copies_that_the_second_polygon_keeps(H):
+    # 2M points in 340 places: some 50 thousand copies of the hull's vertices pass
+    # both polygons, and one workgroup solved them 4096 at a time (1.5 ms), each
+    # time electing among hundreds of copies by position
+    rng = np.random.default_rng(7)
+    n = 2_000_000
+    places = rng.random((340, 2)).astype(np.float32)
+    xy = places[rng.integers(0, 340, n)]
+    xy[rng.random(n) < 0.28] = [0.5, 0.4375]
+    say(f"copies past both polygons n={n}")
+    got, launches, st = timed_hull(H, xy)
+    assert got == hull(xy)
+    assert dict(launches)["k_rest"] < 0.5, launches
+    assert 4096 < st["first_survivors"] <= 65536
