@@ -130,7 +130,9 @@ constexpr int kSolvePasses = 64;  // passes whose sizes are noted
 // float64 intervals (a point's products may overflow in float32, and with no
 // bounds every point challenges its child's leader exactly: 35K points scaled
 // by 1e34 took a batch 25 ms).
-constexpr float kWideFrom = 0x1p62f;
+// So are sets whose coordinates all stay below kFineFrom: their areas come near
+// the bounds' underflow margin of 2^-140 (742K points scaled by 1e-23: 8.4 ms).
+constexpr float kWideFrom = 0x1p62f, kFineFrom = 0x1p-56f;
 // The bounds: the smaller one in the low word. Out of line, so that the float32
 // form keeps its registers (inlined it cost k_batch_big 4 %).
 __device__ __noinline__ uint64_t area_bounds64(float ox, float oy, float ex, float ey, float px, float py)
@@ -171,7 +173,7 @@ struct SolveLds {
     int ns[2], any[2], beat[2];
     int live[2];           // lengths of the lists
     int bad;
-    int wide;              // a coordinate is so large that float32 products may overflow
+    int wide, fine;        // a coordinate is so large that float32 products may overflow; one is no tiny number
 };
 
 // What a call adds up over the sets one workgroup solves.
@@ -179,6 +181,16 @@ struct SolveStats {
     int passes;                                  // passes after the first compaction (the largest of them)
     int pass_v[kSolvePasses], pass_s[kSolvePasses];
 };
+
+template <int P>
+__device__ __forceinline__ void note_scale(SolveLds<P>& L, float top)
+{
+    const bool w = __ballot(top > kWideFrom) != 0ull, f = __ballot(top >= kFineFrom) != 0ull;
+    if (lane_id() == 0) {
+        if (w) L.wide = 1;
+        if (f) L.fine = 1;
+    }
+}
 
 // Solves the points 0 .. cnt-1 of L (cnt >= 1; WHOLE) or the chain from A at
 // position ia to B at ib (both below cnt) over every other position, all of
@@ -212,10 +224,10 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bo
         L.beat[0] = 0; L.beat[1] = 0;
         L.live[0] = cnt; L.live[1] = 0;
         L.map[0] = 0;
-        L.wide = 0;
+        L.wide = 0; L.fine = 0;
     }
     lds_barrier();
-    bool big = false;
+    float top_abs = 0.0f;
     // the first segment's "farthest point" is B itself: its children are the
     // sides of A -> B and, for a set, of B -> A
     int ic = ib;
@@ -226,7 +238,7 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bo
         for (int r = 0; r < R; ++r) {
             const int i = t + T * r;
             const float2 p = i < cnt ? L.xy[i] : make_float2(0.0f, 0.0f);
-            big |= fmaxf(fabsf(p.x), fabsf(p.y)) > kWideFrom;
+            top_abs = fmaxf(top_abs, fmaxf(fabsf(p.x), fabsf(p.y)));
             // (+ 0.0f: -0 counts as +0)
             k[r] = ((uint64_t)order_key(p.x + 0.0f) << 32) | order_key(p.y + 0.0f);
             if (i < cnt) {
@@ -234,7 +246,7 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bo
                 hi = k[r] > hi ? k[r] : hi;
             }
         }
-        if (__ballot(big) && lane == 0) L.wide = 1;
+        note_scale(L, top_abs);
         lo = wave_min_u64(lo);
         hi = wave_max_u64(hi);
         if (lane == 63) {
@@ -265,9 +277,9 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bo
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int i = t + T * r;
-            if (i < cnt) big |= fmaxf(fabsf(L.xy[i].x), fabsf(L.xy[i].y)) > kWideFrom;
+            if (i < cnt) top_abs = fmaxf(top_abs, fmaxf(fabsf(L.xy[i].x), fabsf(L.xy[i].y)));
         }
-        if (__ballot(big) && lane == 0) L.wide = 1;
+        note_scale(L, top_abs);
     }
     if (t == 0) {
         LSegIdx g;
@@ -276,7 +288,7 @@ __device__ __forceinline__ int solve(SolveLds<P>& L, int cnt, int ia, int ib, bo
     }
     lds_barrier();
     // the bounds of areas in float64, where float32 has none (or may not be asked)
-    const bool wide = f64 || L.wide != 0;
+    const bool wide = f64 || L.wide != 0 || L.fine == 0;
     int nodes = WHOLE ? 1 : 0;  // (pass 0 adds B to a ring, or counts A)
     int pass = 0;
     for (;; ++pass) {

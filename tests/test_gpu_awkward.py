@@ -362,7 +362,7 @@ def test_overflowing_areas_are_elected_by_bounds(H, n, mode):
     H.set_precision(mode)
     try:
         for name, unit in (("circles", two), ("disk", workloads.disk(n, 3)), ("square", workloads.square(n, 4))):
-            for scale in (1.0, 2.0 ** 62, 2.0 ** 90, 2.0 ** 125):
+            for scale in (2.0 ** -98, 2.0 ** -70, 1.0, 2.0 ** 62, 2.0 ** 90, 2.0 ** 125):
                 say(f"areas by float64 bounds: {name} n={n} scale={scale:.3g} mode={mode}")
                 xy = (unit.astype(np.float64) * scale).astype(np.float32)
                 want = hull(xy)
