@@ -79,7 +79,7 @@ typedef struct sqh_ctx sqh_ctx;
  * phase ends at a grid-wide barrier, so they partition ms_kernel).
  * A call that the workgroup-local kernels finish (small sets, sets past the
  * sieve, rings, batches) has no such phases: ms_seed .. ms_emit and pass_ms
- * are 0, ms_total and ms_kernel are from the first kernel's start to the last
+ * are 0 (sqh_set_local turns those kernels off), ms_total and ms_kernel are from the first kernel's start to the last
  * one's end by that clock, first_survivors counts the points the sieve left
  * (those of a small set that entered its first pass, all points of a ring),
  * and the passes are those of the last solve. */
@@ -140,8 +140,9 @@ int sqh_set_precision(sqh_ctx *ctx, int mode);
  * input) reads its input once past a sieve, or, if it is a ring of points,
  * cuts it into wedges; what neither takes runs its first phases and passes
  * over few large segments as ordinary launches that never wait for one
- * another, and the cooperative passes kernel for what they leave. Off, and
- * in graphs, such a set runs on the general path. The output is identical
+ * another, and the cooperative passes kernel for what they leave (graphs have
+ * these kernels from the start). Off, such a set runs on the general path. The
+ * output is identical
  * either way. Returns SQH_OK or SQH_EINVAL.
  */
 int sqh_set_streaming(sqh_ctx *ctx, int on);

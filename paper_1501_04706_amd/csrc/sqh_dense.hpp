@@ -26,7 +26,7 @@ constexpr int kDenseMaxK = 1024;   // pockets of one set
 constexpr int kDenseTarget = 150;  // points per pocket aimed at: most pockets fit a wave's 254 (larger ones go to larger solvers)
 
 // One pocket: its points are slots [off, off + len) of the pocket array
-// (three words each: x, y, index); once solved, the first len of them are its
+// (16 bytes each: x, y, index, nothing); once solved, the first len of them are its
 // nodes, v_k first.
 struct Pocket {
     float ax, ay, bx, by;    // v_k, v_{k+1}

@@ -108,7 +108,8 @@ bool make_layout(int64_t N, int64_t nsets, Layout& L)
     L.sv = take(sizeof(int) * 4);
     L.info = take(sizeof(HullInfo));
     // pre-filter of a single hull: corners, the kept subset and its indices
-    L.ext = take(sizeof(uint64_t) * 8 * (size_t)kMaxGrid);
+    // (also the control block of a batch)
+    L.ext = take(std::max(sizeof(uint64_t) * 8 * (size_t)kMaxGrid, batch_ctl_bytes()));
     L.xy2 = take(sizeof(float2) * (size_t)std::max<int64_t>(N, 1));
     L.ids2 = take(sizeof(int) * (size_t)std::max<int64_t>(N, 1));
     L.gs2 = take(sizeof(int) * 2);
