@@ -21,8 +21,8 @@
 //
 // The passes of the streaming path kept nearly every point of a circle for 9
 // of its 16 passes: 1530 us for 5M points. Here each point is read four times
-// and written twice: rays 18, count 18, scan 15, scatter 43, cut 55, pockets
-// 115, wedges 34, join 41, emit 10 us, and 32 us of the sieve's kernels that
+// and written twice: rays 19, count 17, scan 16, scatter 41, cut 56, pockets
+// 113, wedges 31, join 42, emit 6 us, and 35 us of the sieve's kernels that
 // found the ring. The pockets are bound by instruction issue (the sort's 28
 // steps and about 8 rounds of 100 points each), the rest by latency.
 #pragma once
